@@ -143,7 +143,8 @@ def _others(k, groups):
 
 # ------------------------------------------------------------------ one pass
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """The seed's tensors and the generator they were drawn from."""
     dev = torch.device("cuda:0")
     gen = torch.Generator(device=dev)
     gen.manual_seed(int(seed))
@@ -159,10 +160,40 @@ def prepare(case, seed):
         at.mul_(math.sqrt(2.0 / (l["c_in"] * l["khw"])))
         if case["spread"]:
             at.mul_(torch.pow(10.0, torch.rand(l["c_out"], 1, generator=gen, device=dev) * 4 - 3))
-    s = {"form": form, "plan": hs.Plan(cols)}
+    x = {"W": [normal(math.sqrt(1e-3)).add_(base) for _ in range(R)] if R > 1 else [base]}
+    x["U"] = normal(1e-2)
+    if form in ("weighted", "norms", "retrain", "union"):
+        x["Zg"], x["Vd"] = normal(0.05), normal(0.01)
+    if form == "norms":
+        x["Zp"] = normal(0.05)
+    return x, gen
+
+
+def _other_mask(layers, mask, gen):
+    """The mask of a second node that agrees with `mask` on all but a fifth of the groups."""
+    other, at = mask.clone(), 0
+    for l in layers:
+        parts = {hs.MODE_NONE: [(l["c_out"], l["c_out"])], hs.MODE_FILTER: [(l["c_out"], l["k"])],
+                 hs.MODE_CHANNEL: [(l["c_in"], l["k"])],
+                 hs.MODE_BOTH: [(l["c_out"], l["k"]), (l["c_in"], l["k_in"])]}[l["mode"]]
+        for groups, k in parts:
+            more = _others(k, groups)
+            if more:
+                rank = torch.rand(groups, generator=gen, device=mask.device) + 2.0 * other[at:at + groups]
+                other[at + torch.argsort(rank)[:more]] = 1
+            at += groups
+    return other
+
+
+RHO1, RHO2, LAMBDA, NODES = 1.5e-3, 1.5e-4, 1e-4, 16         # penalties of Eq. (9), the same on every layer
+
+
+def prepare(case, seed):
+    x, gen = _inputs(case, seed)
+    cols, n = _table(case)
+    layers, R, form, dev = _rows(cols), case["R"], case["form"], x["U"].device
+    s = {"form": form, "plan": hs.Plan(cols), **x}
     plan = s["plan"]
-    s["W"] = [normal(math.sqrt(1e-3)).add_(base) for _ in range(R)] if R > 1 else [base]
-    s["U"] = normal(1e-2)
     s["Z"] = torch.zeros(n, device=dev)
     s["dst"] = torch.zeros(n, device=dev)
     s["mask"] = torch.zeros(plan.groups_total, dtype=torch.uint8, device=dev)
@@ -171,8 +202,7 @@ def prepare(case, seed):
     s["kept"] = torch.zeros(plan.groups_total, dtype=torch.int32, device=dev)
     s["ws"] = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device=dev)
     if form in ("weighted", "norms", "retrain", "union"):
-        s["Zg"], s["Vd"] = normal(0.05), normal(0.01)
-        a, b = hs.hsadmm_node_coefficients([1.5e-3] * len(layers), [1.5e-4] * len(layers), 1e-4, 16, R)
+        a, b = hs.hsadmm_node_coefficients([RHO1] * len(layers), [RHO2] * len(layers), LAMBDA, NODES, R)
         hs.hsadmm_plan_set_node_weights(plan, a, b)
         s["coef"] = torch.tensor([x for ab in zip(a, b) for x in ab], device=dev)
         s["norms"] = torch.zeros(4 * len(layers), dtype=torch.float64, device=dev)
@@ -181,8 +211,6 @@ def prepare(case, seed):
         s["sel_prev"], s["sel"] = (torch.zeros(plan.groups_total, dtype=torch.int32, device=dev) for _ in range(2))
         hs.hsadmm_step(plan, s["W"], U=s["U"], U_out=s["U_out"], Z=s["Z"], mask=s["mask"], sel=s["sel_prev"],
                        workspace=s["ws"])
-    elif form == "norms":
-        s["Zp"] = normal(0.05)
     elif form in ("retrain", "union"):
         # the masks the dynamic phase ended with, and the iteration that follows it
         hs.hsadmm_project_weighted(plan, s["W"], s["U"], s["Zg"], s["Vd"], s["Z"], None, s["mask"], None, s["ws"])
@@ -190,19 +218,8 @@ def prepare(case, seed):
             hs.hsadmm_retrain_project(plan, s["W"], s["U"], s["Zg"], s["Vd"], s["Z"], None, s["mask"], False,
                                       s["packed"], s["off"], s["kept"], s["norms"], s["ws"])
         else:
-            # the other node agrees on all but a fifth of the groups
-            other, at = s["mask"].clone(), 0
-            for l in layers:
-                parts = {hs.MODE_NONE: [(l["c_out"], l["c_out"])], hs.MODE_FILTER: [(l["c_out"], l["k"])],
-                         hs.MODE_CHANNEL: [(l["c_in"], l["k"])],
-                         hs.MODE_BOTH: [(l["c_out"], l["k"]), (l["c_in"], l["k_in"])]}[l["mode"]]
-                for groups, k in parts:
-                    more = _others(k, groups)
-                    if more:
-                        rank = torch.rand(groups, generator=gen, device=dev) + 2.0 * other[at:at + groups]
-                        other[at + torch.argsort(rank)[:more]] = 1
-                    at += groups
-            s["other"], s["union"] = other, torch.zeros_like(other)
+            s["other"] = _other_mask(layers, s["mask"], gen)
+            s["union"] = torch.zeros_like(s["other"])
     return s
 
 
@@ -271,3 +288,132 @@ def tolerance(case):
     stay the same.  Against the same steps in fp64 the outputs are off by 3e-8 to 1.3e-7 in the 2-norm and by up to
     1e-5 in the worst element (a kept group's dual is what rounding leaves of it); four times that is allowed."""
     return {"rel": 5e-7, "max": 4e-5}
+
+
+# ------------------------------------------------------------------ the same pass in 64 bits
+
+def exact(case, seed):
+    """What `run` returns for these inputs, from the definition of the step in plain torch, 64 bits throughout."""
+    x, gen = _inputs(case, seed)
+    cols, n = _table(case)
+    layers, R, form = _rows(cols), case["R"], case["form"]
+    mean = torch.zeros_like(x["U"], dtype=torch.float64)
+    for w in x["W"]:
+        mean += w
+    mean /= R
+    U = x["U"].double()
+    dev = U.device
+    a, b = 1.0, 0.0
+    if "Zg" in x:
+        gamma = LAMBDA / NODES + R * RHO1 + RHO2
+        a, b = R * RHO1 / gamma, RHO2 / gamma
+        z_old, v_old = x["Zg"].double(), x["Vd"].double()
+
+    def part(t, l):
+        return t[l["elem_off"]:l["elem_off"] + l["c_out"] * l["c_in"] * l["khw"]].view(l["c_out"], l["c_in"], l["khw"])
+
+    def candidate(u):
+        return mean + u if b == 0.0 else a * (mean + u) + b * (z_old - v_old)
+
+    def largest(norms, k):
+        m = torch.zeros(norms.numel(), dtype=torch.uint8, device=dev)
+        m[torch.topk(norms, k).indices] = 1
+        return m
+
+    def selection(c):
+        """Every layer's masks: [filters], [channels] or [filters, channels]."""
+        masks = []
+        for l in layers:
+            sq = part(c, l).square().sum(2)
+            if l["mode"] == hs.MODE_NONE:
+                masks.append([torch.ones(l["c_out"], dtype=torch.uint8, device=dev)])
+            elif l["mode"] == hs.MODE_CHANNEL:
+                masks.append([largest(sq.sum(0), l["k"])])
+            else:
+                f = largest(sq.sum(1), l["k"])
+                masks.append([f] if l["mode"] == hs.MODE_FILTER else [f, largest((sq * f[:, None]).sum(0), l["k_in"])])
+        return masks
+
+    def flat(masks):
+        return torch.cat([m for ms in masks for m in ms])
+
+    def sets(l, ms):
+        """Indices of the layer's kept filters and channels."""
+        f = torch.arange(l["c_out"], device=dev) if l["mode"] == hs.MODE_CHANNEL else ms[0].nonzero().flatten()
+        ch = ms[-1].nonzero().flatten() if l["mode"] in (hs.MODE_CHANNEL, hs.MODE_BOTH) else torch.arange(l["c_in"], device=dev)
+        return f, ch
+
+    def keep(t, masks):
+        out = torch.zeros_like(t)
+        for l, ms in zip(layers, masks):
+            f, ch = (i.view(s) for i, s in zip(sets(l, ms), ((-1, 1), (1, -1))))
+            part(out, l)[f, ch] = part(t, l)[f, ch]
+        return out
+
+    def dual(u, z):
+        out = u.clone()                                          # (the padding between layers is nobody's)
+        for l in layers:
+            part(out, l).copy_(part(u, l) + (part(mean, l) - part(z, l)))
+        return out
+
+    def shrink(t, masks):
+        """packed, off and kept."""
+        packed = torch.zeros(sum(l["c_out"] * l["c_in"] * l["khw"] for l in layers), dtype=torch.float64, device=dev)
+        kept = torch.zeros(sum(m.numel() for ms in masks for m in ms), dtype=torch.int32, device=dev)
+        off, at = [0], 0
+        for l, ms in zip(layers, masks):
+            f, ch = sets(l, ms)
+            block = part(t, l)[f.view(-1, 1), ch.view(1, -1)].flatten()
+            packed[off[-1]:off[-1] + block.numel()] = block
+            off.append(off[-1] + block.numel())
+            for m in ms:
+                i = m.nonzero().flatten()
+                kept[at:at + i.numel()] = i.int()
+                at += i.numel()
+        return packed, torch.tensor(off, dtype=torch.int64, device=dev), kept
+
+    def ranks(masks):
+        return torch.cat([torch.where(m > 0, m.int().cumsum(0).int() - 1, -1) for ms in masks for m in ms]).int()
+
+    def sq(t, minus=None):
+        return [float((part(t, l) - part(minus, l)).square().sum()) for l in layers]
+
+    masks = selection(candidate(U))
+    if form == "union":
+        Z = keep(candidate(U), masks)
+        other, at = _other_mask(layers, flat(masks), gen), 0
+        both = []
+        for ms in masks:
+            row = []
+            for m in ms:
+                row.append(torch.maximum(m, other[at:at + m.numel()]))
+                at += m.numel()
+            both.append(row)
+        z = keep(Z + v_old, both)
+        return [flat(both), *shrink(Z + v_old, both), z, _on_layers(layers, v_old, Z - z)]
+    z_before = x["Zp"].double() if form == "norms" else None
+    if form == "retrain":                                        # two iterations before the one that is timed
+        for _ in range(2):
+            z_before = keep(candidate(U), masks)
+            U = dual(U, z_before)
+    Z = keep(candidate(U), masks)
+    U = dual(U, Z)
+    if form in ("step", "predicted"):
+        head = [U, Z, flat(masks)] + ([ranks(masks)] if form == "predicted" else [])
+        return head + [*shrink(Z, masks), Z]
+    z = keep(Z + v_old, masks)
+    out = [U, Z] + ([] if form == "retrain" else [flat(masks)]) + [*shrink(Z + v_old, masks), z,
+                                                                   _on_layers(layers, v_old, Z - z)]
+    if form == "weighted":
+        return out
+    primal = [sum(v) for v in zip(*(sq(w.double(), Z) for w in x["W"]))]
+    return out + [torch.tensor(primal + sq(Z, z_before) + sq(Z, z) + sq(z, z_old), dtype=torch.float64, device=dev)]
+
+
+def _on_layers(layers, t, d):
+    """t + d where there are layers, t in the padding between them."""
+    out = t.clone()
+    for l in layers:
+        at = slice(l["elem_off"], l["elem_off"] + l["c_out"] * l["c_in"] * l["khw"])
+        out[at] += d[at]
+    return out
