@@ -187,9 +187,10 @@ int ceil_pow2(int x)
 void add_row_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int mode)
 {
     const bool vec = (d.row_len % 4) == 0;
-    const int units = vec ? d.row_len / 4 : d.row_len;          // accesses per row
+    // 128-bit accesses per row; the last one to three floats of a ragged row go to a lane each, so it gets four lanes
+    const int units = vec ? d.row_len / 4 : std::max(4, d.row_len / 4);
     int lpr, bundle;
-    if (d.row_len >= kWideRow && vec) { lpr = kBlock; bundle = 1; }
+    if (d.row_len >= kWideRow) { lpr = kBlock; bundle = 1; }
     else { lpr = units >= kWave ? kWave : ceil_pow2(units); bundle = kWaves * (kWave / lpr); }
     int64_t want = kTileElems / (int64_t)d.row_len;
     if (want < bundle) want = bundle;
@@ -216,7 +217,7 @@ void add_row_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int
 // Tiles of (rows_per_block rows) x (one column strip); d.n_rowblocks must have been set for the same block height.
 void add_tile_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int rows_per_block)
 {
-    const bool vec = (d.row_len % 4) == 0;
+    const bool vec = d.row_len >= 4;
     const int strip_cols = kWave * (vec ? 4 : 1);
     const int nstrips = (d.row_len + strip_cols - 1) / strip_cols;
     for (int r0 = 0; r0 < d.c_out; r0 += rows_per_block) {

@@ -21,6 +21,7 @@ constexpr int kTopkRegs = 8;                // the selection keeps up to 8 keys 
 constexpr int kVersion = 20100;          // 2.1.0 (major * 10000 + minor * 100 + patch)
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_at4 __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any float's address
 
 struct DevLayer {
     int64_t elem_off;
@@ -125,7 +126,8 @@ struct WorkItem {
     int32_t nr;         // rows
     int32_t row_len;    // c_in * khw
     int32_t lpr;        // row item: lanes sharing a row, power of two <= 64, or 256 (whole workgroup)
-    int32_t flags;      // bits 0-1: mode; bit 2: 128-bit path (row_len % 4 == 0)
+    int32_t flags;      // bits 0-1: mode; bit 2: row item: whole 128-bit words (row_len % 4 == 0);
+                        // tile: four columns per lane (row_len >= 4), else one
     int32_t col0;       // tile: first column of the strip; row item: 0
     int32_t khw;
     int32_t layer;
@@ -139,6 +141,15 @@ __device__ __forceinline__ int item_mode(const WorkItem& it) { return it.flags &
 // modes whose packed rows hold a subset of the columns (CHANNEL, BOTH)
 __device__ __forceinline__ bool mode_has_channels(int mode) { return (mode & HSADMM_MODE_CHANNEL) != 0; }
 __device__ __forceinline__ bool item_vec(const WorkItem& it) { return (it.flags & 4) != 0; }
+
+// First column of a lane that owns vw adjacent columns of a tile.  A lane whose four columns would pass the end of the
+// row owns the row's last four instead: it forms, adds up and stores some of its neighbour's columns a second time,
+// from the same inputs and in the same order, so both store the same bits.  (Tiles read nothing that they write.)
+__device__ __forceinline__ int tile_col(const WorkItem& it, int lane, int vw)
+{
+    const int col = it.col0 + lane * vw;
+    return vw == 4 ? min(col, it.row_len - 4) : col;
+}
 
 struct ProjectArgs {
     const float* W[HSADMM_MAX_REPLICAS];
@@ -157,9 +168,11 @@ struct ProjectArgs {
     double* respart;      // per row item: 4 partial sums of squared residuals (kernels that also form the norms)
 };
 
-// Streaming (touch-once) accesses.
-__device__ __forceinline__ v4f ld4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p)); }
-__device__ __forceinline__ void st4(float* p, v4f v) { __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(p)); }
+// Streaming (touch-once) accesses.  ld4 / st4 take any address of a float: rows whose length is not a multiple of four
+// floats start anywhere, and 128-bit accesses that are aligned to 4 bytes only still move such a row at more than twice
+// the rate of 32-bit ones (a wave touches one cache line more).
+__device__ __forceinline__ v4f ld4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const v4f_at4*>(p)); }
+__device__ __forceinline__ void st4(float* p, v4f v) { __builtin_nontemporal_store(v, reinterpret_cast<v4f_at4*>(p)); }
 __device__ __forceinline__ float ld1(const float* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void st1(float* p, float v) { __builtin_nontemporal_store(v, p); }
 // 128-bit access to an address that is only 4-byte aligned (segments of the packed buffer).

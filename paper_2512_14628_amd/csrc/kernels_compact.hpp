@@ -192,16 +192,13 @@ __device__ __forceinline__ void gather_item(const WorkItem& it, const float* src
             const float* s = src + it.base + (int64_t)rr * row_len;
             const float* s1 = SUM ? src1 + it.base + (int64_t)rr * row_len : nullptr;
             float* d = out + (int64_t)p * row_len;
-            if (item_vec(it)) {
-                const int nchunk = row_len >> 2;
-                for (int c = j; c < nchunk; c += lpr) {
-                    v4f v = ld4(s + 4 * c);
-                    if (SUM) v = v + ld4(s1 + 4 * c);
-                    st4u(d + 4 * c, v);
-                }
-            } else {
-                for (int c = j; c < row_len; c += lpr) d[c] = SUM ? s[c] + s1[c] : s[c];
+            const int nchunk = row_len >> 2;
+            for (int c = j; c < nchunk; c += lpr) {
+                v4f v = ld4(s + 4 * c);
+                if (SUM) v = v + ld4(s1 + 4 * c);
+                st4u(d + 4 * c, v);
             }
+            if (const int c = (row_len & ~3) + j; c < row_len) d[c] = SUM ? s[c] + s1[c] : s[c];
         }
     } else {
         // packed row o holds the kept channels' khw-blocks in ascending channel order: packed column
@@ -413,14 +410,10 @@ __global__ __launch_bounds__(kBlock) void expand_scatter(const WorkItem* __restr
             const int p = pos[it.g0 + rr];
             const int64_t d = it.base + (int64_t)rr * row_len;
             const float* s = in + (int64_t)(p < 0 ? 0 : p) * row_len;
-            if (item_vec(it)) {
-                const int nchunk = row_len >> 2;
-                if (p >= 0) for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, ld4u(s + 4 * c));
-                else for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, zero4);
-            } else {
-                if (p >= 0) for (int c = j; c < row_len; c += lpr) put1(d + c, s[c]);
-                else for (int c = j; c < row_len; c += lpr) put1(d + c, 0.f);
-            }
+            const int nchunk = row_len >> 2;
+            if (p >= 0) for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, ld4u(s + 4 * c));
+            else for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, zero4);
+            if (const int c = (row_len & ~3) + j; c < row_len) put1(d + c, p >= 0 ? s[c] : 0.f);
         }
     } else {
         // a wave takes a row of dst; a lane fills 4 adjacent columns (kept ones from the packed row,
@@ -432,7 +425,7 @@ __global__ __launch_bounds__(kBlock) void expand_scatter(const WorkItem* __restr
         const int in_len = kc * khw;
         const DivKhw div(khw);
         const int32_t* pl = pos + (both ? it.aux : (int64_t)it.g0);
-        const int quads = item_vec(it) ? (row_len >> 2) : 0;
+        const int quads = row_len >> 2;
         // Two 128-bit stores in flight per lane: of two rows of the wave, or, when only one row is left for it, of two
         // column groups of that row.
         constexpr int kSlots = 2;

@@ -84,80 +84,77 @@ __device__ __forceinline__ v4f both_candidate(const ProjectArgs& a, int64_t e, c
 // order) with the row written in its predicted final form instead of the parked mean.
 template <int R, bool WEIGHTED>
 __device__ __forceinline__ double pass1_row_both_hinted(const ProjectArgs& a, int Rrt, int64_t base, int row_len,
-                                                        bool vec, int j, int step, bool row_kept,
+                                                        int j, int step, bool row_kept,
                                                         const int32_t* __restrict__ hp_c, const DivKhw& div, int k_in,
                                                         float* drow, float al, float bl)
 {
     const int RR = R > 0 ? R : Rrt;
     double acc = 0.0;
-    if (vec) {
-        const int nchunk = row_len >> 2;
-        int c = j;
-        for (; c + step < nchunk; c += 2 * step) {
-            const int col0 = c << 2, col1 = (c + step) << 2;
-            const int64_t e0 = base + col0, e1 = base + col1;
-            v4f s0 = ld4(a.W[0] + e0), s1 = ld4(a.W[0] + e1);
+    const int nchunk = row_len >> 2;
+    int c = j;
+    for (; c + step < nchunk; c += 2 * step) {
+        const int col0 = c << 2, col1 = (c + step) << 2;
+        const int64_t e0 = base + col0, e1 = base + col1;
+        v4f s0 = ld4(a.W[0] + e0), s1 = ld4(a.W[0] + e1);
 #pragma unroll
-            for (int r = 1; r < RR; ++r) {
-                const v4f w0 = ld4(a.W[r] + e0), w1 = ld4(a.W[r] + e1);
-                s0 = s0 + w0;
-                s1 = s1 + w1;
-            }
-            const v4f u0 = ld4(a.Ur + e0), u1 = ld4(a.Ur + e1);
-            bool k0[4], k1[4];
-            int p0[4], p1[4];
-            quad_predicted_cols(hp_c, div, col0, k_in, k0, p0);
-            quad_predicted_cols(hp_c, div, col1, k_in, k1, p1);
-            const v4f wb0 = s0 * a.inv_R, wb1 = s1 * a.inv_R;
-            v4f vd0, vd1;
-            const v4f v0 = both_candidate<WEIGHTED>(a, e0, wb0, u0, al, bl, vd0);
-            const v4f v1 = both_candidate<WEIGHTED>(a, e1, wb1, u1, al, bl, vd1);
-            both_put<WEIGHTED>(a, e0, wb0, u0, v0, vd0, row_kept, k0, p0, drow);
-            both_put<WEIGHTED>(a, e1, wb1, u1, v1, vd1, row_kept, k1, p1, drow);
-            acc = sq4(acc, v0);
-            acc = sq4(acc, v1);
+        for (int r = 1; r < RR; ++r) {
+            const v4f w0 = ld4(a.W[r] + e0), w1 = ld4(a.W[r] + e1);
+            s0 = s0 + w0;
+            s1 = s1 + w1;
         }
-        if (c < nchunk) {
-            const int col = c << 2;
-            const int64_t e = base + col;
-            v4f s = ld4(a.W[0] + e);
+        const v4f u0 = ld4(a.Ur + e0), u1 = ld4(a.Ur + e1);
+        bool k0[4], k1[4];
+        int p0[4], p1[4];
+        quad_predicted_cols(hp_c, div, col0, k_in, k0, p0);
+        quad_predicted_cols(hp_c, div, col1, k_in, k1, p1);
+        const v4f wb0 = s0 * a.inv_R, wb1 = s1 * a.inv_R;
+        v4f vd0, vd1;
+        const v4f v0 = both_candidate<WEIGHTED>(a, e0, wb0, u0, al, bl, vd0);
+        const v4f v1 = both_candidate<WEIGHTED>(a, e1, wb1, u1, al, bl, vd1);
+        both_put<WEIGHTED>(a, e0, wb0, u0, v0, vd0, row_kept, k0, p0, drow);
+        both_put<WEIGHTED>(a, e1, wb1, u1, v1, vd1, row_kept, k1, p1, drow);
+        acc = sq4(acc, v0);
+        acc = sq4(acc, v1);
+    }
+    if (c < nchunk) {
+        const int col = c << 2;
+        const int64_t e = base + col;
+        v4f s = ld4(a.W[0] + e);
 #pragma unroll
-            for (int r = 1; r < RR; ++r) s = s + ld4(a.W[r] + e);
-            const v4f u = ld4(a.Ur + e);
-            bool k[4];
-            int p[4];
-            quad_predicted_cols(hp_c, div, col, k_in, k, p);
-            const v4f wb = s * a.inv_R;
-            v4f vd;
-            const v4f v = both_candidate<WEIGHTED>(a, e, wb, u, al, bl, vd);
-            both_put<WEIGHTED>(a, e, wb, u, v, vd, row_kept, k, p, drow);
-            acc = sq4(acc, v);
+        for (int r = 1; r < RR; ++r) s = s + ld4(a.W[r] + e);
+        const v4f u = ld4(a.Ur + e);
+        bool k[4];
+        int p[4];
+        quad_predicted_cols(hp_c, div, col, k_in, k, p);
+        const v4f wb = s * a.inv_R;
+        v4f vd;
+        const v4f v = both_candidate<WEIGHTED>(a, e, wb, u, al, bl, vd);
+        both_put<WEIGHTED>(a, e, wb, u, v, vd, row_kept, k, p, drow);
+        acc = sq4(acc, v);
+    }
+    if (const int c = (row_len & ~3) + j; c < row_len) {
+        const int64_t e = base + c;
+        float s = ld1(a.W[0] + e);
+        for (int r = 1; r < RR; ++r) s = s + ld1(a.W[r] + e);
+        const float u = ld1(a.Ur + e);
+        const float wb = s * a.inv_R;
+        float v = wb + u;
+        float vd = 0.f;
+        if (WEIGHTED) {
+            vd = ld1(a.Vd + e);
+            const float q = ld1(a.Zg + e) - vd;
+            const float at = v * al;
+            const float bq = q * bl;
+            v = at + bq;
         }
-    } else {
-        for (int c = j; c < row_len; c += step) {
-            const int64_t e = base + c;
-            float s = ld1(a.W[0] + e);
-            for (int r = 1; r < RR; ++r) s = s + ld1(a.W[r] + e);
-            const float u = ld1(a.Ur + e);
-            const float wb = s * a.inv_R;
-            float v = wb + u;
-            float vd = 0.f;
-            if (WEIGHTED) {
-                vd = ld1(a.Vd + e);
-                const float q = ld1(a.Zg + e) - vd;
-                const float at = v * al;
-                const float bq = q * bl;
-                v = at + bq;
-            }
-            const int ch = div(c);
-            const int r = hp_c[ch];
-            const float z = (row_kept && r >= 0) ? v : 0.f;
-            st1(a.Z + e, z);
-            st1(a.U + e, u + (wb - z));
-            if (a.Wbar) st1(a.Wbar + e, wb);
-            if (drow && r >= 0 && r < k_in) drow[r * div.khw + (c - ch * div.khw)] = WEIGHTED ? z + vd : z;
-            acc = fma((double)v, (double)v, acc);
-        }
+        const int ch = div(c);
+        const int r = hp_c[ch];
+        const float z = (row_kept && r >= 0) ? v : 0.f;
+        st1(a.Z + e, z);
+        st1(a.U + e, u + (wb - z));
+        if (a.Wbar) st1(a.Wbar + e, wb);
+        if (drow && r >= 0 && r < k_in) drow[r * div.khw + (c - ch * div.khw)] = WEIGHTED ? z + vd : z;
+        acc = fma((double)v, (double)v, acc);
     }
     return acc;
 }
@@ -177,7 +174,6 @@ __device__ __forceinline__ void project_rows_both_hinted(const WorkItem& it, con
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     const DivKhw div(it.khw);
     const int k_in = h.layers[it.layer].k_in;
     const int packed_row_len = k_in * it.khw;
@@ -201,7 +197,7 @@ __device__ __forceinline__ void project_rows_both_hinted(const WorkItem& it, con
                 bool kept;
                 float* drow;
                 prediction(rr, kept, drow);
-                acc = pass1_row_both_hinted<R, WEIGHTED>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, vec, j, lpr,
+                acc = pass1_row_both_hinted<R, WEIGHTED>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, j, lpr,
                                                          kept, hp_c, div, k_in, drow, al, bl);
             }
             acc = wave_xor_sum(acc, lpr);
@@ -213,7 +209,7 @@ __device__ __forceinline__ void project_rows_both_hinted(const WorkItem& it, con
             bool kept;
             float* drow;
             prediction(rr, kept, drow);
-            double acc = pass1_row_both_hinted<R, WEIGHTED>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, vec,
+            double acc = pass1_row_both_hinted<R, WEIGHTED>(a, Rrt, it.base + (int64_t)rr * row_len, row_len,
                                                             threadIdx.x, kBlock, kept, hp_c, div, k_in, drow, al, bl);
             acc = wave_xor_sum(acc, kWave);
             if (lane == 0) wsum[wave] = acc;
@@ -251,8 +247,8 @@ __global__ __launch_bounds__(kBlock) void composite_colsums_hinted(const WorkIte
     const int row_len = it.row_len;
     const bool vec = item_vec(it);
     const int vw = vec ? 4 : 1;
-    const int col = it.col0 + lane * vw;
-    const bool in = col < row_len;
+    const bool in = it.col0 + lane * vw < row_len;
+    const int col = tile_col(it, lane, vw);
     const uint8_t* mf = mask + it.g0 + it.row0;                  // filter bytes of the tile's rows
     const int32_t* hp_f = sel_prev + it.g0 + it.row0;            // ... and their predictions
     const int32_t* hp_c = sel_prev + it.g0 + layers[it.layer].c_out;
@@ -351,13 +347,12 @@ __device__ __forceinline__ void hinted_repair_rows(const WorkItem& it, const Pro
                                                    const int32_t* __restrict__ pos, bool stash, float* packed)
 {
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
     const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
     const int rows_at_once = kBlock / lpr;
     const int sub = threadIdx.x / lpr;
     const int j = threadIdx.x - sub * lpr;
-    const int nchunk = row_len >> 2;
+    const int nchunk = row_len >> 2, tail = row_len & ~3;
     float* const U = a.U;
     float* const Z = a.Z;
     for (int rr = sub; rr < it.nr; rr += rows_at_once) {
@@ -368,46 +363,40 @@ __device__ __forceinline__ void hinted_repair_rows(const WorkItem& it, const Pro
         float* pk = (packed && kept) ? packed + (int64_t)pn * row_len : nullptr;
         if (pred_kept && kept) {
             if (!pk || pn == hp) continue;                       // packed in pass 1 already, at this rank
-            if (vec) for (int c = j; c < nchunk; c += lpr) st4u(pk + 4 * c, ld4(Z + base + 4 * c));
-            else for (int c = j; c < row_len; c += lpr) pk[c] = ld1(Z + base + c);
+            for (int c = j; c < nchunk; c += lpr) st4u(pk + 4 * c, ld4(Z + base + 4 * c));
+            if (const int c = tail + j; c < row_len) pk[c] = ld1(Z + base + c);
         } else if (!pred_kept && !kept) {
             if (!stash) continue;
-            if (vec) for (int c = j; c < nchunk; c += lpr) st4(Z + base + 4 * c, zero4);
-            else for (int c = j; c < row_len; c += lpr) st1(Z + base + c, 0.f);
+            for (int c = j; c < nchunk; c += lpr) st4(Z + base + 4 * c, zero4);
+            if (const int c = tail + j; c < row_len) st1(Z + base + c, 0.f);
         } else if (pred_kept) {
-            if (vec) {
-                for (int c = j; c < nchunk; c += lpr) {
-                    const int64_t e = base + 4 * c;
-                    st4(U + e, ld4(Z + e));
-                    st4(Z + e, zero4);
-                }
-            } else {
-                for (int c = j; c < row_len; c += lpr) {
-                    st1(U + base + c, ld1(Z + base + c));
-                    st1(Z + base + c, 0.f);
-                }
+            for (int c = j; c < nchunk; c += lpr) {
+                const int64_t e = base + 4 * c;
+                st4(U + e, ld4(Z + e));
+                st4(Z + e, zero4);
+            }
+            if (const int c = tail + j; c < row_len) {
+                st1(U + base + c, ld1(Z + base + c));
+                st1(Z + base + c, 0.f);
             }
         } else if (stash) {
-            if (vec) {
-                for (int c = j; c < nchunk; c += lpr) {
-                    const int64_t e = base + 4 * c;
-                    const v4f v = ld4(U + e), d = ld4(Z + e);
-                    st4(Z + e, v);
-                    st4(U + e, d);
-                    if (pk) st4u(pk + 4 * c, v);
-                }
-            } else {
-                for (int c = j; c < row_len; c += lpr) {
-                    const float v = ld1(U + base + c), d = ld1(Z + base + c);
-                    st1(Z + base + c, v);
-                    st1(U + base + c, d);
-                    if (pk) pk[c] = v;
-                }
+            for (int c = j; c < nchunk; c += lpr) {
+                const int64_t e = base + 4 * c;
+                const v4f v = ld4(U + e), d = ld4(Z + e);
+                st4(Z + e, v);
+                st4(U + e, d);
+                if (pk) st4u(pk + 4 * c, v);
+            }
+            if (const int c = tail + j; c < row_len) {
+                const float v = ld1(U + base + c), d = ld1(Z + base + c);
+                st1(Z + base + c, v);
+                st1(U + base + c, d);
+                if (pk) pk[c] = v;
             }
         } else {
             // the same arithmetic on the same inputs as in pass 1, so the same bits (the keys are not taken again)
-            if (vec) for (int c = j; c < nchunk; c += lpr) (void)Cand<R>::one_h(a, Rrt, base, c << 2, true, false, pk);
-            else for (int c = j; c < row_len; c += lpr) (void)Cand<R>::scalar_h(a, Rrt, base, c, true, false, pk);
+            for (int c = j; c < nchunk; c += lpr) (void)Cand<R>::one_h(a, Rrt, base, c << 2, true, false, pk);
+            if (const int c = tail + j; c < row_len) (void)Cand<R>::scalar_h(a, Rrt, base, c, true, false, pk);
         }
     }
 }

@@ -214,26 +214,23 @@ struct Cand {
 // Sum of squares of the part of one row that lane j of `step` lanes owns (chunks j, j+step, ...),
 // accumulated in increasing chunk order.
 template <int R, bool PARK>
-__device__ __forceinline__ double pass1_row(const ProjectArgs& a, int Rrt, int64_t base, int row_len, bool vec,
+__device__ __forceinline__ double pass1_row(const ProjectArgs& a, int Rrt, int64_t base, int row_len,
                                             int j, int step)
 {
     double acc = 0.0;
-    if (vec) {
-        const int nchunk = row_len >> 2;
-        int c = j;
-        for (; c + step < nchunk; c += 2 * step) {
-            const int64_t e0 = base + ((int64_t)c << 2), e1 = base + ((int64_t)(c + step) << 2);
-            acc = PARK ? Cand<R>::park_two(a, Rrt, e0, e1, acc) : Cand<R>::two(a, Rrt, e0, e1, acc);
-        }
-        if (c < nchunk) {
-            const int64_t e = base + ((int64_t)c << 2);
-            acc = sq4(acc, PARK ? Cand<R>::park_one(a, Rrt, e) : Cand<R>::one(a, Rrt, e));
-        }
-    } else {
-        for (int c = j; c < row_len; c += step) {
-            const float v = PARK ? Cand<R>::park_scalar(a, Rrt, base + c) : Cand<R>::scalar(a, Rrt, base + c);
-            acc = fma((double)v, (double)v, acc);
-        }
+    const int nchunk = row_len >> 2;
+    int c = j;
+    for (; c + step < nchunk; c += 2 * step) {
+        const int64_t e0 = base + ((int64_t)c << 2), e1 = base + ((int64_t)(c + step) << 2);
+        acc = PARK ? Cand<R>::park_two(a, Rrt, e0, e1, acc) : Cand<R>::two(a, Rrt, e0, e1, acc);
+    }
+    if (c < nchunk) {
+        const int64_t e = base + ((int64_t)c << 2);
+        acc = sq4(acc, PARK ? Cand<R>::park_one(a, Rrt, e) : Cand<R>::one(a, Rrt, e));
+    }
+    if (const int c = (row_len & ~3) + j; c < row_len) {
+        const float v = PARK ? Cand<R>::park_scalar(a, Rrt, base + c) : Cand<R>::scalar(a, Rrt, base + c);
+        acc = fma((double)v, (double)v, acc);
     }
     return acc;
 }
@@ -249,7 +246,6 @@ __device__ __forceinline__ void project_rows(const WorkItem& it, const ProjectAr
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     if (it.lpr <= kWave) {
         const int lpr = it.lpr;
         const int rpw = kWave / lpr;
@@ -259,14 +255,14 @@ __device__ __forceinline__ void project_rows(const WorkItem& it, const ProjectAr
             const int rr = rb + sub;
             const bool active = rr < it.nr;
             double acc = 0.0;
-            if (active) acc = pass1_row<R, PARK>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, vec, j, lpr);
+            if (active) acc = pass1_row<R, PARK>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, j, lpr);
             acc = wave_xor_sum(acc, lpr);
             if (active && j == 0) a.key[it.g0 + rr] = acc;
         }
     } else {
         __shared__ double wsum[kWaves];
         for (int rr = 0; rr < it.nr; ++rr) {
-            double acc = pass1_row<R, PARK>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, vec, threadIdx.x, kBlock);
+            double acc = pass1_row<R, PARK>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, threadIdx.x, kBlock);
             acc = wave_xor_sum(acc, kWave);
             if (lane == 0) wsum[wave] = acc;
             __syncthreads();
@@ -299,8 +295,8 @@ __device__ __forceinline__ void project_tile(const WorkItem& it, const ProjectAr
     const int row_len = it.row_len;
     const bool vec = item_vec(it);
     const int vw = vec ? 4 : 1;
-    const int col = it.col0 + lane * vw;
-    const bool in = col < row_len;
+    const bool in = it.col0 + lane * vw < row_len;
+    const int col = tile_col(it, lane, vw);
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
     if (in) {
         int rr = wave;
@@ -388,21 +384,18 @@ struct HintArgs {
 // pass1_row with the outputs of a row written in the form its prediction makes final (see Cand::put_h); the sum of
 // squares is taken in the same order as there, so the keys carry the same bits.
 template <int R>
-__device__ __forceinline__ double pass1_row_hinted(const ProjectArgs& a, int Rrt, int64_t base, int row_len, bool vec,
+__device__ __forceinline__ double pass1_row_hinted(const ProjectArgs& a, int Rrt, int64_t base, int row_len,
                                                    int j, int step, bool kept, bool stash, float* pk)
 {
     double acc = 0.0;
-    if (vec) {
-        const int nchunk = row_len >> 2;
-        int c = j;
-        for (; c + step < nchunk; c += 2 * step)
-            acc = Cand<R>::two_h(a, Rrt, base, c << 2, (c + step) << 2, kept, stash, pk, acc);
-        if (c < nchunk) acc = sq4(acc, Cand<R>::one_h(a, Rrt, base, c << 2, kept, stash, pk));
-    } else {
-        for (int c = j; c < row_len; c += step) {
-            const float v = Cand<R>::scalar_h(a, Rrt, base, c, kept, stash, pk);
-            acc = fma((double)v, (double)v, acc);
-        }
+    const int nchunk = row_len >> 2;
+    int c = j;
+    for (; c + step < nchunk; c += 2 * step)
+        acc = Cand<R>::two_h(a, Rrt, base, c << 2, (c + step) << 2, kept, stash, pk, acc);
+    if (c < nchunk) acc = sq4(acc, Cand<R>::one_h(a, Rrt, base, c << 2, kept, stash, pk));
+    if (const int c = (row_len & ~3) + j; c < row_len) {
+        const float v = Cand<R>::scalar_h(a, Rrt, base, c, kept, stash, pk);
+        acc = fma((double)v, (double)v, acc);
     }
     return acc;
 }
@@ -419,7 +412,6 @@ __device__ __forceinline__ void project_rows_hinted(const WorkItem& it, const Pr
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     const bool unconstrained = item_mode(it) == HSADMM_MODE_NONE;
     const bool stash = h.stash != 0;
     float* const pk_layer = h.packed ? h.packed + it.packed_off : nullptr;
@@ -441,7 +433,7 @@ __device__ __forceinline__ void project_rows_hinted(const WorkItem& it, const Pr
                 bool kept;
                 float* pk;
                 prediction(rr, kept, pk);
-                acc = pass1_row_hinted<R>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, vec, j, lpr, kept, stash, pk);
+                acc = pass1_row_hinted<R>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, j, lpr, kept, stash, pk);
             }
             acc = wave_xor_sum(acc, lpr);
             if (active && j == 0) a.key[it.g0 + rr] = acc;
@@ -452,7 +444,7 @@ __device__ __forceinline__ void project_rows_hinted(const WorkItem& it, const Pr
             bool kept;
             float* pk;
             prediction(rr, kept, pk);
-            double acc = pass1_row_hinted<R>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, vec, threadIdx.x, kBlock,
+            double acc = pass1_row_hinted<R>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, threadIdx.x, kBlock,
                                              kept, stash, pk);
             acc = wave_xor_sum(acc, kWave);
             if (lane == 0) wsum[wave] = acc;
@@ -484,8 +476,8 @@ __device__ __forceinline__ void project_tile_hinted(const WorkItem& it, const Pr
     const int row_len = it.row_len;
     const bool vec = item_vec(it);
     const int vw = vec ? 4 : 1;
-    const int col = it.col0 + lane * vw;
-    const bool in = col < row_len;
+    const bool in = it.col0 + lane * vw < row_len;
+    const int col = tile_col(it, lane, vw);
     const int khw = it.khw;
     const int packed_row_len = it.k * khw;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
@@ -625,8 +617,8 @@ __global__ __launch_bounds__(kBlock) void composite_colsums(const WorkItem* __re
     const int row_len = it.row_len;
     const bool vec = item_vec(it);
     const int vw = vec ? 4 : 1;
-    const int col = it.col0 + lane * vw;
-    const bool in = col < row_len;
+    const bool in = it.col0 + lane * vw < row_len;
+    const int col = tile_col(it, lane, vw);
     const uint8_t* mf = mask + it.g0 + it.row0;      // filter bytes of the tile's rows
     const float al = coef ? coef[2 * it.layer] : 1.f, bl = coef ? coef[2 * it.layer + 1] : 0.f;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
@@ -703,7 +695,6 @@ __device__ __forceinline__ void quad_pruned(const uint8_t* __restrict__ mc, cons
 __device__ __forceinline__ void fixup_rows(const WorkItem& it, const uint8_t* mask, float* U, float* Z)
 {
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
     // lanes-per-row mapping as in pass 1 (the mapping carries no arithmetic here)
     const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
@@ -713,18 +704,15 @@ __device__ __forceinline__ void fixup_rows(const WorkItem& it, const uint8_t* ma
     for (int rr = sub; rr < it.nr; rr += rows_at_once) {
         if (mask[it.g0 + rr] != 0) continue;
         const int64_t base = it.base + (int64_t)rr * row_len;
-        if (vec) {
-            const int nchunk = row_len >> 2;
-            for (int c = j; c < nchunk; c += lpr) {
-                const int64_t e = base + ((int64_t)c << 2);
-                st4(U + e, ld4(Z + e));
-                st4(Z + e, zero4);
-            }
-        } else {
-            for (int c = j; c < row_len; c += lpr) {
-                st1(U + base + c, ld1(Z + base + c));
-                st1(Z + base + c, 0.f);
-            }
+        const int nchunk = row_len >> 2;
+        for (int c = j; c < nchunk; c += lpr) {
+            const int64_t e = base + ((int64_t)c << 2);
+            st4(U + e, ld4(Z + e));
+            st4(Z + e, zero4);
+        }
+        if (const int c = (row_len & ~3) + j; c < row_len) {
+            st1(U + base + c, ld1(Z + base + c));
+            st1(Z + base + c, 0.f);
         }
     }
 }

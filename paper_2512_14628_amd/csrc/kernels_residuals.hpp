@@ -33,38 +33,35 @@ __global__ __launch_bounds__(kBlock) void residual_partials(const WorkItem* __re
     const int wave = threadIdx.x / kWave;
     const int64_t len = (int64_t)it.nr * it.row_len;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    if (item_vec(it)) {
-        for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
-            const int64_t e = it.base + (c << 2);
-            const v4f zi = ld4(a.Zi + e);
+    for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
+        const int64_t e = it.base + (c << 2);
+        const v4f zi = ld4(a.Zi + e);
 #pragma unroll
-            for (int r = 0; r < RR; ++r) {
-                const v4f w = ld4(a.W[r] + e);
-                s0 = sqd(s0, w.x, zi.x); s0 = sqd(s0, w.y, zi.y); s0 = sqd(s0, w.z, zi.z); s0 = sqd(s0, w.w, zi.w);
-            }
-            if (a.Zi_prev) {
-                const v4f p = ld4(a.Zi_prev + e);
-                s1 = sqd(s1, zi.x, p.x); s1 = sqd(s1, zi.y, p.y); s1 = sqd(s1, zi.z, p.z); s1 = sqd(s1, zi.w, p.w);
-            }
-            if (a.Zg) {
-                const v4f g = ld4(a.Zg + e);
-                s2 = sqd(s2, zi.x, g.x); s2 = sqd(s2, zi.y, g.y); s2 = sqd(s2, zi.z, g.z); s2 = sqd(s2, zi.w, g.w);
-                if (a.Zg_prev) {
-                    const v4f q = ld4(a.Zg_prev + e);
-                    s3 = sqd(s3, g.x, q.x); s3 = sqd(s3, g.y, q.y); s3 = sqd(s3, g.z, q.z); s3 = sqd(s3, g.w, q.w);
-                }
+        for (int r = 0; r < RR; ++r) {
+            const v4f w = ld4(a.W[r] + e);
+            s0 = sqd(s0, w.x, zi.x); s0 = sqd(s0, w.y, zi.y); s0 = sqd(s0, w.z, zi.z); s0 = sqd(s0, w.w, zi.w);
+        }
+        if (a.Zi_prev) {
+            const v4f p = ld4(a.Zi_prev + e);
+            s1 = sqd(s1, zi.x, p.x); s1 = sqd(s1, zi.y, p.y); s1 = sqd(s1, zi.z, p.z); s1 = sqd(s1, zi.w, p.w);
+        }
+        if (a.Zg) {
+            const v4f g = ld4(a.Zg + e);
+            s2 = sqd(s2, zi.x, g.x); s2 = sqd(s2, zi.y, g.y); s2 = sqd(s2, zi.z, g.z); s2 = sqd(s2, zi.w, g.w);
+            if (a.Zg_prev) {
+                const v4f q = ld4(a.Zg_prev + e);
+                s3 = sqd(s3, g.x, q.x); s3 = sqd(s3, g.y, q.y); s3 = sqd(s3, g.z, q.z); s3 = sqd(s3, g.w, q.w);
             }
         }
-    } else {
-        for (int64_t c = threadIdx.x; c < len; c += kBlock) {
-            const int64_t e = it.base + c;
-            const float zi = a.Zi[e];
-            for (int r = 0; r < RR; ++r) s0 = sqd(s0, a.W[r][e], zi);
-            if (a.Zi_prev) s1 = sqd(s1, zi, a.Zi_prev[e]);
-            if (a.Zg) {
-                s2 = sqd(s2, zi, a.Zg[e]);
-                if (a.Zg_prev) s3 = sqd(s3, a.Zg[e], a.Zg_prev[e]);
-            }
+    }
+    for (int64_t c = (len & ~3ll) + threadIdx.x; c < len; c += kBlock) {
+        const int64_t e = it.base + c;
+        const float zi = a.Zi[e];
+        for (int r = 0; r < RR; ++r) s0 = sqd(s0, a.W[r][e], zi);
+        if (a.Zi_prev) s1 = sqd(s1, zi, a.Zi_prev[e]);
+        if (a.Zg) {
+            s2 = sqd(s2, zi, a.Zg[e]);
+            if (a.Zg_prev) s3 = sqd(s3, a.Zg[e], a.Zg_prev[e]);
         }
     }
     s0 = wave_xor_sum(s0, kWave); s1 = wave_xor_sum(s1, kWave);
@@ -89,19 +86,16 @@ __global__ __launch_bounds__(kBlock) void sqnorm_partials(const WorkItem* __rest
     const int wave = threadIdx.x / kWave;
     const int64_t len = (int64_t)it.nr * it.row_len;
     double s = 0.0;
-    if (item_vec(it)) {
-        for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
-            const v4f x = ld4(X + it.base + (c << 2));
-            s = fma((double)x.x, (double)x.x, s);
-            s = fma((double)x.y, (double)x.y, s);
-            s = fma((double)x.z, (double)x.z, s);
-            s = fma((double)x.w, (double)x.w, s);
-        }
-    } else {
-        for (int64_t c = threadIdx.x; c < len; c += kBlock) {
-            const double x = (double)X[it.base + c];
-            s = fma(x, x, s);
-        }
+    for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
+        const v4f x = ld4(X + it.base + (c << 2));
+        s = fma((double)x.x, (double)x.x, s);
+        s = fma((double)x.y, (double)x.y, s);
+        s = fma((double)x.z, (double)x.z, s);
+        s = fma((double)x.w, (double)x.w, s);
+    }
+    for (int64_t c = (len & ~3ll) + threadIdx.x; c < len; c += kBlock) {
+        const double x = (double)X[it.base + c];
+        s = fma(x, x, s);
     }
     s = wave_xor_sum(s, kWave);
     if (lane == 0) red[wave] = s;

@@ -170,6 +170,9 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
     const bool vec = item_vec(it);
     const float al = w.coef[2 * it.layer], bl = w.coef[2 * it.layer + 1];
     if (item_mode(it) != HSADMM_MODE_CHANNEL) {
+        // With residual sums a row of whole words has loops of its own: followed by the last floats of a ragged row they
+        // are slower (ResNet-50, 4 replicas: 184 us against 177 us).
+        const bool whole = !RES || vec;
         const int mode = item_mode(it);
         const bool park = mode == HSADMM_MODE_BOTH;
         const bool all_kept = mode == HSADMM_MODE_NONE;
@@ -187,7 +190,34 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
             double res[4] = {0.0, 0.0, 0.0, 0.0};
             const bool take_res = RES && !park;
             if (active) {
-                if (vec) {
+                auto single = [&](int c) {
+                    float wb, u, zt, vd;
+                    if (take_res) wcand1_res<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd, res);
+                    else wcand1<R>(w, Rrt, base + c, al, bl, wb, u, zt);
+                    if (park) {
+                        st1(w.p.Z + base + c, wb);
+                    } else {
+                        st1(w.p.Z + base + c, all_kept ? zt : wb + u);
+                        st1(w.p.U + base + c, u + (wb - zt));
+                        if (w.p.Wbar) st1(w.p.Wbar + base + c, wb);
+                    }
+                    acc = fma((double)zt, (double)zt, acc);
+                };
+                auto four = [&](int c) {
+                    v4f wb, u, zt, vd;
+                    const int64_t e = base + ((int64_t)c << 2);
+                    if (take_res) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
+                    else wcand4<R>(w, Rrt, e, al, bl, wb, u, zt);
+                    if (park) {
+                        st4(w.p.Z + e, wb);
+                    } else {
+                        st4(w.p.Z + e, all_kept ? zt : wb + u);
+                        st4(w.p.U + e, u + (wb - zt));
+                        if (w.p.Wbar) st4(w.p.Wbar + e, wb);
+                    }
+                    acc = sq4(acc, zt);
+                };
+                if (whole) {
                     const int nchunk = row_len >> 2;
                     int c = j;
                     // two chunks of the row at a time: all their loads are issued before the first store
@@ -209,34 +239,12 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
                         acc = sq4(acc, zt0);
                         acc = sq4(acc, zt1);
                     }
-                    for (; c < nchunk; c += lpr) {
-                        v4f wb, u, zt, vd;
-                        const int64_t e = base + ((int64_t)c << 2);
-                        if (take_res) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
-                        else wcand4<R>(w, Rrt, e, al, bl, wb, u, zt);
-                        if (park) {
-                            st4(w.p.Z + e, wb);
-                        } else {
-                            st4(w.p.Z + e, all_kept ? zt : wb + u);
-                            st4(w.p.U + e, u + (wb - zt));
-                            if (w.p.Wbar) st4(w.p.Wbar + e, wb);
-                        }
-                        acc = sq4(acc, zt);
-                    }
+                    for (; c < nchunk; c += lpr) four(c);
+                    if constexpr (!RES)
+                        if (const int c = (row_len & ~3) + j; c < row_len) single(c);
                 } else {
-                    for (int c = j; c < row_len; c += lpr) {
-                        float wb, u, zt, vd;
-                        if (take_res) wcand1_res<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd, res);
-                        else wcand1<R>(w, Rrt, base + c, al, bl, wb, u, zt);
-                        if (park) {
-                            st1(w.p.Z + base + c, wb);
-                        } else {
-                            st1(w.p.Z + base + c, all_kept ? zt : wb + u);
-                            st1(w.p.U + base + c, u + (wb - zt));
-                            if (w.p.Wbar) st1(w.p.Wbar + base + c, wb);
-                        }
-                        acc = fma((double)zt, (double)zt, acc);
-                    }
+                    for (int c = j; c < (row_len >> 2); c += lpr) four(c);
+                    if (const int c = (row_len & ~3) + j; c < row_len) single(c);
                 }
             }
             if (!wide) {
@@ -271,8 +279,8 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
         }
     } else {
         const int vw = vec ? 4 : 1;
-        const int col = it.col0 + lane * vw;
-        const bool in = col < row_len;
+        const bool in = it.col0 + lane * vw < row_len;
+        const int col = tile_col(it, lane, vw);
         double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
         if (in) {
             for (int rr = wave; rr < it.nr; rr += kWaves) {
@@ -361,36 +369,33 @@ __device__ __forceinline__ void wcand1_v(const WeightedArgs& w, int Rrt, int64_t
 // in the order of weighted_item).  RES: res[0..3] also take the lane's share of the row's residual sums for either
 // outcome (see wcand4_res).
 template <int R, bool RES = false>
-__device__ __forceinline__ double weighted_row_final(const WeightedArgs& w, int Rrt, int64_t base, int row_len, bool vec,
+__device__ __forceinline__ double weighted_row_final(const WeightedArgs& w, int Rrt, int64_t base, int row_len,
                                                      int j, int step, float al, float bl, bool kept, float* pk,
                                                      double* res = nullptr)
 {
     double acc = 0.0;
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
-    if (vec) {
-        const int nchunk = row_len >> 2;
-        for (int c = j; c < nchunk; c += step) {
-            const int64_t e = base + ((int64_t)c << 2);
-            v4f wb, u, zt, vd;
-            if (RES) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
-            else wcand4_v<R>(w, Rrt, e, al, bl, wb, u, zt, vd);
-            st4(w.p.Z + e, kept ? zt : zero4);
-            st4(w.p.U + e, kept ? u + (wb - zt) : wb + u);
-            if (pk) st4u(pk + 4 * c, zt + vd);
-            if (w.p.Wbar) st4(w.p.Wbar + e, wb);
-            acc = sq4(acc, zt);
-        }
-    } else {
-        for (int c = j; c < row_len; c += step) {
-            float wb, u, zt, vd;
-            if (RES) wcand1_res<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd, res);
-            else wcand1_v<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd);
-            st1(w.p.Z + base + c, kept ? zt : 0.f);
-            st1(w.p.U + base + c, kept ? u + (wb - zt) : wb + u);
-            if (pk) pk[c] = zt + vd;
-            if (w.p.Wbar) st1(w.p.Wbar + base + c, wb);
-            acc = fma((double)zt, (double)zt, acc);
-        }
+    const int nchunk = row_len >> 2;
+    for (int c = j; c < nchunk; c += step) {
+        const int64_t e = base + ((int64_t)c << 2);
+        v4f wb, u, zt, vd;
+        if (RES) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
+        else wcand4_v<R>(w, Rrt, e, al, bl, wb, u, zt, vd);
+        st4(w.p.Z + e, kept ? zt : zero4);
+        st4(w.p.U + e, kept ? u + (wb - zt) : wb + u);
+        if (pk) st4u(pk + 4 * c, zt + vd);
+        if (w.p.Wbar) st4(w.p.Wbar + e, wb);
+        acc = sq4(acc, zt);
+    }
+    if (const int c = (row_len & ~3) + j; c < row_len) {
+        float wb, u, zt, vd;
+        if (RES) wcand1_res<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd, res);
+        else wcand1_v<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd);
+        st1(w.p.Z + base + c, kept ? zt : 0.f);
+        st1(w.p.U + base + c, kept ? u + (wb - zt) : wb + u);
+        if (pk) pk[c] = zt + vd;
+        if (w.p.Wbar) st1(w.p.Wbar + base + c, wb);
+        acc = fma((double)zt, (double)zt, acc);
     }
     return acc;
 }
@@ -417,7 +422,6 @@ __device__ __forceinline__ void weighted_rows_hinted(const WorkItem& it, const W
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     const float al = w.coef[2 * it.layer], bl = w.coef[2 * it.layer + 1];
     const bool unconstrained = item_mode(it) == HSADMM_MODE_NONE;
     const bool wide = it.lpr > kWave;
@@ -436,7 +440,7 @@ __device__ __forceinline__ void weighted_rows_hinted(const WorkItem& it, const W
             const int hp = unconstrained ? it.row0 + rr : h.sel_prev[it.g0 + rr];
             const bool kept = hp >= 0;
             float* pk = (pk_layer && kept && hp < it.k) ? pk_layer + (int64_t)hp * row_len : nullptr;
-            acc = weighted_row_final<R, RES>(w, Rrt, it.base + (int64_t)rr * row_len, row_len, vec, j, lpr, al, bl, kept,
+            acc = weighted_row_final<R, RES>(w, Rrt, it.base + (int64_t)rr * row_len, row_len, j, lpr, al, bl, kept,
                                              pk, res);
         }
         if (!wide) {
@@ -512,7 +516,6 @@ __global__ __launch_bounds__(kBlock) void weighted_hinted_repair(const WorkItem*
         }
         if (item_mode(it) != HSADMM_MODE_FILTER) continue;
         const int row_len = it.row_len;
-        const bool vec = item_vec(it);
         const float al = w.coef[2 * it.layer], bl = w.coef[2 * it.layer + 1];
         const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
         const int rows_at_once = kBlock / lpr;
@@ -526,10 +529,10 @@ __global__ __launch_bounds__(kBlock) void weighted_hinted_repair(const WorkItem*
             const int64_t base = it.base + (int64_t)rr * row_len;
             float* pk = (pk_layer && kept) ? pk_layer + (int64_t)pn * row_len : nullptr;
             if (pred_kept != kept) {
-                (void)weighted_row_final<R>(w, Rrt, base, row_len, vec, j, lpr, al, bl, kept, pk);
+                (void)weighted_row_final<R>(w, Rrt, base, row_len, j, lpr, al, bl, kept, pk);
             } else if (pk && pn != hp) {
-                if (vec) for (int c = j; c < (row_len >> 2); c += lpr) st4u(pk + 4 * c, ld4(w.p.Z + base + 4 * c) + ld4(w.Vd + base + 4 * c));
-                else for (int c = j; c < row_len; c += lpr) pk[c] = ld1(w.p.Z + base + c) + ld1(w.Vd + base + c);
+                for (int c = j; c < (row_len >> 2); c += lpr) st4u(pk + 4 * c, ld4(w.p.Z + base + 4 * c) + ld4(w.Vd + base + 4 * c));
+                if (const int c = (row_len & ~3) + j; c < row_len) pk[c] = ld1(w.p.Z + base + c) + ld1(w.Vd + base + c);
             }
         }
     }
@@ -546,7 +549,6 @@ __device__ __forceinline__ void weighted_fixup_rows(const WorkItem& it, const ui
                                                     const PackOut& po)
 {
     const int row_len = it.row_len;
-    const bool vec = item_vec(it);
     const float al = coef[2 * it.layer], bl = coef[2 * it.layer + 1];
     const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
     const int rows_at_once = kBlock / lpr;
@@ -563,40 +565,37 @@ __device__ __forceinline__ void weighted_fixup_rows(const WorkItem& it, const ui
         const int64_t base = it.base + (int64_t)rr * row_len;
         float* d = nullptr;
         if (PACK && keep) d = out + (int64_t)po.pos[it.g0 + rr] * row_len;
-        if (vec) {
-            const int nchunk = row_len >> 2;
-            for (int c = j; c < nchunk; c += lpr) {
-                const int64_t e = base + ((int64_t)c << 2);
-                const v4f t = ld4(Z + e);
-                if (keep) {
-                    const v4f vd = ld4(Vd + e);
-                    const v4f q = ld4(Zg + e) - vd;
-                    const v4f at = t * al;
-                    const v4f bq = q * bl;
-                    const v4f z = at + bq;
-                    st4(Z + e, z);
-                    if (PACK) st4u(d + 4 * c, z + vd);
-                } else {
-                    st4(U + e, t);
-                    st4(Z + e, zero4);
-                }
+        const int nchunk = row_len >> 2;
+        for (int c = j; c < nchunk; c += lpr) {
+            const int64_t e = base + ((int64_t)c << 2);
+            const v4f t = ld4(Z + e);
+            if (keep) {
+                const v4f vd = ld4(Vd + e);
+                const v4f q = ld4(Zg + e) - vd;
+                const v4f at = t * al;
+                const v4f bq = q * bl;
+                const v4f z = at + bq;
+                st4(Z + e, z);
+                if (PACK) st4u(d + 4 * c, z + vd);
+            } else {
+                st4(U + e, t);
+                st4(Z + e, zero4);
             }
-        } else {
-            for (int c = j; c < row_len; c += lpr) {
-                const int64_t e = base + c;
-                const float t = ld1(Z + e);
-                if (keep) {
-                    const float vd = ld1(Vd + e);
-                    const float q = ld1(Zg + e) - vd;
-                    const float at = t * al;
-                    const float bq = q * bl;
-                    const float z = at + bq;
-                    st1(Z + e, z);
-                    if (PACK) d[c] = z + vd;
-                } else {
-                    st1(U + e, t);
-                    st1(Z + e, 0.f);
-                }
+        }
+        if (const int c = (row_len & ~3) + j; c < row_len) {
+            const int64_t e = base + c;
+            const float t = ld1(Z + e);
+            if (keep) {
+                const float vd = ld1(Vd + e);
+                const float q = ld1(Zg + e) - vd;
+                const float at = t * al;
+                const float bq = q * bl;
+                const float z = at + bq;
+                st1(Z + e, z);
+                if (PACK) d[c] = z + vd;
+            } else {
+                st1(U + e, t);
+                st1(Z + e, 0.f);
             }
         }
     }
@@ -618,18 +617,15 @@ __global__ __launch_bounds__(kBlock) void dual_inter_kernel(const WorkItem* __re
 {
     const WorkItem it = items[blockIdx.x];
     const int64_t len = (int64_t)it.nr * it.row_len;
-    if (item_vec(it)) {
-        for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
-            const int64_t e = it.base + (c << 2);
-            const v4f d = ld4(Zi + e) - ld4(Zg + e);
-            st4(Vd + e, ld4(Vd + e) + d);
-        }
-    } else {
-        for (int64_t c = threadIdx.x; c < len; c += kBlock) {
-            const int64_t e = it.base + c;
-            const float d = Zi[e] - Zg[e];
-            Vd[e] = Vd[e] + d;
-        }
+    for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
+        const int64_t e = it.base + (c << 2);
+        const v4f d = ld4(Zi + e) - ld4(Zg + e);
+        st4(Vd + e, ld4(Vd + e) + d);
+    }
+    for (int64_t c = (len & ~3ll) + threadIdx.x; c < len; c += kBlock) {
+        const int64_t e = it.base + c;
+        const float d = Zi[e] - Zg[e];
+        Vd[e] = Vd[e] + d;
     }
 }
 
@@ -643,14 +639,11 @@ __global__ __launch_bounds__(kBlock) void scale_layers_kernel(const WorkItem* __
     const float f = factor[it.layer];
     if (f == 1.0f) return;
     const int64_t len = (int64_t)it.nr * it.row_len;
-    if (item_vec(it)) {
-        for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
-            const int64_t e = it.base + (c << 2);
-            st4(X + e, ld4(X + e) * f);
-        }
-    } else {
-        for (int64_t c = threadIdx.x; c < len; c += kBlock) X[it.base + c] = X[it.base + c] * f;
+    for (int64_t c = threadIdx.x; c < (len >> 2); c += kBlock) {
+        const int64_t e = it.base + (c << 2);
+        st4(X + e, ld4(X + e) * f);
     }
+    for (int64_t c = (len & ~3ll) + threadIdx.x; c < len; c += kBlock) X[it.base + c] = X[it.base + c] * f;
 }
 
 // Eq. (11): global consensus z = (1/M) sum_i (z_i + v_i) over M equally long buffers (the nodes' compact
