@@ -23,8 +23,8 @@
 //                   (composite_final).                     [Section 3, paragraph after Eq. (10)]
 //   scan_mask       index mappings from a given mask: kept counts, positions, kept_idx, layer_off.
 //   compact_gather  packed <- src[K_out, K_in, :]                             [Eq. (15)]
-//   fixup_gather    project_fixup with the kept rows packed on the way, and the gather of the unconstrained layers'
-//                   rows, in one launch (hsadmm_project_compact).
+//   fixup_gather    project_fixup and compact_gather of Z in one launch (hsadmm_project_compact): the
+//                   first rewrites pruned rows only, the second reads kept rows only.
 //   final_gather    without FILTER layers: the last final pass (with its packing) and the gather of the
 //                   unconstrained layers' rows in one launch.
 //   expand_scatter  dst <- zero fill + scatter of packed                      [Section 4.4.3]
@@ -123,7 +123,8 @@ struct hsadmm_plan {
     std::vector<WorkItem> items_est;    // project_pass1_est: items_proj with every FILTER layer's first items ahead of the rest
     std::vector<WorkItem> items_rows;   // compact / expand kernels
     std::vector<WorkItem> items_fix;    // project_fixup, weighted_fixup: the row items of the FILTER layers
-    std::vector<WorkItem> items_none;   // packed by the fix-up's or the final pass's launch: the row items of the unconstrained layers
+    std::vector<WorkItem> items_none;   // weighted_fixup_pack: the row items of the unconstrained layers
+    std::vector<WorkItem> items_plain;  // hsadmm_project_compact: the row items of the FILTER and NONE layers
     std::vector<WorkItem> items_bfinal; // composite_final: the row items of the BOTH layers
     std::vector<WorkItem> items_chan;   // channel_final: the row items of the CHANNEL layers (a subset of items_rows)
     std::vector<WorkItem> items_both;   // composite_colsums: tiles of the layers under both constraints
@@ -142,6 +143,7 @@ struct hsadmm_plan {
     WorkItem* d_items_rows = nullptr;
     WorkItem* d_items_fix = nullptr;
     WorkItem* d_items_none = nullptr;
+    WorkItem* d_items_plain = nullptr;
     WorkItem* d_items_bfinal = nullptr;
     WorkItem* d_items_chan = nullptr;
     WorkItem* d_items_both = nullptr;
@@ -451,6 +453,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
             d.rows_item0 = (int32_t)p->items_rows.size();
             add_row_items(p->items_rows, l, d, x.mode);
             if (x.mode == HSADMM_MODE_NONE) add_row_items(p->items_none, l, d, x.mode);
+            if (!has_colsums) add_row_items(p->items_plain, l, d, x.mode);
             d.rows_items = (int32_t)p->items_rows.size() - d.rows_item0;
             if (x.mode == HSADMM_MODE_CHANNEL) {
                 add_tile_items(p->items_proj, l, d, kChanRows);
@@ -568,6 +571,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
     upload(p->items_fix, &p->d_items_fix);
     upload(p->items_none, &p->d_items_none);
     upload(p->items_est, &p->d_items_est);
+    upload(p->items_plain, &p->d_items_plain);
     upload(p->items_bfinal, &p->d_items_bfinal);
     upload(p->items_chan, &p->d_items_chan);
     upload(p->items_both, &p->d_items_both);
@@ -594,6 +598,7 @@ void hsadmm_plan_destroy(hsadmm_plan_t* p)
     if (p->d_items_fix) (void)hipFree(p->d_items_fix);
     if (p->d_items_none) (void)hipFree(p->d_items_none);
     if (p->d_items_est) (void)hipFree(p->d_items_est);
+    if (p->d_items_plain) (void)hipFree(p->d_items_plain);
     if (p->d_items_bfinal) (void)hipFree(p->d_items_bfinal);
     if (p->d_items_chan) (void)hipFree(p->d_items_chan);
     if (p->d_items_both) (void)hipFree(p->d_items_both);
@@ -661,8 +666,7 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
     // it expects to be kept (and every row of the unconstrained layers).
     const bool hinted_chan = sel_prev != nullptr && U_out != nullptr && !p->items_chan.empty();   // CHANNEL layers too
     const bool hinted_both = sel_prev != nullptr && U_out != nullptr && !p->items_bfinal.empty(); // ... and BOTH layers
-    const bool has_plain = !p->items_fix.empty() || !p->items_none.empty();     // FILTER or unconstrained layers
-    const bool hinted = sel_prev != nullptr && (has_plain || hinted_chan || hinted_both);
+    const bool hinted = sel_prev != nullptr && (!p->items_plain.empty() || hinted_chan || hinted_both);
     const HintArgs h{sel_prev, out ? out->packed : nullptr, U_out ? 0 : 1, reinterpret_cast<int32_t*>(ws + p->ws.work),
                      p->d_layers};
     // Without a caller's prediction, a plan of FILTER and unconstrained layers whose dual is updated in place forms
@@ -706,16 +710,14 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
                           (const WorkItem*)p->d_items_est, a, (int)R, ex);
         });
     } else {
-        // (with FILTER layers the fix-up packs their rows and the selection hands out the offsets and kept lists itself)
-        if (out && !p->items_fix.empty()) wl.co = CopyOut{out->layer_off, out->kept_idx};
         e = for_replica_count<true>(R, [&](auto c) { return launch_pass1<decltype(c)::value>(p, a, R, s); });
     }
     if (e != hipSuccess) return HSADMM_ERR_HIP;
     // (the candidate of a BOTH layer is formed again from its parked mean and U)
     if (run_selection(p, a.key, a.colpart, a, mask, ws, s, sel_out, wl) != hipSuccess) return HSADMM_ERR_HIP;
-    // The compaction of Z under the selection just made: the kept rows of FILTER layers, final since pass 1, are packed
-    // by the FILTER fix-up, which shares its launch with the gather of the unconstrained layers' rows; the CHANNEL and
-    // BOTH layers are packed by the pass that writes their Z.
+    // The compaction of Z under the selection just made reads kept groups only, which FILTER layers hold in
+    // final form since pass 1, so it shares a launch with the FILTER fix-up; the CHANNEL and BOTH layers are
+    // packed by the pass that writes their Z.
     const bool fuse = out && !hinted && !est && !p->items_fix.empty();
     PackOut po{};
     po.pos = reinterpret_cast<const int32_t*>(ws + p->ws.pos);
@@ -770,15 +772,15 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
     }
     // Without FILTER layers the gather of the plain rows (unconstrained layers) has no fix-up to share a launch
     // with; it then rides on the last final pass.
-    bool plain_pending = out && !fuse && !hinted && !est && !p->items_none.empty();
-    const unsigned n_plain = (unsigned)p->items_none.size();      // (plain_pending: there are no FILTER layers)
+    bool plain_pending = out && !fuse && !hinted && !est && !p->items_plain.empty();
+    const unsigned n_plain = (unsigned)p->items_plain.size();
     if (!p->items_bfinal.empty() && !hinted_both) {
         // layers under both constraints: final Z and U from the parked mean and U, under both selections
         const unsigned gb = (unsigned)p->items_bfinal.size();
         if (out && plain_pending && p->items_chan.empty()) {
             e = launch(p, kBothFinal, final_gather<kMeanInZ>, gb + n_plain, kBlock, s,
                        (const WorkItem*)p->d_items_bfinal, (int)gb, a, 0, (const uint8_t*)mask, po,
-                       (const WorkItem*)p->d_items_none);
+                       (const WorkItem*)p->d_items_plain);
             plain_pending = false;
         } else if (out)
             e = launch(p, kBothFinal, project_frozen<kMeanInZ, true>, gb, kBlock, s, (const WorkItem*)p->d_items_bfinal,
@@ -793,7 +795,7 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
         const PackOut* pk = out ? &po : nullptr;
         const unsigned gc = (unsigned)p->items_chan.size();
         const WorkItem* ci = p->d_items_chan;
-        const WorkItem* pi = p->d_items_none;
+        const WorkItem* pi = p->d_items_plain;
         if (plain_pending) {
             switch (a.park_mean ? 0 : R) {
                 case 0: e = launch(p, kChanFinal, final_gather<kMeanInZ>, gc + n_plain, kBlock, s, ci, (int)gc, a, (int)R, cm, po, pi); break;
@@ -810,16 +812,19 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
         }
         if (e != hipSuccess) return HSADMM_ERR_HIP;
     }
-    if (fuse) {
-        const unsigned n_fix = (unsigned)p->items_fix.size();
-        e = launch(p, kFixupGather, fixup_gather, n_fix + (unsigned)p->items_none.size(), kBlock, s,
-                   (const WorkItem*)p->d_items_fix, (int)n_fix, a.U, Z, (const WorkItem*)p->d_items_none, po);
-    } else if (plain_pending) {
-        e = launch(p, kGather, compact_gather<false>, n_plain, kBlock, s, (const WorkItem*)p->d_items_none,
-                   (const float*)Z, (const float*)nullptr, po.pos, po.cnt, po.kept_idx, po.n_layers,
-                   po.layer_off, po.packed, po.co);
+    if (out && !p->items_plain.empty() && (fuse || plain_pending)) {
+        const unsigned n_rows = (unsigned)p->items_plain.size();
+        if (fuse)
+            e = launch(p, kFixupGather, fixup_gather, (unsigned)p->items_fix.size() + n_rows, kBlock, s,
+                       (const WorkItem*)p->d_items_fix, (int)p->items_fix.size(), (const uint8_t*)mask, a.U, Z,
+                       (const WorkItem*)p->d_items_plain, po.pos, po.cnt, po.kept_idx, po.n_layers, po.layer_off,
+                       po.packed, po.co);
+        else
+            e = launch(p, kGather, compact_gather<false>, n_rows, kBlock, s, (const WorkItem*)p->d_items_plain,
+                       (const float*)Z, (const float*)nullptr, po.pos, po.cnt, po.kept_idx, po.n_layers,
+                       po.layer_off, po.packed, po.co);
+        if (e != hipSuccess) return HSADMM_ERR_HIP;
     }
-    if (e != hipSuccess) return HSADMM_ERR_HIP;
     return HSADMM_OK;
 }
 
@@ -1123,7 +1128,7 @@ static int project_weighted_impl(const hsadmm_plan_t* p, const float* const* W_r
     hipError_t e;
     // (a prediction comes with the dual out of place here, so every mode can take it)
     const bool hinted_tiles = sel_prev != nullptr && (!p->items_chan.empty() || !p->items_bfinal.empty());
-    const bool hinted = sel_prev != nullptr && (!p->items_fix.empty() || !p->items_none.empty() || hinted_tiles);
+    const bool hinted = sel_prev != nullptr && (!p->items_plain.empty() || hinted_tiles);
     const WeightedHint wh{sel_prev, out ? out->packed : nullptr, reinterpret_cast<int32_t*>(ws + p->ws.work), p->d_layers};
     WorkList wl{};
     if (hinted) {

@@ -274,18 +274,23 @@ __global__ __launch_bounds__(kBlock) void compact_gather(const WorkItem* __restr
     gather_item<SUM>(items[blockIdx.x], src, src1, pos, cnt, kept_idx, n_layers, layer_off, packed, co);
 }
 
-// The FILTER fix-up with its kept rows packed on the way, and the gather of the unconstrained layers' rows (final since
-// pass 1), in one launch: workgroups [0, n_fix) take the FILTER row items, the rest those of the unconstrained layers.
-__global__ __launch_bounds__(kBlock) void fixup_gather(const WorkItem* __restrict__ fix_items, int n_fix, float* U,
-                                                       float* Z, const WorkItem* __restrict__ none_items, PackOut po)
+// The FILTER fix-up and the compaction of Z in one launch: the fix-up rewrites pruned rows only, the gather
+// reads kept rows only (final since pass 1), so the two kinds of workgroup touch disjoint memory and need no
+// order between them.  Workgroups [0, n_fix) take the fix-up items, the rest the row items.
+__global__ __launch_bounds__(kBlock) void fixup_gather(const WorkItem* __restrict__ fix_items, int n_fix,
+                                                       const uint8_t* __restrict__ mask, float* U, float* Z,
+                                                       const WorkItem* __restrict__ row_items,
+                                                       const int32_t* __restrict__ pos,
+                                                       const int32_t* __restrict__ cnt,
+                                                       const int32_t* __restrict__ kept_idx, int n_layers,
+                                                       const int64_t* __restrict__ layer_off, float* packed,
+                                                       CopyOut co)
 {
-    if ((int)blockIdx.x < n_fix) {
-        const WorkItem it = fix_items[blockIdx.x];
-        fixup_pack_rows(it, po.pos, U, Z, po.packed + it.packed_off);
-    } else {
-        gather_item<false>(none_items[(int)blockIdx.x - n_fix], Z, nullptr, po.pos, po.cnt, po.kept_idx, po.n_layers,
-                           po.layer_off, po.packed, po.co);
-    }
+    if ((int)blockIdx.x < n_fix)
+        fixup_rows(fix_items[blockIdx.x], mask, U, Z);
+    else
+        gather_item<false>(row_items[(int)blockIdx.x - n_fix], Z, nullptr, pos, cnt, kept_idx, n_layers, layer_off,
+                           packed, co);
 }
 
 // After the selection of a step whose pass 1 formed its own prediction (kernels_estimate.hpp): every FILTER row from
@@ -316,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void fixup_gather_est(const WorkItem* __res
 }
 
 // The final pass of CHANNEL or BOTH layers with its packing (project_frozen<R, true>) and the gather of the plain
-// layers' rows (NONE, final before this launch) in one launch: workgroups [0, n_final) take the final-pass
+// layers' rows (FILTER / NONE, final before this launch) in one launch: workgroups [0, n_final) take the final-pass
 // items, the rest the plain row items.  The two kinds of workgroup touch different layers.
 template <int R>
 __global__ __launch_bounds__(kBlock) void final_gather(const WorkItem* __restrict__ final_items, int n_final,

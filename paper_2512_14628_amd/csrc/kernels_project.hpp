@@ -717,70 +717,6 @@ __device__ __forceinline__ void fixup_rows(const WorkItem& it, const uint8_t* ma
     }
 }
 
-// The same with a compaction: a kept row's values (final since pass 1) also go to the packed buffer, at the row's rank.
-// Whatever becomes of a row, its values are read from Z, so a lane's loads wait for neither the mask nor the ranks and
-// two of them are in flight: of two rows, or of two chunks of a row that is longer than its lanes reach at once.
-__device__ __forceinline__ void fixup_pack_rows(const WorkItem& it, const int32_t* __restrict__ pos, float* U, float* Z,
-                                                float* packed)
-{
-    const int row_len = it.row_len;
-    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
-    const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
-    const int rows_at_once = kBlock / lpr;
-    const int sub = threadIdx.x / lpr;
-    const int j = threadIdx.x - sub * lpr;
-    const int nchunk = row_len >> 2;
-    const int32_t* const rank = pos + it.g0;
-    auto put = [&](int rr, int p, int col, const v4f& v) {
-        const int64_t e = it.base + (int64_t)rr * row_len + col;
-        if (p >= 0) {
-            st4u(packed + (int64_t)p * row_len + col, v);
-        } else {
-            st4(U + e, v);
-            st4(Z + e, zero4);
-        }
-    };
-    auto tail = [&](int rr, int p) {
-        const int64_t base = it.base + (int64_t)rr * row_len;
-        if (const int c = (row_len & ~3) + j; c < row_len) {
-            const float v = ld1(Z + base + c);
-            if (p >= 0) {
-                packed[(int64_t)p * row_len + c] = v;
-            } else {
-                st1(U + base + c, v);
-                st1(Z + base + c, 0.f);
-            }
-        }
-    };
-    if (nchunk <= lpr) {
-        for (int r0 = sub; r0 < it.nr; r0 += 2 * rows_at_once) {
-            const int r1 = r0 + rows_at_once;
-            const bool two = r1 < it.nr, on = j < nchunk;
-            v4f v0 = zero4, v1 = zero4;
-            if (on) v0 = ld4(Z + it.base + (int64_t)r0 * row_len + 4 * j);
-            if (on && two) v1 = ld4(Z + it.base + (int64_t)r1 * row_len + 4 * j);
-            const int p0 = rank[r0], p1 = two ? rank[r1] : 0;
-            if (on) put(r0, p0, 4 * j, v0);
-            if (on && two) put(r1, p1, 4 * j, v1);
-            tail(r0, p0);
-            if (two) tail(r1, p1);
-        }
-    } else {
-        for (int rr = sub; rr < it.nr; rr += rows_at_once) {
-            const float* row = Z + it.base + (int64_t)rr * row_len;
-            const int p = rank[rr];
-            int c = j;
-            for (; c + lpr < nchunk; c += 2 * lpr) {
-                const v4f v0 = ld4(row + 4 * c), v1 = ld4(row + 4 * (c + lpr));
-                put(rr, p, 4 * c, v0);
-                put(rr, p, 4 * (c + lpr), v1);
-            }
-            if (c < nchunk) put(rr, p, 4 * c, ld4(row + 4 * c));
-            tail(rr, p);
-        }
-    }
-}
-
 __global__ __launch_bounds__(kBlock) void project_fixup(const WorkItem* __restrict__ items,
                                                         const uint8_t* __restrict__ mask,
                                                         float* __restrict__ U, float* __restrict__ Z)
