@@ -205,9 +205,10 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
     const int mode = item_mode(it);
     const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
     const int row_len = it.row_len;
-    // With residual sums a row of whole words has loops of its own: followed by the last floats of a ragged row they are
-    // slower (ResNet-50, 4 replicas: 162 us against 158 us).
-    const bool whole = !RES || item_vec(it);
+    // columns a lane takes in fours, and where the ones it takes singly begin.  The pass with residual sums takes rows of
+    // whole words in fours and any other row singly: with both in one row it is slower (ResNet-50, 4 replicas: 162 us
+    // against 158 us).
+    const bool fours = !RES || item_vec(it);
     const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
     const int rows_at_once = kBlock / lpr;
     const int sub = threadIdx.x / lpr;
@@ -245,28 +246,26 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
                     if (r >= 0) drow[r * it.khw + (c - ch * it.khw)] = z;
                 }
             };
-            auto four = [&](int c) {
-                const int col = c << 2;
-                bool pr[4];
-                quad_pruned(mc, div, col, pr);
-                const v4f z = frozen4<R, false, WEIGHTED, RES>(a, Rrt, base + col, !pr[0], !pr[1], !pr[2], !pr[3], nullptr, al, bl, acc);
-                if (PACK && drow) {
-                    int pc[4];
-                    quad_packed_cols(rank, div, col, pc);
-                    if (pc[0] >= 0) drow[pc[0]] = z.x;
-                    if (pc[1] >= 0) drow[pc[1]] = z.y;
-                    if (pc[2] >= 0) drow[pc[2]] = z.z;
-                    if (pc[3] >= 0) drow[pc[3]] = z.w;
-                }
-            };
-            if (whole) {
+            if (fours) {
                 const int nchunk = row_len >> 2;
-                for (int c = j; c < nchunk; c += lpr) four(c);
+                for (int c = j; c < nchunk; c += lpr) {
+                    const int col = c << 2;
+                    bool pr[4];
+                    quad_pruned(mc, div, col, pr);
+                    const v4f z = frozen4<R, false, WEIGHTED, RES>(a, Rrt, base + col, !pr[0], !pr[1], !pr[2], !pr[3], nullptr, al, bl, acc);
+                    if (PACK && drow) {
+                        int pc[4];
+                        quad_packed_cols(rank, div, col, pc);
+                        if (pc[0] >= 0) drow[pc[0]] = z.x;
+                        if (pc[1] >= 0) drow[pc[1]] = z.y;
+                        if (pc[2] >= 0) drow[pc[2]] = z.z;
+                        if (pc[3] >= 0) drow[pc[3]] = z.w;
+                    }
+                }
                 if constexpr (!RES)
                     if (const int c = (row_len & ~3) + j; c < row_len) single(c);
             } else {
-                for (int c = j; c < (row_len >> 2); c += lpr) four(c);
-                if (const int c = (row_len & ~3) + j; c < row_len) single(c);
+                for (int c = j; c < row_len; c += lpr) single(c);
             }
             continue;
         }
@@ -279,7 +278,7 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
         auto single = [&](int c) {
             frozen1<R, PACK, WEIGHTED, RES>(a, Rrt, base + c, keep, d ? d + c : nullptr, al, bl, acc);
         };
-        if (whole) {
+        if (fours) {
             const int nchunk = row_len >> 2;
             int c = j;
             for (; c + lpr < nchunk; c += 2 * lpr)
@@ -291,10 +290,7 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
             if constexpr (!RES)
                 if (const int c = (row_len & ~3) + j; c < row_len) single(c);
         } else {
-            for (int c = j; c < (row_len >> 2); c += lpr)
-                frozen4<R, PACK, WEIGHTED, RES>(a, Rrt, base + ((int64_t)c << 2), keep, keep, keep, keep,
-                                                d ? d + 4 * c : nullptr, al, bl, acc);
-            if (const int c = (row_len & ~3) + j; c < row_len) single(c);
+            for (int c = j; c < row_len; c += lpr) single(c);
         }
     }
 }

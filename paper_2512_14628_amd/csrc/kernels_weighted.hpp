@@ -170,9 +170,9 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
     const bool vec = item_vec(it);
     const float al = w.coef[2 * it.layer], bl = w.coef[2 * it.layer + 1];
     if (item_mode(it) != HSADMM_MODE_CHANNEL) {
-        // With residual sums a row of whole words has loops of its own: followed by the last floats of a ragged row they
-        // are slower (ResNet-50, 4 replicas: 184 us against 177 us).
-        const bool whole = !RES || vec;
+        // rows in fours and a tail, but not with residual sums: there a row that is not whole words is taken singly
+        // (with both in one row ResNet-50 with 4 replicas takes 184 us against 177 us)
+        const bool fours = !RES || vec;
         const int mode = item_mode(it);
         const bool park = mode == HSADMM_MODE_BOTH;
         const bool all_kept = mode == HSADMM_MODE_NONE;
@@ -203,21 +203,7 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
                     }
                     acc = fma((double)zt, (double)zt, acc);
                 };
-                auto four = [&](int c) {
-                    v4f wb, u, zt, vd;
-                    const int64_t e = base + ((int64_t)c << 2);
-                    if (take_res) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
-                    else wcand4<R>(w, Rrt, e, al, bl, wb, u, zt);
-                    if (park) {
-                        st4(w.p.Z + e, wb);
-                    } else {
-                        st4(w.p.Z + e, all_kept ? zt : wb + u);
-                        st4(w.p.U + e, u + (wb - zt));
-                        if (w.p.Wbar) st4(w.p.Wbar + e, wb);
-                    }
-                    acc = sq4(acc, zt);
-                };
-                if (whole) {
+                if (fours) {
                     const int nchunk = row_len >> 2;
                     int c = j;
                     // two chunks of the row at a time: all their loads are issued before the first store
@@ -239,12 +225,24 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
                         acc = sq4(acc, zt0);
                         acc = sq4(acc, zt1);
                     }
-                    for (; c < nchunk; c += lpr) four(c);
+                    for (; c < nchunk; c += lpr) {
+                        v4f wb, u, zt, vd;
+                        const int64_t e = base + ((int64_t)c << 2);
+                        if (take_res) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
+                        else wcand4<R>(w, Rrt, e, al, bl, wb, u, zt);
+                        if (park) {
+                            st4(w.p.Z + e, wb);
+                        } else {
+                            st4(w.p.Z + e, all_kept ? zt : wb + u);
+                            st4(w.p.U + e, u + (wb - zt));
+                            if (w.p.Wbar) st4(w.p.Wbar + e, wb);
+                        }
+                        acc = sq4(acc, zt);
+                    }
                     if constexpr (!RES)
                         if (const int c = (row_len & ~3) + j; c < row_len) single(c);
                 } else {
-                    for (int c = j; c < (row_len >> 2); c += lpr) four(c);
-                    if (const int c = (row_len & ~3) + j; c < row_len) single(c);
+                    for (int c = j; c < row_len; c += lpr) single(c);
                 }
             }
             if (!wide) {
