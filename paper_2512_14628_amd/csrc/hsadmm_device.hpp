@@ -169,8 +169,9 @@ struct ProjectArgs {
 };
 
 // Streaming (touch-once) accesses.  ld4 / st4 take any address of a float: rows whose length is not a multiple of four
-// floats start anywhere, and 128-bit accesses that are aligned to 4 bytes only still move such a row at more than twice
-// the rate of 32-bit ones (a wave touches one cache line more).
+// floats start anywhere, and a 128-bit access that is aligned to 4 bytes only costs a wave one cache line more.  Such rows
+// one float per lane instead: ResNet-18 of width 45, 3 replicas, a step in 65.4 us against 60.5 us; weighted candidate of
+// width 41, 5 replicas, 108 us against 95.5 us.
 __device__ __forceinline__ v4f ld4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const v4f_at4*>(p)); }
 __device__ __forceinline__ void st4(float* p, v4f v) { __builtin_nontemporal_store(v, reinterpret_cast<v4f_at4*>(p)); }
 __device__ __forceinline__ float ld1(const float* p) { return __builtin_nontemporal_load(p); }

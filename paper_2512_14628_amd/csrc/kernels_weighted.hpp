@@ -409,7 +409,8 @@ struct WeightedHint {
 // Row items of FILTER and unconstrained layers under a predicted selection, dual out of place: every row is written
 // in the final form of its predicted outcome and, if predicted kept, packed at its predicted rank (ranks outside
 // [0, k) are left for the repair pass).  The keys are taken with the lane mapping of weighted_item; its sums run
-// two chunks at a time where this loop takes one, in the same order of additions.  RES: as in weighted_item, the
+// two chunks at a time where this loop takes one, in the same order of additions (but for rows that are not whole
+// 128-bit words with residual sums, which weighted_item adds up float by float).  RES: as in weighted_item, the
 // residual sums of either outcome of every row go to rowres (the selection picks by the real outcome, so a wrong
 // prediction costs them nothing).
 template <int R, bool RES>
