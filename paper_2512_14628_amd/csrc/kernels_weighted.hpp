@@ -145,6 +145,125 @@ __device__ __forceinline__ void wcand1(const WeightedArgs& w, int Rrt, int64_t e
     zt = at + bq;
 }
 
+// The rows of a FILTER, unconstrained or BOTH item.  SPLIT: never those of a BOTH item, so that the residual sums are
+// taken of every row and the loop asks nothing.
+// A row is taken in fours and the one to three floats after them singly, in every form of the pass (with and without the
+// residual sums, and under a prediction), so that a key has the same bits in all of them.  With the residual sums a row of
+// whole words has a loop of its own: with the tail behind the one loop ResNet-50 with 4 replicas takes 184 us for 177 us.
+template <int R, bool RES, bool SPLIT>
+__device__ __forceinline__ void weighted_rows(const WorkItem& it, const WeightedArgs& w, int Rrt, double (*wsum)[5])
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int row_len = it.row_len;
+    const int nchunk = row_len >> 2;
+    const float al = w.coef[2 * it.layer], bl = w.coef[2 * it.layer + 1];
+    const int mode = item_mode(it);
+    const bool park = !SPLIT && mode == HSADMM_MODE_BOTH;
+    const bool take_res = RES && !park;
+    const bool all_kept = mode == HSADMM_MODE_NONE;
+    const bool wide = it.lpr > kWave;
+    const int lpr = wide ? kBlock : it.lpr;
+    const int rows_at_once = kBlock / lpr;
+    const int sub = threadIdx.x / lpr;
+    const int j = threadIdx.x - sub * lpr;
+    const int rounds = (it.nr + rows_at_once - 1) / rows_at_once;
+    for (int rd = 0; rd < rounds; ++rd) {
+        const int rr = rd * rows_at_once + sub;
+        const bool active = rr < it.nr;
+        const int64_t base = it.base + (int64_t)rr * row_len;
+        double acc = 0.0;
+        double res[4] = {0.0, 0.0, 0.0, 0.0};
+        auto four = [&](int c) {
+            v4f wb, u, zt, vd;
+            const int64_t e = base + ((int64_t)c << 2);
+            if (take_res) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
+            else wcand4<R>(w, Rrt, e, al, bl, wb, u, zt);
+            if (park) {
+                st4(w.p.Z + e, wb);
+            } else {
+                st4(w.p.Z + e, all_kept ? zt : wb + u);
+                st4(w.p.U + e, u + (wb - zt));
+                if (w.p.Wbar) st4(w.p.Wbar + e, wb);
+            }
+            acc = sq4(acc, zt);
+        };
+        auto tail = [&]() {
+            const int c = (row_len & ~3) + j;
+            if (c >= row_len) return;
+            float wb, u, zt, vd;
+            if (take_res) wcand1_res<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd, res);
+            else wcand1<R>(w, Rrt, base + c, al, bl, wb, u, zt);
+            if (park) {
+                st1(w.p.Z + base + c, wb);
+            } else {
+                st1(w.p.Z + base + c, all_kept ? zt : wb + u);
+                st1(w.p.U + base + c, u + (wb - zt));
+                if (w.p.Wbar) st1(w.p.Wbar + base + c, wb);
+            }
+            acc = fma((double)zt, (double)zt, acc);
+        };
+        if (active) {
+            if (!RES || item_vec(it)) {
+                int c = j;
+                // two chunks of the row at a time: all their loads are issued before the first store
+                // (one at a time when the residual sums are taken: the replicas' values stay live then)
+                for (; !take_res && c + lpr < nchunk; c += 2 * lpr) {
+                    const int64_t e0 = base + ((int64_t)c << 2), e1 = base + ((int64_t)(c + lpr) << 2);
+                    v4f wb0, u0, zt0, wb1, u1, zt1;
+                    wcand4x2<R>(w, Rrt, e0, e1, al, bl, wb0, u0, zt0, wb1, u1, zt1);
+                    if (park) {
+                        st4(w.p.Z + e0, wb0);
+                        st4(w.p.Z + e1, wb1);
+                    } else {
+                        st4(w.p.Z + e0, all_kept ? zt0 : wb0 + u0);
+                        st4(w.p.Z + e1, all_kept ? zt1 : wb1 + u1);
+                        st4(w.p.U + e0, u0 + (wb0 - zt0));
+                        st4(w.p.U + e1, u1 + (wb1 - zt1));
+                        if (w.p.Wbar) { st4(w.p.Wbar + e0, wb0); st4(w.p.Wbar + e1, wb1); }
+                    }
+                    acc = sq4(acc, zt0);
+                    acc = sq4(acc, zt1);
+                }
+                for (; c < nchunk; c += lpr) four(c);
+                if constexpr (!RES) tail();
+            } else {
+                for (int c = j; c < nchunk; c += lpr) four(c);
+                tail();
+            }
+        }
+        if (!wide) {
+            acc = wave_xor_sum(acc, lpr);
+            if (active && j == 0) w.p.key[it.g0 + rr] = acc;
+            if (take_res) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    res[k] = wave_xor_sum(res[k], lpr);
+                    if (active && j == 0) w.rowres[4 * (int64_t)(it.g0 + rr) + k] = res[k];
+                }
+            }
+        } else {
+            acc = wave_xor_sum(acc, kWave);
+            if (take_res) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) res[k] = wave_xor_sum(res[k], kWave);
+            }
+            if (lane == 0) {
+                wsum[wave][0] = acc;
+                if (take_res) { wsum[wave][1] = res[0]; wsum[wave][2] = res[1]; wsum[wave][3] = res[2]; wsum[wave][4] = res[3]; }
+            }
+            __syncthreads();
+            if (threadIdx.x < (take_res ? 5 : 1)) {
+                double s = wsum[0][threadIdx.x];
+                for (int v = 1; v < kWaves; ++v) s += wsum[v][threadIdx.x];
+                if (threadIdx.x == 0) w.p.key[it.g0 + rr] = s;
+                else w.rowres[4 * (int64_t)(it.g0 + rr) + (threadIdx.x - 1)] = s;
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // Pass 1 of the weighted projection: keys of the candidate z~ with the lane mappings and the order of
 // additions of project_pass1.  With the rho_2 term a pruned group needs t = Wbar + U (its dual becomes t) and
 // a kept group z~ and U + (Wbar - z~); z~ follows from t, Zg and Vd, so per mode:
@@ -170,111 +289,12 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
     const bool vec = item_vec(it);
     const float al = w.coef[2 * it.layer], bl = w.coef[2 * it.layer + 1];
     if (item_mode(it) != HSADMM_MODE_CHANNEL) {
-        // rows in fours and a tail, but not with residual sums: there a row that is not whole words is taken singly
-        // (with both in one row ResNet-50 with 4 replicas takes 184 us against 177 us)
-        const bool fours = !RES || vec;
-        const int mode = item_mode(it);
-        const bool park = mode == HSADMM_MODE_BOTH;
-        const bool all_kept = mode == HSADMM_MODE_NONE;
-        const bool wide = it.lpr > kWave;
-        const int lpr = wide ? kBlock : it.lpr;
-        const int rows_at_once = kBlock / lpr;
-        const int sub = threadIdx.x / lpr;
-        const int j = threadIdx.x - sub * lpr;
-        const int rounds = (it.nr + rows_at_once - 1) / rows_at_once;
-        for (int rd = 0; rd < rounds; ++rd) {
-            const int rr = rd * rows_at_once + sub;
-            const bool active = rr < it.nr;
-            const int64_t base = it.base + (int64_t)rr * row_len;
-            double acc = 0.0;
-            double res[4] = {0.0, 0.0, 0.0, 0.0};
-            const bool take_res = RES && !park;
-            if (active) {
-                auto single = [&](int c) {
-                    float wb, u, zt, vd;
-                    if (take_res) wcand1_res<R>(w, Rrt, base + c, al, bl, wb, u, zt, vd, res);
-                    else wcand1<R>(w, Rrt, base + c, al, bl, wb, u, zt);
-                    if (park) {
-                        st1(w.p.Z + base + c, wb);
-                    } else {
-                        st1(w.p.Z + base + c, all_kept ? zt : wb + u);
-                        st1(w.p.U + base + c, u + (wb - zt));
-                        if (w.p.Wbar) st1(w.p.Wbar + base + c, wb);
-                    }
-                    acc = fma((double)zt, (double)zt, acc);
-                };
-                if (fours) {
-                    const int nchunk = row_len >> 2;
-                    int c = j;
-                    // two chunks of the row at a time: all their loads are issued before the first store
-                    // (one at a time when the residual sums are taken: the replicas' values stay live then)
-                    for (; !take_res && c + lpr < nchunk; c += 2 * lpr) {
-                        const int64_t e0 = base + ((int64_t)c << 2), e1 = base + ((int64_t)(c + lpr) << 2);
-                        v4f wb0, u0, zt0, wb1, u1, zt1;
-                        wcand4x2<R>(w, Rrt, e0, e1, al, bl, wb0, u0, zt0, wb1, u1, zt1);
-                        if (park) {
-                            st4(w.p.Z + e0, wb0);
-                            st4(w.p.Z + e1, wb1);
-                        } else {
-                            st4(w.p.Z + e0, all_kept ? zt0 : wb0 + u0);
-                            st4(w.p.Z + e1, all_kept ? zt1 : wb1 + u1);
-                            st4(w.p.U + e0, u0 + (wb0 - zt0));
-                            st4(w.p.U + e1, u1 + (wb1 - zt1));
-                            if (w.p.Wbar) { st4(w.p.Wbar + e0, wb0); st4(w.p.Wbar + e1, wb1); }
-                        }
-                        acc = sq4(acc, zt0);
-                        acc = sq4(acc, zt1);
-                    }
-                    for (; c < nchunk; c += lpr) {
-                        v4f wb, u, zt, vd;
-                        const int64_t e = base + ((int64_t)c << 2);
-                        if (take_res) wcand4_res<R>(w, Rrt, e, al, bl, wb, u, zt, vd, res);
-                        else wcand4<R>(w, Rrt, e, al, bl, wb, u, zt);
-                        if (park) {
-                            st4(w.p.Z + e, wb);
-                        } else {
-                            st4(w.p.Z + e, all_kept ? zt : wb + u);
-                            st4(w.p.U + e, u + (wb - zt));
-                            if (w.p.Wbar) st4(w.p.Wbar + e, wb);
-                        }
-                        acc = sq4(acc, zt);
-                    }
-                    if constexpr (!RES)
-                        if (const int c = (row_len & ~3) + j; c < row_len) single(c);
-                } else {
-                    for (int c = j; c < row_len; c += lpr) single(c);
-                }
-            }
-            if (!wide) {
-                acc = wave_xor_sum(acc, lpr);
-                if (active && j == 0) w.p.key[it.g0 + rr] = acc;
-                if (take_res) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        res[k] = wave_xor_sum(res[k], lpr);
-                        if (active && j == 0) w.rowres[4 * (int64_t)(it.g0 + rr) + k] = res[k];
-                    }
-                }
-            } else {
-                acc = wave_xor_sum(acc, kWave);
-                if (take_res) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) res[k] = wave_xor_sum(res[k], kWave);
-                }
-                if (lane == 0) {
-                    wsum[wave][0] = acc;
-                    if (take_res) { wsum[wave][1] = res[0]; wsum[wave][2] = res[1]; wsum[wave][3] = res[2]; wsum[wave][4] = res[3]; }
-                }
-                __syncthreads();
-                if (threadIdx.x < (take_res ? 5 : 1)) {
-                    double s = wsum[0][threadIdx.x];
-                    for (int v = 1; v < kWaves; ++v) s += wsum[v][threadIdx.x];
-                    if (threadIdx.x == 0) w.p.key[it.g0 + rr] = s;
-                    else w.rowres[4 * (int64_t)(it.g0 + rr) + (threadIdx.x - 1)] = s;
-                }
-                __syncthreads();
-            }
-        }
+        // Split with eight replicas only, where the plain loop keeps too much alive: ResNet-50, 427 us for a step with
+        // norms, split 411 us (two replicas 311 / 307 us, but ResNet-152 with one 636 / 648 us, with five 1019 / 1051 us).
+        constexpr bool split = RES && R == 8;
+        if constexpr (!split) weighted_rows<R, RES, false>(it, w, Rrt, wsum);
+        else if (item_mode(it) != HSADMM_MODE_BOTH) weighted_rows<R, true, true>(it, w, Rrt, wsum);
+        else weighted_rows<R, false, false>(it, w, Rrt, wsum);
     } else {
         const int vw = vec ? 4 : 1;
         const bool in = it.col0 + lane * vw < row_len;
@@ -315,8 +335,11 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
     }
 }
 
+// (With the residual sums four replicas get the registers of three waves per SIMD, eight those of two: ResNet-50 step with
+// norms, 4 replicas, left to the compiler 347 us, so 341 us; 8 replicas 418 us, so 410 us.)
 template <int R, bool RES = false>
-__global__ __launch_bounds__(kBlock) void weighted_pass1(const WorkItem* __restrict__ items, WeightedArgs w, int Rrt)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, !RES || R < 4 ? 8 : R < 8 ? 3 : 2)))
+void weighted_pass1(const WorkItem* __restrict__ items, WeightedArgs w, int Rrt)
 {
     weighted_item<R, RES>(items[blockIdx.x], w, Rrt);
 }
@@ -409,8 +432,7 @@ struct WeightedHint {
 // Row items of FILTER and unconstrained layers under a predicted selection, dual out of place: every row is written
 // in the final form of its predicted outcome and, if predicted kept, packed at its predicted rank (ranks outside
 // [0, k) are left for the repair pass).  The keys are taken with the lane mapping of weighted_item; its sums run
-// two chunks at a time where this loop takes one, in the same order of additions (but for rows that are not whole
-// 128-bit words with residual sums, which weighted_item adds up float by float).  RES: as in weighted_item, the
+// two chunks at a time where this loop takes one, in the same order of additions.  RES: as in weighted_item, the
 // residual sums of either outcome of every row go to rowres (the selection picks by the real outcome, so a wrong
 // prediction costs them nothing).
 template <int R, bool RES>

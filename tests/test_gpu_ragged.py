@@ -44,3 +44,60 @@ def test_row_lengths_that_are_not_whole_words_with_the_estimate(monkeypatch):
     from tests.test_gpu_parity import _run
     monkeypatch.setenv("HSADMM_FORCE_ESTIMATE", "1")
     _run(_workload(wk.MODE_FILTER, 4, 5), want_wbar=True, want_sqnorm=True)
+
+
+@pytest.mark.parametrize("mode", [wk.MODE_NONE, wk.MODE_FILTER, wk.MODE_CHANNEL, wk.MODE_BOTH])
+@pytest.mark.parametrize("R", [1, 2, 4, 5, 8])
+def test_every_form_of_the_step_on_rows_that_are_not_whole_words(mode, R):
+    """The weighted candidate with the dual out of place, un-predicted and under a right and a partly wrong prediction,
+    with and without the residual norms: floats, masks and ranks are the oracle's, and neither the prediction nor the
+    norms change a bit of the group keys, nor the prediction one of the norms (every form adds a row in one order)."""
+    from tests.test_gpu_hinted import _Bufs, degrade, record_of
+    import oracle
+    import paper_2512_14628_amd as pkg
+    wl = _workload(mode, R, 100 * R + mode)
+    W, U = wk.generate(wl)
+    rng = np.random.default_rng(7 * R + mode)
+    t, L = wl.table(), len(wl.layers)
+    a, bb = oracle.node_coefficients(rng.uniform(1e-3, 2e-3, L), rng.uniform(1e-4, 3e-4, L), 1e-4, 16, R)
+    Zg, Vd, Zp = (rng.standard_normal(wl.n_arena).astype(np.float32) * s for s in (0.05, 0.01, 0.05))
+    ref = oracle.project_weighted(t, W, U, Zg, Vd, a, bb, want_wbar=True)
+    refc = oracle.compact(t, oracle.add_arenas(t, ref["Z"], Vd), ref["mask"])
+    sq = oracle.residuals(t, W, ref["Z"], Zp)
+    b = _Bufs(wl, W, U, 1)
+    dev = b.U.device
+    dZg, dVd, dZp = (torch.from_numpy(x).to(dev) for x in (Zg, Vd, Zp))
+    coef = torch.from_numpy(np.stack([a, bb], axis=1).astype(np.float32).reshape(-1).copy()).to(dev)
+    right = record_of(wl, ref["mask"])
+    keys = norms = None
+    for name, rec in (("none", None), ("right", right), ("wrong", record_of(wl, degrade(wl, ref["mask"], 0.2, rng)))):
+        for with_norms in (False, True):
+            case = "%s, norms %s" % (name, with_norms)
+            b.reset()
+            b.out_of_place = True
+            res = torch.full((4 * L,), -7.0, dtype=torch.float64, device=dev)
+            pkg.hsadmm_step(b.plan, b.W, U=b.U, U_out=b.Uout, Zg=dZg, Vd=dVd, coef=coef, Z=b.Z, Wbar=b.Wbar, mask=b.mask,
+                            sqnorm=b.key, sel=b.sel, sel_prev=None if rec is None else torch.from_numpy(rec).to(dev),
+                            packed=b.packed, layer_off=b.off, kept_idx=b.kept, workspace=b.ws,
+                            **(dict(residuals=res, Zi_prev=dZp) if with_norms else {}))
+            got = b.outputs()
+            assert np.array_equal(got["mask"], ref["mask"]) and np.array_equal(got["sel"], right), case
+            for key in ("Z", "U", "Wbar"):
+                for l in wl.layers:
+                    sl = slice(l.elem_off, l.elem_off + l.n)
+                    assert np.array_equal(got[key][sl].view(np.uint32), ref[key][sl].view(np.uint32)), (case, key, l.name)
+            assert np.array_equal(got["layer_off"], refc["layer_off"]), case
+            n = int(refc["layer_off"][-1])
+            assert np.array_equal(got["packed"][:n].view(np.uint32), refc["packed"][:n].view(np.uint32)), case
+            np.testing.assert_allclose(got["key"], ref["key"], rtol=1e-12, err_msg=case)
+            if keys is None:
+                keys = got["key"].view(np.uint64)
+            assert np.array_equal(got["key"].view(np.uint64), keys), "keys differ in their last bits: " + case
+            if with_norms:
+                r = res.cpu().numpy().reshape(4, L)[:2]
+                for li, l in enumerate(wl.layers):
+                    np.testing.assert_allclose(r[:, li], sq[:2, li], rtol=max(1e-12, l.n * R * 2.0 ** -53), err_msg=case)
+                if norms is None:
+                    norms = r.view(np.uint64)
+                assert np.array_equal(r.view(np.uint64), norms), "norms differ in their last bits: " + case
+    b.plan.close()
