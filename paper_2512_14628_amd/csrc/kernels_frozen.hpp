@@ -197,6 +197,10 @@ __device__ __forceinline__ void quad_packed_cols(const int32_t* __restrict__ ran
 // mask (po): a kept FILTER row or a row of a NONE layer whole, at its rank; of a CHANNEL row, or a kept filter's
 // row of a BOTH layer, the columns of kept channels, each at its packed column.
 // RES: acc[0], acc[1] take this thread's share of the item's two intra-node residual sums (see frozen4).
+// The one to three floats after a ragged row's words go to a lane each.  With the residual sums the row loop of whole words
+// is a loop of its own: with the tail behind the one loop a retraining iteration's pass over ResNet-50 with 4 replicas takes
+// 162 us for 158 us.  (Ragged rows one float per lane, on the lanes they have in fours, made every lane walk four floats one
+// after another: the iteration on a plain network of width 45 with channel groups 41.8 us, in fours 26.2 us.)
 template <int R, bool PACK, bool WEIGHTED = false, bool RES = false>
 __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArgs& a, int Rrt,
                                             const uint8_t* __restrict__ mask, const PackOut& po,
@@ -205,10 +209,7 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
     const int mode = item_mode(it);
     const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
     const int row_len = it.row_len;
-    // columns a lane takes in fours, and where the ones it takes singly begin.  The pass with residual sums takes rows of
-    // whole words in fours and any other row singly: with both in one row it is slower (ResNet-50, 4 replicas: 162 us
-    // against 158 us).
-    const bool fours = !RES || item_vec(it);
+    const int nchunk = row_len >> 2;
     const int lpr = it.lpr <= kWave ? it.lpr : kBlock;
     const int rows_at_once = kBlock / lpr;
     const int sub = threadIdx.x / lpr;
@@ -229,25 +230,24 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
             rank = po.pos + (mode == HSADMM_MODE_BOTH ? it.aux : (int64_t)it.g0);
         }
     }
-    for (int rr = sub; rr < it.nr; rr += rows_at_once) {
-        const bool keep = mode == HSADMM_MODE_NONE || mode == HSADMM_MODE_CHANNEL || mask[it.g0 + rr] != 0;
-        const int64_t base = it.base + (int64_t)rr * row_len;
-        if (columns && keep) {
-            float* drow = nullptr;          // this row in the packed buffer
-            if (PACK) {
-                const int p = mode == HSADMM_MODE_CHANNEL ? it.row0 + rr : po.pos[it.g0 + rr];
-                if (p >= 0) drow = out + (int64_t)p * packed_row_len;
-            }
-            auto single = [&](int c) {
-                const int ch = div(c);
-                const float z = frozen1<R, false, WEIGHTED, RES>(a, Rrt, base + c, mc[ch] != 0, nullptr, al, bl, acc);
-                if (PACK && drow) {
-                    const int r = rank[ch];
-                    if (r >= 0) drow[r * it.khw + (c - ch * it.khw)] = z;
+    auto rows = [&](auto whole) {             // whole: no row has a tail
+        for (int rr = sub; rr < it.nr; rr += rows_at_once) {
+            const bool keep = mode == HSADMM_MODE_NONE || mode == HSADMM_MODE_CHANNEL || mask[it.g0 + rr] != 0;
+            const int64_t base = it.base + (int64_t)rr * row_len;
+            if (columns && keep) {
+                float* drow = nullptr;          // this row in the packed buffer
+                if (PACK) {
+                    const int p = mode == HSADMM_MODE_CHANNEL ? it.row0 + rr : po.pos[it.g0 + rr];
+                    if (p >= 0) drow = out + (int64_t)p * packed_row_len;
                 }
-            };
-            if (fours) {
-                const int nchunk = row_len >> 2;
+                auto single = [&](int c) {
+                    const int ch = div(c);
+                    const float z = frozen1<R, false, WEIGHTED, RES>(a, Rrt, base + c, mc[ch] != 0, nullptr, al, bl, acc);
+                    if (PACK && drow) {
+                        const int r = rank[ch];
+                        if (r >= 0) drow[r * it.khw + (c - ch * it.khw)] = z;
+                    }
+                };
                 for (int c = j; c < nchunk; c += lpr) {
                     const int col = c << 2;
                     bool pr[4];
@@ -262,24 +262,19 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
                         if (pc[3] >= 0) drow[pc[3]] = z.w;
                     }
                 }
-                if constexpr (!RES)
+                if constexpr (!decltype(whole)::value)
                     if (const int c = (row_len & ~3) + j; c < row_len) single(c);
-            } else {
-                for (int c = j; c < row_len; c += lpr) single(c);
+                continue;
             }
-            continue;
-        }
-        // a kept row of a FILTER or NONE layer is packed whole, at its rank (NONE: its own index)
-        float* d = nullptr;
-        if (PACK && !columns && keep) {
-            const int p = mode == HSADMM_MODE_NONE ? it.row0 + rr : po.pos[it.g0 + rr];
-            if (p >= 0) d = out + (int64_t)p * row_len;     // (mappings of another mask: the row is left out)
-        }
-        auto single = [&](int c) {
-            frozen1<R, PACK, WEIGHTED, RES>(a, Rrt, base + c, keep, d ? d + c : nullptr, al, bl, acc);
-        };
-        if (fours) {
-            const int nchunk = row_len >> 2;
+            // a kept row of a FILTER or NONE layer is packed whole, at its rank (NONE: its own index)
+            float* d = nullptr;
+            if (PACK && !columns && keep) {
+                const int p = mode == HSADMM_MODE_NONE ? it.row0 + rr : po.pos[it.g0 + rr];
+                if (p >= 0) d = out + (int64_t)p * row_len;     // (mappings of another mask: the row is left out)
+            }
+            auto single = [&](int c) {
+                frozen1<R, PACK, WEIGHTED, RES>(a, Rrt, base + c, keep, d ? d + c : nullptr, al, bl, acc);
+            };
             int c = j;
             for (; c + lpr < nchunk; c += 2 * lpr)
                 frozen4x2<R, PACK, WEIGHTED, RES>(a, Rrt, base + ((int64_t)c << 2), base + ((int64_t)(c + lpr) << 2), keep,
@@ -287,18 +282,20 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
             if (c < nchunk)
                 frozen4<R, PACK, WEIGHTED, RES>(a, Rrt, base + ((int64_t)c << 2), keep, keep, keep, keep,
                                                 d ? d + 4 * c : nullptr, al, bl, acc);
-            if constexpr (!RES)
+            if constexpr (!decltype(whole)::value)
                 if (const int c = (row_len & ~3) + j; c < row_len) single(c);
-        } else {
-            for (int c = j; c < row_len; c += lpr) single(c);
         }
-    }
+    };
+    if (RES && item_vec(it)) rows(std::true_type{});
+    else rows(std::false_type{});
 }
 
-// RES: the item's two intra-node residual sums also go to a.respart[4 * item + 0, 1].
+// RES: the item's two intra-node residual sums also go to a.respart[4 * item + 0, 1].  (With them two and four replicas get
+// the registers of three waves per SIMD, eight those of two: left to the compiler a retraining iteration on ResNet-50 of
+// width 48 takes 158.2 us for 156.3 us with 2 replicas, 230 us for 225 us with 8.)
 template <int R, bool PACK = false, bool WEIGHTED = false, bool RES = false>
-__global__ __launch_bounds__(kBlock) void project_frozen(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt,
-                                                         const uint8_t* __restrict__ mask, PackOut po)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, !RES || R < 2 ? 8 : R < 8 ? 3 : 2)))
+void project_frozen(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt, const uint8_t* __restrict__ mask, PackOut po)
 {
     if constexpr (RES) {
         double acc[2] = {0.0, 0.0};

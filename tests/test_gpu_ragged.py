@@ -101,3 +101,18 @@ def test_every_form_of_the_step_on_rows_that_are_not_whole_words(mode, R):
                     norms = r.view(np.uint64)
                 assert np.array_equal(r.view(np.uint64), norms), "norms differ in their last bits: " + case
     b.plan.close()
+
+
+@pytest.mark.parametrize("mode", [wk.MODE_NONE, wk.MODE_FILTER, wk.MODE_CHANNEL, wk.MODE_BOTH])
+@pytest.mark.parametrize("R", [1, 2, 4, 5, 8])
+def test_retraining_iteration_on_rows_that_are_not_whole_words(mode, R):
+    """The passes of an iteration after the masks are frozen, with and without the residual norms, under a mask of half the
+    groups: every output the oracle's, the norms to the bound of their own test."""
+    from tests.test_gpu_weighted import _check_weighted_frozen
+    wl = _workload(mode, R, 200 * R + mode)
+    W, U = wk.generate(wl)
+    rng = np.random.default_rng(9 * R + mode)
+    L = len(wl.layers)
+    a, b = rng.uniform(0.3, 1.0, L).astype(np.float32), rng.uniform(0.0, 0.7, L).astype(np.float32)
+    Zg, Vd = ((rng.standard_normal(wl.n_arena) * s).astype(np.float32) for s in (0.05, 0.01))
+    _check_weighted_frozen(wl, W, U, a, b, Zg, Vd, (rng.random(wl.groups_total) < 0.5).astype(np.uint8))
