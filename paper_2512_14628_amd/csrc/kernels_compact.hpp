@@ -193,10 +193,18 @@ __device__ __forceinline__ void gather_item(const WorkItem& it, const float* src
             const float* s1 = SUM ? src1 + it.base + (int64_t)rr * row_len : nullptr;
             float* d = out + (int64_t)p * row_len;
             const int nchunk = row_len >> 2;
-            for (int c = j; c < nchunk; c += lpr) {
-                v4f v = ld4(s + 4 * c);
-                if (SUM) v = v + ld4(s1 + 4 * c);
-                st4u(d + 4 * c, v);
+            if (item_vec(it)) {
+                for (int c = j; c < nchunk; c += lpr) {
+                    v4f v = ld4(s + 4 * c);
+                    if (SUM) v = v + ld4(s1 + 4 * c);
+                    st4u(d + 4 * c, v);
+                }
+            } else {
+                for (int c = j; c < nchunk; c += lpr) {          // (ordinary accesses, see expand_scatter)
+                    v4f v = ld4u(s + 4 * c);
+                    if (SUM) v = v + ld4u(s1 + 4 * c);
+                    st4u(d + 4 * c, v);
+                }
             }
             if (const int c = (row_len & ~3) + j; c < row_len) d[c] = SUM ? s[c] + s1[c] : s[c];
         }
@@ -383,6 +391,22 @@ __global__ __launch_bounds__(kBlock) void expand_scatter(const WorkItem* __restr
             }
         }
     };
+    // The same with ordinary accesses, for ragged rows: a wave's run of unaligned 128-bit accesses begins and ends inside a
+    // line that its neighbours touch too, and the caches put the pieces together.  Non-temporal / ordinary: exchange under a
+    // union, filter groups, ResNet-18 of width 125 228.4 / 224.1 us, bottleneck 2-3-4-2 of width 91 198.9 / 194.7 us (one
+    // float per lane 225.4 and 194.2 us, but 49.5 us against 42.7 us on a plain network of width 201).
+    auto put4u = [&](int64_t e, const v4f& z) {
+        st4u(dst + e, z);
+        if (DUAL) {
+            const v4f zi = ld4u(Zi + e);
+            const v4f d = zi - z;
+            st4u(Vd + e, ld4u(Vd + e) + d);
+            if (RES) {
+                s_ro = sqd4(s_ro, zi, z);
+                s_so = sqd4(s_so, z, ld4u(z_prev + e));
+            }
+        }
+    };
     auto put1 = [&](int64_t e, float z) {
         dst[e] = z;
         if (DUAL) {
@@ -411,8 +435,13 @@ __global__ __launch_bounds__(kBlock) void expand_scatter(const WorkItem* __restr
             const int64_t d = it.base + (int64_t)rr * row_len;
             const float* s = in + (int64_t)(p < 0 ? 0 : p) * row_len;
             const int nchunk = row_len >> 2;
-            if (p >= 0) for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, ld4u(s + 4 * c));
-            else for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, zero4);
+            if (item_vec(it)) {
+                if (p >= 0) for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, ld4u(s + 4 * c));
+                else for (int c = j; c < nchunk; c += lpr) put4(d + 4 * c, zero4);
+            } else {
+                if (p >= 0) for (int c = j; c < nchunk; c += lpr) put4u(d + 4 * c, ld4u(s + 4 * c));
+                else for (int c = j; c < nchunk; c += lpr) put4u(d + 4 * c, zero4);
+            }
             if (const int c = (row_len & ~3) + j; c < row_len) put1(d + c, p >= 0 ? s[c] : 0.f);
         }
     } else {
