@@ -175,23 +175,26 @@ bool spans_overlap(const float* a, const float* b, int64_t n)
     return x < y + bytes && y < x + bytes;
 }
 
-int ceil_pow2(int x)
-{
-    int p = 1;
-    while (p < x) p *= 2;
-    return p;
-}
-
 // Row items of one layer.  `mode` is the mode the kernels should see (compact / expand walk a
 // CHANNEL layer row by row as well).
-void add_row_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int mode)
+// A row has a lane for every 128-bit access; the one to three floats after a ragged row's words go to a lane each, so it has
+// four lanes at least.  An item is about kTileElems elements of whole bundles of rows, a bundle being the rows that keep a
+// workgroup busy.  For ragged rows a bundle is counted as if every float had a lane: some kernels walk them so, and the
+// scratch, which has a record per item, stays what it is for items of that length.
+// Rows of kWideRow floats and more are shared by the whole workgroup and are an item each; ragged ones are four to an item
+// unless `fine` (a plain network of width 201, most of its rows 3618 floats, both constraints: a step in 97.5 us with one,
+// 127.4 us with four).
+void add_row_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int mode, bool fine)
 {
     const bool vec = (d.row_len % 4) == 0;
-    // 128-bit accesses per row; the last one to three floats of a ragged row go to a lane each, so it gets four lanes
-    const int units = vec ? d.row_len / 4 : std::max(4, d.row_len / 4);
     int lpr, bundle;
-    if (d.row_len >= kWideRow) { lpr = kBlock; bundle = 1; }
-    else { lpr = units >= kWave ? kWave : ceil_pow2(units); bundle = kWaves * (kWave / lpr); }
+    if (d.row_len >= kWideRow) {
+        lpr = kBlock;
+        bundle = vec || fine ? 1 : kWaves;
+    } else {
+        lpr = lanes_of(vec ? d.row_len / 4 : std::max(4, d.row_len / 4));
+        bundle = kWaves * (kWave / lanes_of(vec ? d.row_len / 4 : d.row_len));
+    }
     int64_t want = kTileElems / (int64_t)d.row_len;
     if (want < bundle) want = bundle;
     want = (want + bundle - 1) / bundle * bundle;
@@ -377,6 +380,110 @@ int run_scan(const hsadmm_plan* p, const uint8_t* mask, char* ws, hipStream_t s,
     return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
 }
 
+// The plan's tables and the places of the scratch, from the layers.  Called again it starts over.
+int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* nest, int32_t L, bool fine,
+            std::vector<uint16_t>& group_layer)
+{
+    for (auto* items : {&p->items_proj, &p->items_rows, &p->items_fix, &p->items_none, &p->items_plain, &p->items_bfinal,
+                        &p->items_chan, &p->items_both})
+        items->clear();
+    p->dev_layers.clear();
+    p->both_layers.clear();
+    int64_t gb = 0, cp = 0, cap = 0, poff = 0, nest_bytes = 0;
+    int32_t seg = 0, kstart = 0;
+    group_layer.clear();
+    for (int32_t l = 0; l < L; ++l) {
+        const hsadmm_layer_t& x = layers[l];
+        DevLayer d{};
+        d.elem_off = x.elem_off;
+        d.c_out = x.c_out; d.c_in = x.c_in; d.khw = x.khw; d.mode = x.mode;
+        const bool both = x.mode == HSADMM_MODE_BOTH;
+        const bool has_colsums = x.mode == HSADMM_MODE_CHANNEL || both;
+        d.G = x.mode == HSADMM_MODE_CHANNEL ? x.c_in : (both ? x.c_out + x.c_in : x.c_out);
+        d.k = x.mode == HSADMM_MODE_NONE ? d.G : x.k;
+        d.k_in = both ? x.k_in : 0;
+        d.seg0 = seg;
+        if (nest && nest[l].span >= 1) {
+            // the selection's notes about the runs: their keys, the channels' shifted key patterns (8 bytes
+            // each), the runs' ranks and kept list (4 bytes each), the runs' mask
+            const int64_t runs = x.c_in / nest[l].span;
+            d.span = nest[l].span;
+            d.k_coarse = nest[l].k_coarse;
+            d.nest_off = nest_bytes;
+            p->any_nested = true;
+            nest_bytes += (int64_t)align_up((size_t)(8 * runs + 8 * (int64_t)x.c_in + 8 * runs + runs), 8);
+        }
+        if (gb + d.G > INT32_MAX) return HSADMM_ERR_UNSUPPORTED;    // group indices are int32
+        d.group_base = (int32_t)gb;
+        d.row_len = x.c_in * x.khw;
+        const int tile_rows = both ? kBothRows : kChanRows;
+        d.n_rowblocks = (x.c_out + tile_rows - 1) / tile_rows;
+        d.colpart_off = cp;
+        if (x.mode == HSADMM_MODE_CHANNEL) d.unit = (int64_t)x.c_out * x.khw;
+        else if (x.mode == HSADMM_MODE_FILTER) d.unit = d.row_len;
+        else if (both) d.unit = x.khw;
+        else d.unit = (int64_t)x.c_out * d.row_len;
+        if (has_colsums) cp += (int64_t)d.n_rowblocks * d.row_len;
+        // where the layer starts in the packed buffer / in kept_idx when the mask is the plan's own selection
+        d.packed_off = poff;
+        d.kept_start = kstart;
+        const int32_t c0 = x.mode == HSADMM_MODE_NONE ? d.G : x.k;
+        poff += packed_size(x.mode, d.unit, c0, d.k_in, p->pack_align);
+        kstart += c0 + d.k_in;
+        gb += d.G;
+        cap += (int64_t)x.c_out * d.row_len;
+        cap = (cap + p->pack_align - 1) / p->pack_align * p->pack_align;
+        d.rows_item0 = (int32_t)p->items_rows.size();
+        add_row_items(p->items_rows, l, d, x.mode, fine);
+        if (x.mode == HSADMM_MODE_NONE) add_row_items(p->items_none, l, d, x.mode, fine);
+        if (!has_colsums) add_row_items(p->items_plain, l, d, x.mode, fine);
+        d.rows_items = (int32_t)p->items_rows.size() - d.rows_item0;
+        if (x.mode == HSADMM_MODE_CHANNEL) {
+            add_tile_items(p->items_proj, l, d, kChanRows);
+            add_row_items(p->items_chan, l, d, x.mode, fine);
+        } else {
+            add_row_items(p->items_proj, l, d, x.mode, fine);
+            if (x.mode == HSADMM_MODE_FILTER) add_row_items(p->items_fix, l, d, x.mode, fine);
+            if (x.mode == HSADMM_MODE_BOTH) {
+                add_row_items(p->items_bfinal, l, d, x.mode, fine);
+            }
+        }
+        if (both) {
+            add_tile_items(p->items_both, l, d, kBothRows);
+            p->both_layers.push_back(l);
+        }
+        p->dev_layers.push_back(d);
+        // scan segments: at most 2 * HSADMM_MAX_LAYERS = 8192, so an id fits below bit 15
+        for (int32_t g = 0; g < d.G; ++g) {
+            const int32_t sg = seg + ((both && g >= x.c_out) ? 1 : 0);
+            group_layer.push_back((uint16_t)(sg | (x.mode == HSADMM_MODE_NONE ? 0x8000 : 0)));
+        }
+        seg += both ? 2 : 1;
+    }
+    p->n_segments = seg;
+    p->groups_total = gb;
+    p->colpart_total = cp;
+    p->packed_capacity = cap;
+    size_t off = 0;
+    p->ws.key = off;        off = align_up(off + sizeof(double) * (size_t)gb, 256);
+    p->ws.colpart = off;    off = align_up(off + sizeof(double) * (size_t)(cp ? cp : 1), 256);
+    p->ws.pos = off;        off = align_up(off + sizeof(int32_t) * (size_t)gb, 256);
+    p->ws.cnt = off;        off = align_up(off + sizeof(int32_t) * (size_t)L * 3, 256);
+    p->ws.layer_off = off;  off = align_up(off + sizeof(int64_t) * (size_t)(L + 1), 256);
+    p->ws.kept_idx = off;   off = align_up(off + sizeof(int32_t) * (size_t)gb, 256);
+    p->ws.respart = off;    off = align_up(off + sizeof(double) * 4 * p->items_rows.size(), 256);
+    p->ws.work = off;       off = align_up(off + sizeof(int32_t) * (kWorkHeader + p->items_rows.size()), 256);
+    p->ws.rowres = off;     off = align_up(off + sizeof(double) * 4 * (size_t)gb, 256);
+    p->ws.pred = off;       off = align_up(off + sizeof(int32_t) * (size_t)gb, 256);
+    p->ws.est_cnt = off;    off = align_up(off + sizeof(unsigned int) * (size_t)L * kSampleKeys, 256);
+    p->ws.est_keys = off;   off = align_up(off + sizeof(double) * (size_t)L * kSampleKeys, 256);
+    p->ws.est_thr = off;    off = align_up(off + sizeof(double) * (size_t)L, 256);
+    p->ws.est_thr_tag = off; off = align_up(off + sizeof(unsigned int) * (size_t)L, 256);
+    p->ws.nest = off;       off = align_up(off + (size_t)nest_bytes, 256);
+    p->ws.total = off;
+    return HSADMM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -428,98 +535,11 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
         p->pack_align = pack_align_elems;
         p->layers.assign(layers, layers + L);
         p->arena_elems = prev_end;
-        int64_t gb = 0, cp = 0, cap = 0, poff = 0, nest_bytes = 0;
-        int32_t seg = 0, kstart = 0;
-        group_layer.clear();
-        for (int32_t l = 0; l < L; ++l) {
-            const hsadmm_layer_t& x = layers[l];
-            DevLayer d{};
-            d.elem_off = x.elem_off;
-            d.c_out = x.c_out; d.c_in = x.c_in; d.khw = x.khw; d.mode = x.mode;
-            const bool both = x.mode == HSADMM_MODE_BOTH;
-            const bool has_colsums = x.mode == HSADMM_MODE_CHANNEL || both;
-            d.G = x.mode == HSADMM_MODE_CHANNEL ? x.c_in : (both ? x.c_out + x.c_in : x.c_out);
-            d.k = x.mode == HSADMM_MODE_NONE ? d.G : x.k;
-            d.k_in = both ? x.k_in : 0;
-            d.seg0 = seg;
-            if (nest && nest[l].span >= 1) {
-                // the selection's notes about the runs: their keys, the channels' shifted key patterns (8 bytes
-                // each), the runs' ranks and kept list (4 bytes each), the runs' mask
-                const int64_t runs = x.c_in / nest[l].span;
-                d.span = nest[l].span;
-                d.k_coarse = nest[l].k_coarse;
-                d.nest_off = nest_bytes;
-                p->any_nested = true;
-                nest_bytes += (int64_t)align_up((size_t)(8 * runs + 8 * (int64_t)x.c_in + 8 * runs + runs), 8);
-            }
-            if (gb + d.G > INT32_MAX) { delete p; return HSADMM_ERR_UNSUPPORTED; }    // group indices are int32
-            d.group_base = (int32_t)gb;
-            d.row_len = x.c_in * x.khw;
-            const int tile_rows = both ? kBothRows : kChanRows;
-            d.n_rowblocks = (x.c_out + tile_rows - 1) / tile_rows;
-            d.colpart_off = cp;
-            if (x.mode == HSADMM_MODE_CHANNEL) d.unit = (int64_t)x.c_out * x.khw;
-            else if (x.mode == HSADMM_MODE_FILTER) d.unit = d.row_len;
-            else if (both) d.unit = x.khw;
-            else d.unit = (int64_t)x.c_out * d.row_len;
-            if (has_colsums) cp += (int64_t)d.n_rowblocks * d.row_len;
-            // where the layer starts in the packed buffer / in kept_idx when the mask is the plan's own selection
-            d.packed_off = poff;
-            d.kept_start = kstart;
-            const int32_t c0 = x.mode == HSADMM_MODE_NONE ? d.G : x.k;
-            poff += packed_size(x.mode, d.unit, c0, d.k_in, pack_align_elems);
-            kstart += c0 + d.k_in;
-            gb += d.G;
-            cap += (int64_t)x.c_out * d.row_len;
-            cap = (cap + pack_align_elems - 1) / pack_align_elems * pack_align_elems;
-            d.rows_item0 = (int32_t)p->items_rows.size();
-            add_row_items(p->items_rows, l, d, x.mode);
-            if (x.mode == HSADMM_MODE_NONE) add_row_items(p->items_none, l, d, x.mode);
-            if (!has_colsums) add_row_items(p->items_plain, l, d, x.mode);
-            d.rows_items = (int32_t)p->items_rows.size() - d.rows_item0;
-            if (x.mode == HSADMM_MODE_CHANNEL) {
-                add_tile_items(p->items_proj, l, d, kChanRows);
-                add_row_items(p->items_chan, l, d, x.mode);
-            } else {
-                add_row_items(p->items_proj, l, d, x.mode);
-                if (x.mode == HSADMM_MODE_FILTER) add_row_items(p->items_fix, l, d, x.mode);
-                if (x.mode == HSADMM_MODE_BOTH) {
-                    add_row_items(p->items_bfinal, l, d, x.mode);
-                }
-            }
-            if (both) {
-                add_tile_items(p->items_both, l, d, kBothRows);
-                p->both_layers.push_back(l);
-            }
-            p->dev_layers.push_back(d);
-            // scan segments: at most 2 * HSADMM_MAX_LAYERS = 8192, so an id fits below bit 15
-            for (int32_t g = 0; g < d.G; ++g) {
-                const int32_t sg = seg + ((both && g >= x.c_out) ? 1 : 0);
-                group_layer.push_back((uint16_t)(sg | (x.mode == HSADMM_MODE_NONE ? 0x8000 : 0)));
-            }
-            seg += both ? 2 : 1;
-        }
-        p->n_segments = seg;
-        p->groups_total = gb;
-        p->colpart_total = cp;
-        p->packed_capacity = cap;
-        size_t off = 0;
-        p->ws.key = off;        off = align_up(off + sizeof(double) * (size_t)gb, 256);
-        p->ws.colpart = off;    off = align_up(off + sizeof(double) * (size_t)(cp ? cp : 1), 256);
-        p->ws.pos = off;        off = align_up(off + sizeof(int32_t) * (size_t)gb, 256);
-        p->ws.cnt = off;        off = align_up(off + sizeof(int32_t) * (size_t)L * 3, 256);
-        p->ws.layer_off = off;  off = align_up(off + sizeof(int64_t) * (size_t)(L + 1), 256);
-        p->ws.kept_idx = off;   off = align_up(off + sizeof(int32_t) * (size_t)gb, 256);
-        p->ws.respart = off;    off = align_up(off + sizeof(double) * 4 * p->items_rows.size(), 256);
-        p->ws.work = off;       off = align_up(off + sizeof(int32_t) * (kWorkHeader + p->items_rows.size()), 256);
-        p->ws.rowres = off;     off = align_up(off + sizeof(double) * 4 * (size_t)gb, 256);
-        p->ws.pred = off;       off = align_up(off + sizeof(int32_t) * (size_t)gb, 256);
-        p->ws.est_cnt = off;    off = align_up(off + sizeof(unsigned int) * (size_t)L * kSampleKeys, 256);
-        p->ws.est_keys = off;   off = align_up(off + sizeof(double) * (size_t)L * kSampleKeys, 256);
-        p->ws.est_thr = off;    off = align_up(off + sizeof(double) * (size_t)L, 256);
-        p->ws.est_thr_tag = off; off = align_up(off + sizeof(unsigned int) * (size_t)L, 256);
-        p->ws.nest = off;       off = align_up(off + (size_t)nest_bytes, 256);
-        p->ws.total = off;
+        // (a plan whose scratch would outgrow the static array with one wide ragged row per item takes four: it has workgroups
+        // enough, and hsadmm_project_compact_static takes it as long as its scratch fits either way)
+        int rc = lay_out(p, layers, nest, L, true, group_layer);
+        if (rc == HSADMM_OK && p->ws.total > kStaticScratchBytes) rc = lay_out(p, layers, nest, L, false, group_layer);
+        if (rc != HSADMM_OK) { delete p; return rc; }
         // The estimate's item order: of every FILTER layer the items that cover its first rows (a sixteenth of them,
         // 16 at least, kSampleKeys at most), then everything else in the usual order.
         bool only_rows = true, any_filter = false;

@@ -137,6 +137,14 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "WorkItem layout");
 
+// Lanes that share a row of n accesses: a power of two, a wave at most.
+constexpr int lanes_of(int n)
+{
+    int p = 1;
+    while (p < n && p < kWave) p *= 2;
+    return p;
+}
+
 __device__ __forceinline__ int item_mode(const WorkItem& it) { return it.flags & 3; }
 // modes whose packed rows hold a subset of the columns (CHANNEL, BOTH)
 __device__ __forceinline__ bool mode_has_channels(int mode) { return (mode & HSADMM_MODE_CHANNEL) != 0; }

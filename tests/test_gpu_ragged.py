@@ -116,3 +116,24 @@ def test_retraining_iteration_on_rows_that_are_not_whole_words(mode, R):
     a, b = rng.uniform(0.3, 1.0, L).astype(np.float32), rng.uniform(0.0, 0.7, L).astype(np.float32)
     Zg, Vd = ((rng.standard_normal(wl.n_arena) * s).astype(np.float32) for s in (0.05, 0.01))
     _check_weighted_frozen(wl, W, U, a, b, Zg, Vd, (rng.random(wl.groups_total) < 0.5).astype(np.uint8))
+
+
+def test_wide_rows_that_are_not_whole_words_ask_for_no_more_scratch_than_the_static_array_holds():
+    """240 000 rows of 2049 floats: 52 bytes of scratch a row and 36 an item of four rows fit the static array (16 MiB),
+    which hsadmm_project_compact_static therefore takes; 36 bytes for every row would not."""
+    import paper_2512_14628_amd as pkg
+    rows = 240000
+    plan = pkg.Plan(dict(elem_off=[0], c_out=[rows], c_in=[2049], khw=[1], mode=[wk.MODE_FILTER], k=[rows // 2], k_in=[0]))
+    assert plan.workspace_bytes <= 16 << 20, plan.workspace_bytes
+    plan.close()
+
+
+@pytest.mark.parametrize("mode", [wk.MODE_FILTER, wk.MODE_CHANNEL, wk.MODE_BOTH])
+def test_wide_rows_that_are_not_whole_words_in_a_plan_that_outgrows_the_static_array(mode):
+    """350 000 groups beside them bring the plan's scratch over 16 MiB, where such rows come four to a work item."""
+    from tests.test_gpu_parity import _run
+    shapes = [(350000, 1, 1, wk.MODE_NONE, 350000)]
+    for rows, n in ((37, 2050), (6, 3619), (1, 2049)):
+        shapes.append((rows, n, 1, mode, max(1, (n if mode == wk.MODE_CHANNEL else rows) // 2)) +
+                      ((n // 3,) if mode == wk.MODE_BOTH else ()))
+    _run(wk.custom_workload(shapes, R=3, seed=40 + mode, sigma_replica=0.03), want_wbar=True, want_sqnorm=True)
