@@ -380,6 +380,8 @@ int run_scan(const hsadmm_plan* p, const uint8_t* mask, char* ws, hipStream_t s,
     return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
 }
 
+constexpr int64_t kFineRowsMaxElems = 20ll << 20;     // (see there)
+
 // The plan's tables and the places of the scratch, from the layers.  Called again it starts over.
 int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* nest, int32_t L, bool fine,
             std::vector<uint16_t>& group_layer)
@@ -392,6 +394,13 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
     int64_t gb = 0, cp = 0, cap = 0, poff = 0, nest_bytes = 0;
     int32_t seg = 0, kstart = 0;
     group_layer.clear();
+    // Gather and expansion give a wave a whole row of a CHANNEL or BOTH layer when an item has four.  A small plan needs the
+    // workgroups of one wide ragged row per item more: exchange under a union, both constraints, with one / with four a
+    // plain network of width 201 (2.9 M elements) 72 / 96.5 us, one of four basic blocks of width 117 (17 M) 123 / 126.8,
+    // but ResNet-18 of width 125 (42 M) 257 / 251 us.
+    int64_t n_elems = 0;
+    for (int32_t l = 0; l < L; ++l) n_elems += (int64_t)layers[l].c_out * layers[l].c_in * layers[l].khw;
+    const bool small = n_elems < kFineRowsMaxElems;
     for (int32_t l = 0; l < L; ++l) {
         const hsadmm_layer_t& x = layers[l];
         DevLayer d{};
@@ -434,7 +443,7 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
         cap += (int64_t)x.c_out * d.row_len;
         cap = (cap + p->pack_align - 1) / p->pack_align * p->pack_align;
         d.rows_item0 = (int32_t)p->items_rows.size();
-        add_row_items(p->items_rows, l, d, x.mode, fine);
+        add_row_items(p->items_rows, l, d, x.mode, fine && (!has_colsums || small));
         if (x.mode == HSADMM_MODE_NONE) add_row_items(p->items_none, l, d, x.mode, fine);
         if (!has_colsums) add_row_items(p->items_plain, l, d, x.mode, fine);
         d.rows_items = (int32_t)p->items_rows.size() - d.rows_item0;
