@@ -218,9 +218,10 @@ void add_row_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int
 }
 
 // Tiles of (rows_per_block rows) x (one column strip); d.n_rowblocks must have been set for the same block height.
-void add_tile_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int rows_per_block)
+// A lane owns four adjacent columns of whole-word rows, and of ragged ones too if `wide_strips`, else one.
+void add_tile_items(std::vector<WorkItem>& out, int layer, const DevLayer& d, int rows_per_block, bool wide_strips)
 {
-    const bool vec = d.row_len >= 4;
+    const bool vec = (d.row_len % 4) == 0 || (wide_strips && d.row_len >= 4);
     const int strip_cols = kWave * (vec ? 4 : 1);
     const int nstrips = (d.row_len + strip_cols - 1) / strip_cols;
     for (int r0 = 0; r0 < d.c_out; r0 += rows_per_block) {
@@ -380,7 +381,9 @@ int run_scan(const hsadmm_plan* p, const uint8_t* mask, char* ws, hipStream_t s,
     return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
 }
 
-constexpr int64_t kFineRowsMaxElems = 20ll << 20;     // (see there)
+constexpr int64_t kFineRowsMaxElems = 20ll << 20;     // (see lay_out)
+constexpr int64_t kWideStripsMinTiles = 512;          // ... two per compute unit
+static_assert(kChanRows == kBothRows, "the tiles of both kinds of layer are counted alike");
 
 // The plan's tables and the places of the scratch, from the layers.  Called again it starts over.
 int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* nest, int32_t L, bool fine,
@@ -401,6 +404,18 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
     int64_t n_elems = 0;
     for (int32_t l = 0; l < L; ++l) n_elems += (int64_t)layers[l].c_out * layers[l].c_in * layers[l].khw;
     const bool small = n_elems < kFineRowsMaxElems;
+    // Strips of 64 columns make four times the workgroups that strips of 256 make of a ragged layer, and a tile is a serial
+    // walk over up to 16 rows: below two narrow tiles per compute unit in the whole plan, narrow strips win.  Weighted
+    // step, channel groups, 8 replicas, narrow / wide: plain networks of width 45 (81 tiles) 41.2 / 49.3 us, 101 (383) 81.7 /
+    // 82.7, 143 (685) 126.1 / 121.3.
+    int64_t narrow_tiles = 0;
+    for (int32_t l = 0; l < L; ++l) {
+        if (!mode_has_channels(layers[l].mode)) continue;
+        const int row_len = layers[l].c_in * layers[l].khw;
+        const int cols = kWave * (row_len % 4 == 0 ? 4 : 1);
+        narrow_tiles += (int64_t)((layers[l].c_out + kChanRows - 1) / kChanRows) * ((row_len + cols - 1) / cols);
+    }
+    const bool wide_strips = narrow_tiles >= kWideStripsMinTiles;
     for (int32_t l = 0; l < L; ++l) {
         const hsadmm_layer_t& x = layers[l];
         DevLayer d{};
@@ -448,7 +463,7 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
         if (!has_colsums) add_row_items(p->items_plain, l, d, x.mode, fine);
         d.rows_items = (int32_t)p->items_rows.size() - d.rows_item0;
         if (x.mode == HSADMM_MODE_CHANNEL) {
-            add_tile_items(p->items_proj, l, d, kChanRows);
+            add_tile_items(p->items_proj, l, d, kChanRows, wide_strips);
             add_row_items(p->items_chan, l, d, x.mode, fine);
         } else {
             add_row_items(p->items_proj, l, d, x.mode, fine);
@@ -458,7 +473,7 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
             }
         }
         if (both) {
-            add_tile_items(p->items_both, l, d, kBothRows);
+            add_tile_items(p->items_both, l, d, kBothRows, wide_strips);
             p->both_layers.push_back(l);
         }
         p->dev_layers.push_back(d);

@@ -327,6 +327,26 @@ __device__ __forceinline__ void project_tile(const WorkItem& it, const ProjectAr
                     finish4(e0, s0, u0);
                     finish4(e1, s1, u1);
                 }
+            } else {
+                auto finish1 = [&](int64_t e, float s, float u) {
+                    const float wb = s * a.inv_R;
+                    if (a.park_mean) st1(a.Z + e, wb);
+                    const float v = wb + u;
+                    acc0 = fma((double)v, (double)v, acc0);
+                };
+                for (; rr + kWaves < it.nr; rr += 2 * kWaves) {
+                    const int64_t e0 = it.base + (int64_t)rr * row_len + col, e1 = e0 + (int64_t)kWaves * row_len;
+                    float s0 = ld1(a.W[0] + e0), s1 = ld1(a.W[0] + e1);
+#pragma unroll
+                    for (int r = 1; r < R; ++r) {
+                        const float w0 = ld1(a.W[r] + e0), w1 = ld1(a.W[r] + e1);
+                        s0 = s0 + w0;
+                        s1 = s1 + w1;
+                    }
+                    const float u0 = ld1(a.Ur + e0), u1 = ld1(a.Ur + e1);
+                    finish1(e0, s0, u0);
+                    finish1(e1, s1, u1);
+                }
             }
         }
         for (; rr < it.nr; rr += kWaves) {

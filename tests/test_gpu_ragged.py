@@ -137,3 +137,37 @@ def test_wide_rows_that_are_not_whole_words_in_a_plan_that_outgrows_the_static_a
         shapes.append((rows, n, 1, mode, max(1, (n if mode == wk.MODE_CHANNEL else rows) // 2)) +
                       ((n // 3,) if mode == wk.MODE_BOTH else ()))
     _run(wk.custom_workload(shapes, R=3, seed=40 + mode, sigma_replica=0.03), want_wbar=True, want_sqnorm=True)
+
+
+@pytest.mark.parametrize("mode", [wk.MODE_CHANNEL, wk.MODE_BOTH])
+@pytest.mark.parametrize("R", [1, 4, 5])
+def test_column_tiles_of_ragged_rows_four_columns_to_a_lane(mode, R):
+    """A plan of 512 tiles and more takes ragged rows four columns to a lane, the last lane overlapping its neighbour;
+    the plans above are smaller and take one.  A layer of 512 whole-word tiles brings this one over the line."""
+    from tests.test_gpu_hinted import _Bufs, _hinted_step, record_of
+    from tests.test_gpu_parity import _run
+    import oracle
+    shapes = [(8192, 1024, 1, wk.MODE_CHANNEL, 300)]
+    for n in (4, 5, 6, 7, 63, 255, 257, 258, 259, 511, 1023, 2049, 2051):
+        rows = 70 if n < 300 else 5
+        shapes.append((rows, n, 1, mode, (n if mode == wk.MODE_CHANNEL else rows) // 2) +
+                      ((n // 2,) if mode == wk.MODE_BOTH else ()))
+    wl = wk.custom_workload(shapes, R=R, seed=60 + R + mode, sigma_replica=0.03)
+    _run(wl, want_wbar=True, want_sqnorm=True)
+    # ... and under a right prediction with the dual out of place, where tiles write and pack
+    W, U = wk.generate(wl)
+    t = wl.table()
+    ref = oracle.project(t, W, U)
+    refc = oracle.compact(t, ref["Z"], ref["mask"])
+    b = _Bufs(wl, W, U, 1)
+    b.reset()
+    _hinted_step(b, torch.from_numpy(record_of(wl, ref["mask"])).to(b.U.device), out_of_place=True)
+    got = b.outputs()
+    assert np.array_equal(got["mask"], ref["mask"])
+    n = int(refc["layer_off"][-1])
+    assert np.array_equal(got["packed"][:n].view(np.uint32), refc["packed"][:n].view(np.uint32))
+    for key in ("Z", "U"):
+        for l in wl.layers:
+            sl = slice(l.elem_off, l.elem_off + l.n)
+            assert np.array_equal(got[key][sl].view(np.uint32), ref[key][sl].view(np.uint32)), (key, l.name)
+    b.plan.close()
