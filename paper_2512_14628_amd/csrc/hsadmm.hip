@@ -281,24 +281,20 @@ hipError_t launch(const hsadmm_plan* cp, int kid, void (*kernel)(KArgs...), unsi
     return launch_spare(cp, kid, kernel, grid, block, 0u, s, args...);
 }
 
-// A pass 1 of many replicas runs as many input streams per wave, and with every wave the registers allow in flight they
-// crowd the memory: three workgroups per compute unit (two where the staging takes 38 KB each and there are eight
-// replicas or more) move the same bytes sooner.  Measured without / with the bound: predicted pass 1 ResNet-50, 4
-// replicas 123.8 / 120.0 us; column sums of ResNet-152, 4 replicas 270.9 / 266.6 us, weighted 372.0 / 366.7 us; pass 1
-// under both constraints 104.7 / 101.2 us; staged pass 1 of the four times wider ResNet-50, 8 replicas 3.07 / 2.96 ms
-// (with 4 replicas it loses: 123.4 / 125.1 us).  One and two replicas are left alone: nothing to gain
-// (ResNet-18 34.0 / 33.4 us).
-constexpr unsigned kSpareThree = 40u << 10;      // beside the 8 KB of the tiles' sums: three workgroups in 160 KB
-constexpr unsigned kSpareStaged = 20u << 10;     // beside the 38 KB of the staging: two
-// RC: the replica count compiled into the kernel (0: a loop at run time, which has few loads in flight per wave and
-// needs every wave).
-constexpr unsigned spare_lds(int RC) { return RC >= 3 ? kSpareThree : 0u; }
-constexpr unsigned spare_lds_staged(int RC) { return RC >= 8 ? kSpareStaged : 0u; }
+// The estimating pass 1 with eight replicas: two workgroups per compute unit instead of the four its staging leaves room for
+// (see pass1_waves; held to two through its registers it is scheduled worse).  The four times wider ResNet-50, 8 replicas,
+// a step without 4110 us, with 3994 us, through the registers 4068 us.  With 4 replicas it loses.
+constexpr unsigned kSpareStaged = 20u << 10;
+constexpr unsigned kStagedLds = 2u * kStageElems * sizeof(float) + kStageRows * (sizeof(double) + 1) + (kSampleKeys + 2) * sizeof(double);
+constexpr unsigned kLdsPerUnit = 160u << 10, kLdsPerWorkgroup = 64u << 10;
+static_assert(kStagedLds + kSpareStaged <= kLdsPerWorkgroup && 3 * (kStagedLds + kSpareStaged) > kLdsPerUnit,
+              "two workgroups, not three, and each within what a launch may ask for");
+constexpr unsigned spare_lds_staged(int RC) { return RC == 8 ? kSpareStaged : 0u; }
 
 template <int R>
 hipError_t launch_pass1(const hsadmm_plan* p, const ProjectArgs& a, int Rrt, hipStream_t s)
 {
-    return launch_spare(p, kPass1, project_pass1<R>, (unsigned)p->items_proj.size(), kBlock, spare_lds(R), s,
+    return launch(p, kPass1, project_pass1<R>, (unsigned)p->items_proj.size(), kBlock, s,
                   (const WorkItem*)p->d_items_proj, a, Rrt);
 }
 
@@ -764,9 +760,8 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
             });
         else
             e = for_replica_count<true>(R, [&](auto c) {
-                return launch_spare(p, kPass1Hinted, project_pass1_hinted<decltype(c)::value>,
-                                    (unsigned)p->items_proj.size(), kBlock, spare_lds(decltype(c)::value), s,
-                                    (const WorkItem*)p->d_items_proj, a, (int)R, h);
+                return launch(p, kPass1Hinted, project_pass1_hinted<decltype(c)::value>, (unsigned)p->items_proj.size(),
+                              kBlock, s, (const WorkItem*)p->d_items_proj, a, (int)R, h);
             });
     } else if (est) {
         // the prediction is formed inside pass 1 and recorded for the repair pass; the selection hands out the offsets
@@ -1214,13 +1209,11 @@ static int project_weighted_impl(const hsadmm_plan_t* p, const float* const* W_r
         });
     } else if (residuals)
         e = for_replica_count<false>(R, [&](auto c) {
-            return launch_spare(p, kWKeys, weighted_pass1<decltype(c)::value, true>, grid, kBlock,
-                                spare_lds(decltype(c)::value), s, items, w, (int)R);
+            return launch(p, kWKeys, weighted_pass1<decltype(c)::value, true>, grid, kBlock, s, items, w, (int)R);
         });
     else
         e = for_replica_count<false>(R, [&](auto c) {
-            return launch_spare(p, kWKeys, weighted_pass1<decltype(c)::value>, grid, kBlock,
-                                spare_lds(decltype(c)::value), s, items, w, (int)R);
+            return launch(p, kWKeys, weighted_pass1<decltype(c)::value>, grid, kBlock, s, items, w, (int)R);
         });
     if (e != hipSuccess) return HSADMM_ERR_HIP;
     // (the weighted candidate of a BOTH layer is formed again from its parked mean, U, Zg and Vd)

@@ -137,6 +137,21 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "WorkItem layout");
 
+// Waves per SIMD (a workgroup is one on each of the four) that a kernel is held to through its registers: a pass 1 reads as
+// many streams per wave as there are replicas, and with every wave the registers allow in flight they crowd the memory.  For
+// the kernels and compiled replica counts where it was measured to help; 8 is every wave there is.  Without / with, us:
+//   pass 1, R = 3, 4 (3)            ResNet-152, channel groups 484 / 480, 531 / 526; both constraints 481 / 474, 527 / 510;
+//                                   R = 1, 2 and 8: nothing
+//   predicted pass 1, R = 3, 4 (3)  ResNet-152, filter groups 304 / 292, 347 / 329; R = 8: nothing
+//   weighted pass 1, R = 4 (3)      ResNet-152, filter groups 690 / 678; with norms 777 / 755
+//   ... R = 8                       loses without the norms (849 / 867), gains with them (2): 967 / 928
+// Not the predicted pass 1 with column tiles (ResNet-152 with 3 replicas: channel groups 351 / 346, but both constraints 361 /
+// 375), nor the weighted one (with 4: filter groups 561 / 545, both constraints 855 / 867), nor run-time replica counts, which
+// have few loads in flight per wave and need them all.
+constexpr int kAllWaves = 8;
+constexpr int pass1_waves(int R) { return R == 3 || R == 4 ? 3 : kAllWaves; }
+constexpr int weighted_pass1_waves(int R, bool RES) { return R == 4 ? 3 : (RES && R == 8 ? 2 : kAllWaves); }
+
 // Lanes that share a row of n accesses: a power of two, a wave at most.
 constexpr int lanes_of(int n)
 {

@@ -294,7 +294,7 @@ __device__ __forceinline__ void frozen_item(const WorkItem& it, const ProjectArg
 // the registers of three waves per SIMD, eight those of two: left to the compiler a retraining iteration on ResNet-50 of
 // width 48 takes 158.2 us for 156.3 us with 2 replicas, 230 us for 225 us with 8.)
 template <int R, bool PACK = false, bool WEIGHTED = false, bool RES = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, !RES || R < 2 ? 8 : R < 8 ? 3 : 2)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, !RES || R < 2 ? kAllWaves : R < 8 ? 3 : 2)))
 void project_frozen(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt, const uint8_t* __restrict__ mask, PackOut po)
 {
     if constexpr (RES) {

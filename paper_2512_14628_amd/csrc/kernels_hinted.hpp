@@ -314,8 +314,8 @@ __global__ __launch_bounds__(kBlock) void composite_colsums_hinted(const WorkIte
 // the prediction when the dual is written out of place (TILES: an instantiation of its own for plans with such layers,
 // so that the other plans' kernel keeps its registers); else they only sum here and are written after the selection.
 template <int R, bool TILES = false>
-__global__ __launch_bounds__(kBlock) void project_pass1_hinted(const WorkItem* __restrict__ items, ProjectArgs a,
-                                                               int Rrt, HintArgs h)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, TILES ? kAllWaves : pass1_waves(R))))
+void project_pass1_hinted(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt, HintArgs h)
 {
     const WorkItem it = items[blockIdx.x];
     const int mode = item_mode(it);

@@ -379,7 +379,8 @@ __device__ __forceinline__ void project_tile(const WorkItem& it, const ProjectAr
 }
 
 template <int R>
-__global__ __launch_bounds__(kBlock) void project_pass1(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, pass1_waves(R))))
+void project_pass1(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt)
 {
     const WorkItem it = items[blockIdx.x];
     const int mode = item_mode(it);

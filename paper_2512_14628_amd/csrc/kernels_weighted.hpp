@@ -335,10 +335,8 @@ __device__ __forceinline__ void weighted_item(const WorkItem& it, const Weighted
     }
 }
 
-// (With the residual sums four replicas get the registers of three waves per SIMD, eight those of two: ResNet-50 step with
-// norms, 4 replicas, left to the compiler 347 us, so 341 us; 8 replicas 418 us, so 410 us.)
 template <int R, bool RES = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, !RES || R < 4 ? 8 : R < 8 ? 3 : 2)))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, weighted_pass1_waves(R, RES))))
 void weighted_pass1(const WorkItem* __restrict__ items, WeightedArgs w, int Rrt)
 {
     weighted_item<R, RES>(items[blockIdx.x], w, Rrt);
