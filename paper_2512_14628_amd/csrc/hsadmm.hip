@@ -379,7 +379,6 @@ int run_scan(const hsadmm_plan* p, const uint8_t* mask, char* ws, hipStream_t s,
 
 constexpr int64_t kFineRowsMaxElems = 20ll << 20;     // (see lay_out)
 constexpr int64_t kWideStripsMinTiles = 512;          // ... two per compute unit
-static_assert(kChanRows == kBothRows, "the tiles of both kinds of layer are counted alike");
 
 // The plan's tables and the places of the scratch, from the layers.  Called again it starts over.
 int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* nest, int32_t L, bool fine,
@@ -401,12 +400,13 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
     for (int32_t l = 0; l < L; ++l) n_elems += (int64_t)layers[l].c_out * layers[l].c_in * layers[l].khw;
     const bool small = n_elems < kFineRowsMaxElems;
     // Strips of 64 columns make four times the workgroups that strips of 256 make of a ragged layer, and a tile is a serial
-    // walk over up to 16 rows: below two narrow tiles per compute unit in the whole plan, narrow strips win.  Weighted
-    // step, channel groups, 8 replicas, narrow / wide: plain networks of width 45 (81 tiles) 41.2 / 49.3 us, 101 (383) 81.7 /
-    // 82.7, 143 (685) 126.1 / 121.3.
+    // walk over up to 16 rows: below two narrow tiles per compute unit in pass 1, narrow strips win.  Weighted step, channel
+    // groups, 8 replicas, narrow / wide: plain networks of width 45 (81 tiles) 41.2 / 49.3 us, 101 (383) 81.7 / 82.7, 143
+    // (685) 126.1 / 121.3.  The column sums of BOTH layers take wide strips always: narrow ones gain them a microsecond in
+    // the smallest plans' un-predicted steps (plain, width 45: 47.9 / 49.2 us) but lose five under a prediction (48.9 / 45.3).
     int64_t narrow_tiles = 0;
     for (int32_t l = 0; l < L; ++l) {
-        if (!mode_has_channels(layers[l].mode)) continue;
+        if (layers[l].mode != HSADMM_MODE_CHANNEL) continue;
         const int row_len = layers[l].c_in * layers[l].khw;
         const int cols = kWave * (row_len % 4 == 0 ? 4 : 1);
         narrow_tiles += (int64_t)((layers[l].c_out + kChanRows - 1) / kChanRows) * ((row_len + cols - 1) / cols);
@@ -469,7 +469,7 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
             }
         }
         if (both) {
-            add_tile_items(p->items_both, l, d, kBothRows, wide_strips);
+            add_tile_items(p->items_both, l, d, kBothRows, true);
             p->both_layers.push_back(l);
         }
         p->dev_layers.push_back(d);

@@ -162,7 +162,7 @@ constexpr int lanes_of(int n)
 
 __device__ __forceinline__ int item_mode(const WorkItem& it) { return it.flags & 3; }
 // modes whose packed rows hold a subset of the columns (CHANNEL, BOTH)
-__host__ __device__ __forceinline__ bool mode_has_channels(int mode) { return (mode & HSADMM_MODE_CHANNEL) != 0; }
+__device__ __forceinline__ bool mode_has_channels(int mode) { return (mode & HSADMM_MODE_CHANNEL) != 0; }
 __device__ __forceinline__ bool item_vec(const WorkItem& it) { return (it.flags & 4) != 0; }
 
 // First column of a lane that owns vw adjacent columns of a tile.  A lane whose four columns would pass the end of the

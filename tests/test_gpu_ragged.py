@@ -142,8 +142,9 @@ def test_wide_rows_that_are_not_whole_words_in_a_plan_that_outgrows_the_static_a
 @pytest.mark.parametrize("mode", [wk.MODE_CHANNEL, wk.MODE_BOTH])
 @pytest.mark.parametrize("R", [1, 4, 5])
 def test_column_tiles_of_ragged_rows_four_columns_to_a_lane(mode, R):
-    """A plan of 512 tiles and more takes ragged rows four columns to a lane, the last lane overlapping its neighbour;
-    the plans above are smaller and take one.  A layer of 512 whole-word tiles brings this one over the line."""
+    """In a plan of 512 tiles and more the lanes of a tile of ragged CHANNEL rows own four columns each, the last one
+    overlapping its neighbour; the plans above are smaller, and theirs own one.  A layer of 512 whole-word tiles brings this
+    plan over the line.  (The column sums of BOTH layers are always taken so.)"""
     from tests.test_gpu_hinted import _Bufs, _hinted_step, record_of
     from tests.test_gpu_parity import _run
     import oracle
