@@ -127,7 +127,7 @@ struct WorkItem {
     int32_t row_len;    // c_in * khw
     int32_t lpr;        // row item: lanes sharing a row, power of two <= 64, or 256 (whole workgroup)
     int32_t flags;      // bits 0-1: mode; bit 2: row item: whole 128-bit words (row_len % 4 == 0);
-                        // tile: four columns per lane (row_len >= 4), else one
+                        // tile: four columns per lane, else one
     int32_t col0;       // tile: first column of the strip; row item: 0
     int32_t khw;
     int32_t layer;
@@ -193,8 +193,8 @@ struct ProjectArgs {
 
 // Streaming (touch-once) accesses.  ld4 / st4 take any address of a float: rows whose length is not a multiple of four
 // floats start anywhere, and a 128-bit access that is aligned to 4 bytes only costs a wave one cache line more.  Such rows
-// one float per lane instead: ResNet-18 of width 45, 3 replicas, a step in 65.4 us against 60.5 us; weighted candidate of
-// width 41, 5 replicas, 108 us against 95.5 us.
+// one float per lane instead: ResNet-18 of width 45, 3 replicas, a step in 66.3 us against 61.2 us; weighted candidate, 8
+// replicas, 125.6 us against 118.6 us.  (Gather and expansion of such rows have loops of their own, see expand_scatter.)
 __device__ __forceinline__ v4f ld4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const v4f_at4*>(p)); }
 __device__ __forceinline__ void st4(float* p, v4f v) { __builtin_nontemporal_store(v, reinterpret_cast<v4f_at4*>(p)); }
 __device__ __forceinline__ float ld1(const float* p) { return __builtin_nontemporal_load(p); }
