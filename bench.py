@@ -392,6 +392,8 @@ def main():
         "compact_gather": bytes_["compact"],
         "expand_scatter": bytes_["expand"],
     }
+    if one_call and not launches_per_step.get("select_topk"):     # one launch that selects, and packs what it keeps
+        kernel_bytes["project_pass1"] += 4 * nk
     dom = max(kernel_us_per_step, key=lambda k: kernel_us_per_step[k])
     dom_us = per_launch_us[dom]
     achieved = kernel_bytes.get(dom, 0) / (dom_us * 1e-6) / 1e9 if dom_us else 0.0

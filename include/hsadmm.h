@@ -775,8 +775,10 @@ int hsadmm_kernel_timing_read(hsadmm_plan_t* plan, double* total_ms, int64_t* la
 int hsadmm_kernel_grid(const hsadmm_plan_t* plan, int kernel_id);
 /*
  * 1 if the un-predicted projection of this plan (hsadmm_project, hsadmm_project_compact, hsadmm_step without sel_prev,
- * dual in place) forms a prediction inside its first pass, else 0 (also for a NULL plan).  It does so for plans of
- * FILTER and unconstrained layers of 20 Mi elements or more: every FILTER layer's first rows (a sixteenth, 16 to 128)
+ * dual in place) forms a prediction inside its first pass, else 0 (also for a NULL plan).  Plans of FILTER and
+ * unconstrained layers whose rows can wait for their selection on the chip (rows of at most about 10 K floats, no layer larger
+ * than about 7 M elements) need none: one launch makes the selection and writes every row once.  Of the
+ * others, those of 20 Mi elements or more estimate: every FILTER layer's first rows (a sixteenth, 16 to 128)
  * are processed ahead of the rest, the key that the layer's keep ratio of them exceed estimates the layer's selection
  * threshold (Eq. (10) keeps the k largest norms), and every later row is written in the form its own key suggests --
  * kept, or pruned with the kept-form dual held in Z -- before the selection has been made.  The selection and the
@@ -789,7 +791,7 @@ int hsadmm_kernel_grid(const hsadmm_plan_t* plan, int kernel_id);
  * plans that take turns on one workspace do not read each other's keys.  A captured graph replays its call number: a
  * replay may then use the estimate an earlier replay left, which again changes no result.  Environment, read by
  * hsadmm_plan_create: HSADMM_NO_ESTIMATE (any value)
- * switches the estimate off, HSADMM_FORCE_ESTIMATE takes it whatever the size.
+ * switches the estimate and the one launch off, HSADMM_FORCE_ESTIMATE takes the estimate whatever the size.
  */
 int hsadmm_plan_estimates(const hsadmm_plan_t* plan);
 /* Name of a kernel id ("" when out of range). */

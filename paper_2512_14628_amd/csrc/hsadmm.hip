@@ -6,6 +6,8 @@
 //   project_pass1   streams the R replicas and U once.  Computes Wbar, V = Wbar + U and the fp64
 //                   partial sums of V^2; for FILTER / NONE layers it writes the values that are
 //                   final if the group is kept: Z <- V, U <- U + (Wbar - V).   [Eq. (9), (12)]
+//   project_held    un-predicted plans of FILTER and unconstrained layers whose rows can wait on the chip: pass 1, selection,
+//                   final values and packing in one launch that touches everything once
 //   select_topk     one workgroup per layer: radix select, eight bits a pass, of the k-th largest key on
 //                   the uint64 view of the non-negative doubles (taken relative to the smallest upper
 //                   word, so the first digit already spreads the keys; the last few candidates are
@@ -61,6 +63,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <random>
 #include <type_traits>
 #include <vector>
 
@@ -72,6 +75,7 @@
 #include "kernels_frozen.hpp"
 #include "kernels_hinted.hpp"
 #include "kernels_estimate.hpp"
+#include "kernels_held.hpp"
 #include "kernels_weighted.hpp"
 #include "kernels_residuals.hpp"
 #include "kernels_compact.hpp"
@@ -121,6 +125,9 @@ struct hsadmm_plan {
     std::vector<DevLayer> dev_layers;
     std::vector<WorkItem> items_proj;   // project kernels
     std::vector<WorkItem> items_est;    // project_pass1_est: items_proj with every FILTER layer's first items ahead of the rest
+    std::vector<WorkItem> items_held;   // project_held: the row items of the FILTER layers, then those of the unconstrained ones
+    int32_t n_held = 0;                 // ... how many of them are held (FILTER)
+    long long held_patience = kHeldPatience;
     std::vector<WorkItem> items_rows;   // compact / expand kernels
     std::vector<WorkItem> items_fix;    // project_fixup, weighted_fixup: the row items of the FILTER layers
     std::vector<WorkItem> items_none;   // weighted_fixup_pack: the row items of the unconstrained layers
@@ -140,6 +147,7 @@ struct hsadmm_plan {
     DevLayer* d_layers = nullptr;
     WorkItem* d_items_proj = nullptr;
     WorkItem* d_items_est = nullptr;
+    WorkItem* d_items_held = nullptr;
     WorkItem* d_items_rows = nullptr;
     WorkItem* d_items_fix = nullptr;
     WorkItem* d_items_none = nullptr;
@@ -166,6 +174,8 @@ struct hsadmm_plan {
 };
 
 namespace {
+
+bool mode_has_channels_host(int mode) { return (mode & HSADMM_MODE_CHANNEL) != 0; }
 
 // true when two buffers of n floats share an element
 bool spans_overlap(const float* a, const float* b, int64_t n)
@@ -504,6 +514,83 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
     return HSADMM_OK;
 }
 
+// The held row items (kernels_held.hpp), if the plan's rows can wait for their selection on the chip: FILTER and
+// unconstrained layers only, rows of at most kHeldSlots chunks per lane, and every layer's items on the chip at once
+// with a quarter of the places to spare, as a layer that takes them all leaves no one to load while it waits.  Without /
+// with, us: bottleneck 3-4-23-3 of width 96 (768 items in the largest layer) 512 / 511, 719 / 686, 967 / 937 with 1, 4, 8
+// replicas; 3-4-6-3 of width 112 (896 items) 414 / 434, 587 / 598, 800 / 838.
+void lay_out_held(hsadmm_plan* p, int compute_units)
+{
+    p->items_held.clear();
+    p->n_held = 0;
+    bool any_filter = false;
+    for (const DevLayer& d : p->dev_layers) {
+        if (mode_has_channels_host(d.mode)) return;
+        any_filter = any_filter || d.mode == HSADMM_MODE_FILTER;
+    }
+    if (!any_filter) return;
+    const int64_t places = (int64_t)kHeldPerUnit * compute_units;      // workgroups on the chip at once
+    // the fewest slots with which the whole plan is on the chip at once, or, if it never is, all of them
+    for (int want = 1; want <= kHeldSlots; ++want) {
+        std::vector<WorkItem> items;
+        for (size_t l = 0; l < p->dev_layers.size(); ++l) {
+            const DevLayer& d = p->dev_layers[l];
+            if (d.mode != HSADMM_MODE_FILTER) continue;
+            const bool vec = (d.row_len % 4) == 0;
+            const int nchunk = d.row_len / 4;
+            const int lpr = d.row_len >= kWideRow ? kBlock : lanes_of(vec ? nchunk : std::max(4, nchunk));
+            const int cpr = (nchunk + lpr - 1) / lpr + (vec ? 0 : 1);
+            if (cpr > kHeldSlots) return;
+            const int at_once = kBlock / lpr;
+            const int rows = std::min((int)std::max(1, want / cpr) * at_once, kHeldRows);
+            const int64_t n = (d.c_out + rows - 1) / rows;
+            if (want == kHeldSlots && (n > places * 3 / 4 || n > kHeldLayerItems)) return;
+            const int64_t first = (int64_t)items.size();
+            for (int r0 = 0; r0 < d.c_out; r0 += rows) {
+                WorkItem it{};
+                it.base = d.elem_off + (int64_t)r0 * d.row_len;
+                it.aux = first | (n << 32);
+                it.g0 = d.group_base + r0;
+                it.nr = std::min(rows, d.c_out - r0);
+                it.row_len = d.row_len;
+                it.lpr = lpr;
+                it.flags = HSADMM_MODE_FILTER | (vec ? 4 : 0);
+                it.khw = cpr;
+                it.layer = (int)l;
+                it.row0 = r0;
+                it.k = d.k;
+                it.packed_off = d.packed_off;
+                items.push_back(it);
+            }
+        }
+        if (want < kHeldSlots && (int64_t)items.size() > places) continue;
+        // (tags and give-ups, two words an item, take the place of the residual sums' partials: four words a row item)
+        if (items.size() > 2 * p->items_rows.size()) continue;
+        p->n_held = (int32_t)items.size();
+        p->items_held = std::move(items);
+        p->items_held.insert(p->items_held.end(), p->items_none.begin(), p->items_none.end());
+        return;
+    }
+}
+
+// A number for a call of project_held that no other call has and no other content of the scratch can equal: a negative
+// NaN's bits (the scratch holds sums of squares and whole numbers otherwise) with 50 bits of a counter that starts
+// anywhere.
+unsigned long long held_number()
+{
+    static const unsigned long long start =
+        ((unsigned long long)std::random_device{}() << 32) ^ (unsigned long long)std::random_device{}();
+    static std::atomic<unsigned long long> calls{0};
+    return 0xFFF4000000000000ull | ((start + 4 * calls.fetch_add(1, std::memory_order_relaxed)) & 0x3FFFFFFFFFFFCull);
+}
+
+bool stream_is_captured(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return true; }
+    return st != hipStreamCaptureStatusNone;
+}
+
 }  // namespace
 
 extern "C" {
@@ -575,6 +662,15 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
         // it whatever the size, which is how the tests reach it with small tables)
         p->use_estimate = only_rows && any_filter && std::getenv("HSADMM_NO_ESTIMATE") == nullptr &&
                           (n_elems_total >= kEstimateMinElems || std::getenv("HSADMM_FORCE_ESTIMATE") != nullptr);
+        int compute_units = 0;
+        if (std::getenv("HSADMM_NO_ESTIMATE") == nullptr && std::getenv("HSADMM_FORCE_ESTIMATE") == nullptr &&
+            hipGetDevice(&p->device) == hipSuccess &&
+            hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess)
+            lay_out_held(p, compute_units);
+        // (environment, read here once per plan: HSADMM_HELD_PATIENCE, ticks of 10 ns, is how the tests have rows written
+        // before their selection is known)
+        if (const char* t = std::getenv("HSADMM_HELD_PATIENCE")) p->held_patience = std::max(0ll, std::min(std::atoll(t), 100 * kHeldPatience));
+        if (p->n_held > 0) p->use_estimate = false;
         if (p->use_estimate) {
             std::vector<WorkItem> rest;
             for (WorkItem it : p->items_proj) {
@@ -633,6 +729,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
     upload(p->items_fix, &p->d_items_fix);
     upload(p->items_none, &p->d_items_none);
     upload(p->items_est, &p->d_items_est);
+    upload(p->items_held, &p->d_items_held);
     upload(p->items_plain, &p->d_items_plain);
     upload(p->items_bfinal, &p->d_items_bfinal);
     upload(p->items_chan, &p->d_items_chan);
@@ -660,6 +757,7 @@ void hsadmm_plan_destroy(hsadmm_plan_t* p)
     if (p->d_items_fix) (void)hipFree(p->d_items_fix);
     if (p->d_items_none) (void)hipFree(p->d_items_none);
     if (p->d_items_est) (void)hipFree(p->d_items_est);
+    if (p->d_items_held) (void)hipFree(p->d_items_held);
     if (p->d_items_plain) (void)hipFree(p->d_items_plain);
     if (p->d_items_bfinal) (void)hipFree(p->d_items_bfinal);
     if (p->d_items_chan) (void)hipFree(p->d_items_chan);
@@ -734,6 +832,37 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
     // Without a caller's prediction, a plan of FILTER and unconstrained layers whose dual is updated in place forms
     // one inside pass 1 (kernels_estimate.hpp).
     const bool est = !hinted && sel_prev == nullptr && U_out == nullptr && p->use_estimate;
+    // ... or its rows wait for the selection on the chip, where they can (kernels_held.hpp): one launch
+    if (sel_prev == nullptr && p->n_held > 0) {
+        HeldArgs x{};
+        x.tag = reinterpret_cast<unsigned long long*>(ws + p->ws.respart);
+        x.state = x.tag + p->n_held;
+        x.gen = held_number();
+        x.patience = p->held_patience;
+        x.pred = reinterpret_cast<int32_t*>(ws + p->ws.pred);
+        x.layers = p->d_layers;
+        x.mask = mask;
+        x.im.pos = reinterpret_cast<int32_t*>(ws + p->ws.pos);
+        x.im.cnt = reinterpret_cast<int32_t*>(ws + p->ws.cnt);
+        x.im.layer_off = reinterpret_cast<int64_t*>(ws + p->ws.layer_off);
+        x.im.kept_idx = reinterpret_cast<int32_t*>(ws + p->ws.kept_idx);
+        x.im.sel = sel_out;
+        if (out) { x.co = CopyOut{out->layer_off, out->kept_idx}; x.packed = out->packed; }
+        x.n_layers = (int)p->layers.size();
+        x.pack_align = (int)p->pack_align;
+        x.n_items = (int)p->items_held.size();
+        x.n_held = (int)p->n_held;
+        if (stream_is_captured(s)) {
+            const int n = 2 * p->n_held;
+            hipLaunchKernelGGL(held_clear, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, x.tag, n);
+            if (hipGetLastError() != hipSuccess) return HSADMM_ERR_HIP;
+        }
+        e = for_replica_count<true>(R, [&](auto c) {
+            return launch(p, kPass1, project_held<decltype(c)::value>, (unsigned)p->items_held.size() + kHeldCleaners, kBlock, s,
+                          (const WorkItem*)p->d_items_held, a, (int)R, x);
+        });
+        return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
+    }
     EstArgs ex{};
     if (est) {
         ex.pred = reinterpret_cast<int32_t*>(ws + p->ws.pred);

@@ -404,16 +404,17 @@ struct HintArgs {
 
 // pass1_row with the outputs of a row written in the form its prediction makes final (see Cand::put_h); the sum of
 // squares is taken in the same order as there, so the keys carry the same bits.
-template <int R>
+// PAIRS: two chunks at a time (else one, for a kernel that has no registers to spare).
+template <int R, bool PAIRS = true>
 __device__ __forceinline__ double pass1_row_hinted(const ProjectArgs& a, int Rrt, int64_t base, int row_len,
                                                    int j, int step, bool kept, bool stash, float* pk)
 {
     double acc = 0.0;
     const int nchunk = row_len >> 2;
     int c = j;
-    for (; c + step < nchunk; c += 2 * step)
+    for (; PAIRS && c + step < nchunk; c += 2 * step)
         acc = Cand<R>::two_h(a, Rrt, base, c << 2, (c + step) << 2, kept, stash, pk, acc);
-    if (c < nchunk) acc = sq4(acc, Cand<R>::one_h(a, Rrt, base, c << 2, kept, stash, pk));
+    for (; c < nchunk; c += step) acc = sq4(acc, Cand<R>::one_h(a, Rrt, base, c << 2, kept, stash, pk));
     if (const int c = (row_len & ~3) + j; c < row_len) {
         const float v = Cand<R>::scalar_h(a, Rrt, base, c, kept, stash, pk);
         acc = fma((double)v, (double)v, acc);
@@ -426,7 +427,7 @@ __device__ __forceinline__ double pass1_row_hinted(const ProjectArgs& a, int Rrt
 // predicted pruned is written in its pruned form (see Cand::put_h).  The rows of an unconstrained layer are always
 // kept, at their own index.  A rank outside [0, k) cannot have come from a selection of this plan: such a row is
 // treated as kept and left for the repair pass to pack.
-template <int R>
+template <int R, bool PAIRS = true>
 __device__ __forceinline__ void project_rows_hinted(const WorkItem& it, const ProjectArgs& a, int Rrt,
                                                     const HintArgs& h)
 {
@@ -454,7 +455,7 @@ __device__ __forceinline__ void project_rows_hinted(const WorkItem& it, const Pr
                 bool kept;
                 float* pk;
                 prediction(rr, kept, pk);
-                acc = pass1_row_hinted<R>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, j, lpr, kept, stash, pk);
+                acc = pass1_row_hinted<R, PAIRS>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, j, lpr, kept, stash, pk);
             }
             acc = wave_xor_sum(acc, lpr);
             if (active && j == 0) a.key[it.g0 + rr] = acc;
@@ -465,7 +466,7 @@ __device__ __forceinline__ void project_rows_hinted(const WorkItem& it, const Pr
             bool kept;
             float* pk;
             prediction(rr, kept, pk);
-            double acc = pass1_row_hinted<R>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, threadIdx.x, kBlock,
+            double acc = pass1_row_hinted<R, PAIRS>(a, Rrt, it.base + (int64_t)rr * row_len, row_len, threadIdx.x, kBlock,
                                              kept, stash, pk);
             acc = wave_xor_sum(acc, kWave);
             if (lane == 0) wsum[wave] = acc;

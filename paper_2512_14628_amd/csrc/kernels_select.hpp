@@ -84,12 +84,19 @@ struct TopkShared {
     unsigned int n_list;
 };
 
-// Keys of a layer as seen by the selection: in registers (G <= 8 * 1024) or re-read from memory.
-template <bool INREG>
+// Keys of a layer as seen by the selection: in registers (G <= 8 * the workgroup's threads) or re-read from memory.
+// NT: the threads of the workgroup that selects.  AGENT: the keys were written inside this launch, by workgroups on other
+// compute units, and are read past the caches that may hold older values.
+template <int NT, bool INREG, bool AGENT>
 struct LayerKeys {
     unsigned long long kreg[kTopkRegs];
     const unsigned long long* kb;
     int G;
+    __device__ __forceinline__ unsigned long long at(int g) const
+    {
+        if (AGENT) return __hip_atomic_load(&kb[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return kb[g];
+    }
     __device__ __forceinline__ void load(const unsigned long long* p, int g_count)
     {
         kb = p;
@@ -97,23 +104,23 @@ struct LayerKeys {
         if (INREG) {
 #pragma unroll
             for (int i = 0; i < kTopkRegs; ++i) {
-                const int g = (int)threadIdx.x + i * kScanBlock;
-                kreg[i] = (g < G) ? kb[g] : 0ull;
+                const int g = (int)threadIdx.x + i * NT;
+                kreg[i] = (g < G) ? at(g) : 0ull;
             }
         }
     }
-    // calls f(g, key) for every group this thread owns (g = tid, tid + 1024, ...)
+    // calls f(g, key) for every group this thread owns (g = tid, tid + NT, ...)
     template <typename F>
     __device__ __forceinline__ void for_each(F f) const
     {
         if (INREG) {
 #pragma unroll
             for (int i = 0; i < kTopkRegs; ++i) {
-                const int g = (int)threadIdx.x + i * kScanBlock;
+                const int g = (int)threadIdx.x + i * NT;
                 if (g < G) f(g, kreg[i]);
             }
         } else {
-            for (int g = threadIdx.x; g < G; g += kScanBlock) f(g, kb[g]);
+            for (int g = threadIdx.x; g < G; g += NT) f(g, at(g));
         }
     }
 };
@@ -124,6 +131,7 @@ struct LayerKeys {
 // histogram per pass, which every wave then reads for itself (one barrier per pass).  `need` tracks how
 // many groups must still be taken from the candidates that share the prefix found so far.  Groups with
 // key > tau are kept; of the groups with key == tau the first `need` in index order are kept.
+// AGENT: the ranks are read by other workgroups of the same launch and are stored past the caches.
 // pos_l / kidx_l receive the layer's index mappings: the rank of every kept group (-1: pruned) and the
 // ascending list of the kept groups.
 __device__ __forceinline__ bool same_prefix(unsigned long long y, unsigned long long prefix, int known)
@@ -131,14 +139,16 @@ __device__ __forceinline__ bool same_prefix(unsigned long long y, unsigned long 
     return known >= 64 || (y >> known) == (prefix >> known);
 }
 
-template <bool INREG>
+template <bool INREG, int NT = kScanBlock, bool AGENT = false>
 __device__ __forceinline__ void topk_layer(int G, const unsigned long long* kb, uint8_t* ml, int kk, TopkShared& sh,
                                            int32_t* pos_l, int32_t* kidx_l, int32_t* sel_l, int32_t* ck_l)
 {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid / kWave;
-    LayerKeys<INREG> keys;
+    constexpr int kNW = NT / kWave;
+    static_assert(NT % kWave == 0 && NT >= 256 && kNW <= 16 && (kNW & (kNW - 1)) == 0, "a histogram bin per thread at least");
+    LayerKeys<NT, INREG, AGENT> keys;
     keys.load(kb, G);
 
     // range of the upper key words
@@ -156,12 +166,11 @@ __device__ __forceinline__ void topk_layer(int G, const unsigned long long* kb, 
         hi = hi > h1 ? hi : h1; hi = hi > h2 ? hi : h2; hi = hi > h3 ? hi : h3;
     }
     if (lane == 0) { sh.w_lo[wave] = lo; sh.w_hi[wave] = hi; }
-    if (tid < 768) (&sh.hist[0][0])[tid] = 0u;
-    if (tid == 768) sh.n_list = 0u;
+    for (int i = tid; i < 768; i += NT) (&sh.hist[0][0])[i] = 0u;
+    if (tid == NT - 1) sh.n_list = 0u;
     __syncthreads();
-    lo = sh.w_lo[lane & (kScanWaves - 1)];
-    hi = sh.w_hi[lane & (kScanWaves - 1)];
-    static_assert(kScanWaves == 16, "one row of lanes holds one value per wave");
+    lo = sh.w_lo[lane & (kNW - 1)];                            // (a row of 16 lanes holds every wave's value)
+    hi = sh.w_hi[lane & (kNW - 1)];
     row_min_max(lo, hi);
     const unsigned long long c = (unsigned long long)lo << 32;
     const unsigned int span = hi - lo;                        // every y is below (span + 1) << 32
@@ -243,16 +252,67 @@ __device__ __forceinline__ void topk_layer(int G, const unsigned long long* kb, 
     }
     // final pass in index order: the kept flag (ties: the first `need` groups equal to tau), then the rank
     // of every kept group among the kept ones
+    if constexpr (AGENT && INREG) {
+        // a smaller workgroup has several groups to a thread: all its waves' counts in one go
+        static_assert(kTopkRegs * kNW <= kWave, "a count per lane");
+        unsigned int* cnt = &sh.hist[0][0];
+        __syncthreads();                                         // the histograms are done with
+        auto ranks = [&](auto flag, int* rank, bool need_rank) { // rank[i]: flagged groups before this thread's i-th
+            unsigned long long b[kTopkRegs];
+#pragma unroll
+            for (int i = 0; i < kTopkRegs; ++i) {
+                b[i] = __ballot(flag(i));
+                if (lane == 0) cnt[i * kNW + wave] = (unsigned int)__popcll(b[i]);
+            }
+            __syncthreads();
+            unsigned int v = lane < kTopkRegs * kNW ? cnt[lane] : 0u, sum = v;
+            for (int o = 1; o < kTopkRegs * kNW; o <<= 1) {
+                const unsigned int x = __shfl_up(sum, o, kWave);
+                if (lane >= o) sum += x;
+            }
+            const unsigned int before = sum - v;
+#pragma unroll
+            for (int i = 0; i < kTopkRegs; ++i)
+                rank[i] = (int)lane_value(before, i * kNW + wave) + __popcll(b[i] & ((1ull << lane) - 1ull));
+            if (need_rank) __syncthreads();                      // the counts may be written again
+        };
+        int r[kTopkRegs];
+        bool kept[kTopkRegs];
+        auto in = [&](int i) { return tid + i * NT < G; };
+        if (scan_ties) {
+            ranks([&](int i) { return in(i) && keys.kreg[i] == tau; }, r, true);
+#pragma unroll
+            for (int i = 0; i < kTopkRegs; ++i)
+                kept[i] = in(i) && (keys.kreg[i] > tau || (keys.kreg[i] == tau && r[i] < need));
+        } else {
+#pragma unroll
+            for (int i = 0; i < kTopkRegs; ++i) kept[i] = in(i) && keys.kreg[i] >= tau;
+        }
+        ranks([&](int i) { return kept[i]; }, r, false);
+#pragma unroll
+        for (int i = 0; i < kTopkRegs; ++i)
+            if (in(i)) __hip_atomic_store(&pos_l[tid + i * NT], kept[i] ? r[i] : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < kTopkRegs; ++i)
+            if (in(i)) {
+                const int g = tid + i * NT;
+                ml[g] = kept[i] ? 1 : 0;
+                if (sel_l) sel_l[g] = kept[i] ? r[i] : -1;
+                if (kept[i]) kidx_l[r[i]] = g;
+                if (kept[i] && ck_l) ck_l[r[i]] = g;
+            }
+        return;
+    }
     int carry_eq = 0, carry_kept = 0;
-    for (int base = 0; base < G; base += kScanBlock) {
+    for (int base = 0; base < G; base += NT) {
         const int g = base + tid;
         unsigned long long x = 0ull;
         if (g < G) {
             if (INREG) {
 #pragma unroll
-                for (int i = 0; i < kTopkRegs; ++i) if (i * kScanBlock == base) x = keys.kreg[i];
+                for (int i = 0; i < kTopkRegs; ++i) if (i * NT == base) x = keys.kreg[i];
             } else {
-                x = kb[g];
+                x = keys.at(g);
             }
         }
         bool kept = (g < G) && (x >= tau);
@@ -260,15 +320,16 @@ __device__ __forceinline__ void topk_layer(int G, const unsigned long long* kb, 
             const bool eq = (g < G) && (x == tau);
             const bool gt = (g < G) && (x > tau);
             int total;
-            const int rank = carry_eq + block_excl_scan<kScanWaves>(eq, sh.wtot, total);
+            const int rank = carry_eq + block_excl_scan<kNW>(eq, sh.wtot, total);
             kept = gt || (eq && rank < need);
             carry_eq += total;
         }
         int total_kept;
-        const int r = carry_kept + block_excl_scan<kScanWaves>(kept, sh.wtot, total_kept);
+        const int r = carry_kept + block_excl_scan<kNW>(kept, sh.wtot, total_kept);
         if (g < G) {
             ml[g] = kept ? 1 : 0;
-            pos_l[g] = kept ? r : -1;
+            if (AGENT) __hip_atomic_store(&pos_l[g], kept ? r : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else pos_l[g] = kept ? r : -1;
             if (sel_l) sel_l[g] = kept ? r : -1;
             if (kept) kidx_l[r] = g;
             if (kept && ck_l) ck_l[r] = g;

@@ -1,0 +1,172 @@
+"""Plans of FILTER and unconstrained layers whose rows wait for their selection on the chip: the un-predicted projection
+is one launch that makes the selection itself and writes every row once.  Every output against the oracle, at the edges of
+what a workgroup holds (rows of one to ten chunks a lane, ragged rows, one row to 256 rows an item, layers of one item and
+of more groups than the selection ranks from registers), and with no patience at all, so that rows are written before
+their selection is known and the workgroups behind finish them."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2512_14628_amd as pkg
+import workloads as wk
+
+pytestmark = pytest.mark.gpu
+
+F, N = wk.MODE_FILTER, wk.MODE_NONE
+# (c_out, c_in, khw, mode, k): row lengths 1 .. 10240 floats, on either side of four floats, a wave and the whole workgroup
+EDGES = [(700, 1, 1, F, 300), (260, 2, 1, F, 7), (2600, 4, 1, F, 1300), (90, 5, 1, F, 90), (300, 7, 9, F, 100),
+         (64, 64, 1, F, 1), (129, 65, 1, F, 64), (40, 255, 1, F, 39), (37, 256, 1, F, 12), (33, 2047, 1, F, 20),
+         (18, 2048, 1, F, 5), (21, 2049, 1, F, 11), (1, 512, 9, F, 1), (19, 1024, 9, F, 9), (7, 9215, 1, F, 3),
+         (9, 10240, 1, F, 4), (30, 100, 1, N, 30), (3, 2050, 1, N, 3)]
+
+
+@pytest.fixture(params=["", "0"], ids=["patient", "impatient"])
+def patience(request, monkeypatch):
+    for name in ("HSADMM_NO_ESTIMATE", "HSADMM_FORCE_ESTIMATE"):
+        monkeypatch.delenv(name, raising=False)
+    if request.param:
+        monkeypatch.setenv("HSADMM_HELD_PATIENCE", request.param)
+
+
+def _launches(plan, call):
+    pkg.hsadmm_kernel_timing_enable(plan, True)
+    call()
+    torch.cuda.synchronize()
+    got = {k: v[1] for k, v in pkg.hsadmm_kernel_timing_read(plan).items() if v[1]}
+    pkg.hsadmm_kernel_timing_enable(plan, False)
+    return got
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 5, 8])
+def test_edges_of_what_a_workgroup_holds(R, patience):
+    from tests.gpu_harness import GpuRun
+    from tests.test_gpu_parity import _run
+    wl = wk.custom_workload(EDGES, R=R, seed=40 + R, sigma_replica=0.03)
+    _run(wl, pack_align=4 if R == 3 else 1)
+    r = GpuRun(wl, *wk.generate(wl))
+    assert _launches(r.plan, r.project_compact) == {"project_pass1": 1}
+    r.close()
+
+
+@pytest.mark.parametrize("n_layers", [1, 40])
+def test_small_and_full_items(n_layers, patience):
+    """Layers alone (items of one chunk a lane) and enough of them to fill every place with ten."""
+    from tests.test_gpu_parity import _run
+    _run(wk.custom_workload([(128, 64, 9, F, 50), (96, 512, 1, F, 40)] * n_layers + [(64, 96, 1, N, 64)], R=2, seed=3,
+                            sigma_replica=0.03), determinism=False)
+
+
+def test_steps_on_one_workspace_with_every_option_and_replayed(patience):
+    """Outer iterations with the selection record, the dual in place and in a second buffer, on one scratch that starts as
+    garbage, then replayed from a captured graph (where a call's number is always the same)."""
+    wl = wk.custom_workload([(384, 128, 9, F, 150), (512, 256, 1, F, 200), (100, 512, 1, N, 100), (300, 147, 1, F, 100)],
+                            R=3, seed=8, sigma_replica=0.03)
+    W, U = wk.generate(wl)
+    t = wl.table()
+    dev = torch.device("cuda:0")
+    plan = pkg.Plan(t)
+    dW = [torch.from_numpy(np.ascontiguousarray(W[r])).to(dev) for r in range(wl.R)]
+    refs, u = [], U.copy()
+    for _ in range(6):
+        refs.append(oracle.project(t, W, u))
+        u = refs[-1]["U"]
+
+    def buffers():
+        n = wl.n_arena
+        return {"U": torch.from_numpy(U.copy()).to(dev), "U2": torch.zeros(n, device=dev), "Z": torch.zeros(n, device=dev),
+                "mask": torch.zeros(plan.groups_total, dtype=torch.uint8, device=dev),
+                "sel": torch.zeros(plan.groups_total, dtype=torch.int32, device=dev),
+                "ws": torch.full((plan.workspace_bytes,), 0xF4, dtype=torch.uint8, device=dev),
+                "packed": torch.zeros(plan.packed_capacity_elems, device=dev),
+                "off": torch.zeros(plan.n_layers + 1, dtype=torch.int64, device=dev),
+                "kept": torch.zeros(plan.groups_total, dtype=torch.int32, device=dev)}
+
+    def step(b, out_of_place, stream=None):
+        pkg.hsadmm_step(plan, dW, U=b["U"], U_out=b["U2"] if out_of_place else None, Z=b["Z"], mask=b["mask"], sel=b["sel"],
+                        packed=b["packed"], layer_off=b["off"], kept_idx=b["kept"], workspace=b["ws"], stream=stream)
+
+    def check(b, it, dual):
+        torch.cuda.synchronize()
+        ref = refs[it]
+        assert np.array_equal(b["mask"].cpu().numpy(), ref["mask"]), it
+        for name, want in (("Z", ref["Z"]), (dual, ref["U"])):
+            g = b[name].cpu().numpy()
+            for l in wl.layers:
+                sl = slice(l.elem_off, l.elem_off + l.n)
+                assert np.array_equal(g[sl].view(np.uint32), want[sl].view(np.uint32)), (it, name, l.name)
+        refc = oracle.compact(t, ref["Z"], ref["mask"])
+        assert np.array_equal(b["off"].cpu().numpy(), refc["layer_off"])
+        assert np.array_equal(b["kept"].cpu().numpy()[:refc["kept_idx"].size], refc["kept_idx"])
+        assert np.array_equal(b["packed"].cpu().numpy()[:refc["packed"].size].view(np.uint32), refc["packed"].view(np.uint32))
+        ranks = np.concatenate([np.where(m, np.cumsum(m) - 1, -1) for m in
+                                (ref["mask"][l.group_base:l.group_base + l.groups].astype(np.int64) for l in wl.layers)])
+        assert np.array_equal(b["sel"].cpu().numpy(), ranks), it
+
+    b = buffers()
+    for it in range(6):
+        step(b, it % 2 == 1)
+        check(b, it, "U2" if it % 2 else "U")
+        if it % 2:
+            b["U"].copy_(b["U2"])
+
+    g = buffers()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step(g, False, stream=side)
+    torch.cuda.synchronize()
+    scratch = torch.zeros(1 << 16, device=dev)
+    for it in range(6):
+        graph.replay()
+        check(g, it, "U")
+        scratch.add_(1.0)
+    plan.close()
+
+
+def test_equal_rows_go_to_the_lower_index(patience):
+    from tests.gpu_harness import GpuRun, check_against_oracle
+    wl = wk.custom_workload([(300, 128, 1, F, 150), (2500, 16, 1, F, 1100)], R=4, seed=3, sigma_replica=0.03)
+    W, U = (np.array(x) for x in wk.generate(wl))
+    for l, n in ((wl.layers[0], 128), (wl.layers[1], 16)):
+        for r in range(1, l.c_out):
+            at = l.elem_off + n * r
+            W[:, at:at + n] = W[:, l.elem_off:l.elem_off + n]
+            U[at:at + n] = U[l.elem_off:l.elem_off + n]
+    t = wl.table()
+    ref = oracle.project(t, W, U, want_wbar=True)
+    r = GpuRun(wl, W, U)
+    r.step(fused=True)
+    rep = check_against_oracle(wl, r.outputs(), ref, oracle.compact(t, ref["Z"], ref["mask"]))
+    assert all(v == 0 for v in rep.values()), rep
+    r.close()
+
+
+def test_two_streams_at_once(patience):
+    """Two calls at the same time, each wanting every place on the chip."""
+    wl = wk.custom_workload([(512, 512, 9, F, 200)] * 4 + [(2048, 512, 1, F, 900)] * 3, R=2, seed=5, sigma_replica=0.03)
+    W, U = wk.generate(wl)
+    ref = oracle.project(wl.table(), W, U)
+    dev = torch.device("cuda:0")
+    plan = pkg.Plan(wl.table())
+    dW = [torch.from_numpy(np.ascontiguousarray(W[r])).to(dev) for r in range(wl.R)]
+    dU = torch.from_numpy(U.copy()).to(dev)
+    sets = []
+    for _ in range(2):
+        sets.append((torch.cuda.Stream(), torch.zeros_like(dU), torch.zeros_like(dU),
+                     torch.zeros(plan.groups_total, dtype=torch.uint8, device=dev),
+                     torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device=dev)))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for st, U2, Z, mask, ws in sets:
+            pkg.hsadmm_step(plan, dW, U=dU, U_out=U2, Z=Z, mask=mask, workspace=ws, stream=st)
+    torch.cuda.synchronize()
+    for _, U2, Z, mask, _ in sets:
+        assert np.array_equal(mask.cpu().numpy(), ref["mask"])
+        for got, want in ((Z, ref["Z"]), (U2, ref["U"])):
+            g = got.cpu().numpy()
+            for l in wl.layers:
+                sl = slice(l.elem_off, l.elem_off + l.n)
+                assert np.array_equal(g[sl].view(np.uint32), want[sl].view(np.uint32)), l.name
+    plan.close()
