@@ -7,7 +7,8 @@
 //                   partial sums of V^2; for FILTER / NONE layers it writes the values that are
 //                   final if the group is kept: Z <- V, U <- U + (Wbar - V).   [Eq. (9), (12)]
 //   project_held    un-predicted plans of FILTER and unconstrained layers whose rows can wait on the chip: pass 1, selection,
-//                   final values and packing in one launch that touches everything once
+//                   final values and packing in one launch that touches everything once; weighted_held: the same with
+//                   the full candidate of Eq. (9), without the residual norms
 //   select_topk     one workgroup per layer: radix select, eight bits a pass, of the k-th largest key on
 //                   the uint64 view of the non-negative doubles (taken relative to the smallest upper
 //                   word, so the first digit already spreads the keys; the last few candidates are
@@ -75,8 +76,8 @@
 #include "kernels_frozen.hpp"
 #include "kernels_hinted.hpp"
 #include "kernels_estimate.hpp"
-#include "kernels_held.hpp"
 #include "kernels_weighted.hpp"
+#include "kernels_held.hpp"
 #include "kernels_residuals.hpp"
 #include "kernels_compact.hpp"
 
@@ -125,8 +126,10 @@ struct hsadmm_plan {
     std::vector<DevLayer> dev_layers;
     std::vector<WorkItem> items_proj;   // project kernels
     std::vector<WorkItem> items_est;    // project_pass1_est: items_proj with every FILTER layer's first items ahead of the rest
-    std::vector<WorkItem> items_held;   // project_held: the row items of the FILTER layers, then those of the unconstrained ones
-    int32_t n_held = 0;                 // ... how many of them are held (FILTER)
+    // project_held / weighted_held: the row items of the FILTER layers, then those of the unconstrained ones, and how many of
+    // them are held (FILTER; none: the plan does not take that path)
+    std::vector<WorkItem> items_held, items_wheld;
+    int32_t n_held = 0, n_wheld = 0;
     long long held_patience = kHeldPatience;
     std::vector<WorkItem> items_rows;   // compact / expand kernels
     std::vector<WorkItem> items_fix;    // project_fixup, weighted_fixup: the row items of the FILTER layers
@@ -148,6 +151,7 @@ struct hsadmm_plan {
     WorkItem* d_items_proj = nullptr;
     WorkItem* d_items_est = nullptr;
     WorkItem* d_items_held = nullptr;
+    WorkItem* d_items_wheld = nullptr;
     WorkItem* d_items_rows = nullptr;
     WorkItem* d_items_fix = nullptr;
     WorkItem* d_items_none = nullptr;
@@ -519,17 +523,17 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
 // with a quarter of the places to spare, as a layer that takes them all leaves no one to load while it waits.  Without /
 // with, us: bottleneck 3-4-23-3 of width 96 (768 items in the largest layer) 512 / 511, 719 / 686, 967 / 937 with 1, 4, 8
 // replicas; 3-4-6-3 of width 112 (896 items) 414 / 434, 587 / 598, 800 / 838.
-void lay_out_held(hsadmm_plan* p, int compute_units)
+// places: workgroups on the chip at once.
+void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& out, int32_t& n_held)
 {
-    p->items_held.clear();
-    p->n_held = 0;
+    out.clear();
+    n_held = 0;
     bool any_filter = false;
     for (const DevLayer& d : p->dev_layers) {
         if (mode_has_channels_host(d.mode)) return;
         any_filter = any_filter || d.mode == HSADMM_MODE_FILTER;
     }
     if (!any_filter) return;
-    const int64_t places = (int64_t)kHeldPerUnit * compute_units;      // workgroups on the chip at once
     // the fewest slots with which the whole plan is on the chip at once, or, if it never is, all of them
     for (int want = 1; want <= kHeldSlots; ++want) {
         std::vector<WorkItem> items;
@@ -544,7 +548,7 @@ void lay_out_held(hsadmm_plan* p, int compute_units)
             const int at_once = kBlock / lpr;
             const int rows = std::min((int)std::max(1, want / cpr) * at_once, kHeldRows);
             const int64_t n = (d.c_out + rows - 1) / rows;
-            if (want == kHeldSlots && (n > places * 3 / 4 || n > kHeldLayerItems)) return;
+            if (want == kHeldSlots && (n > places * 3 / 4)) return;
             const int64_t first = (int64_t)items.size();
             for (int r0 = 0; r0 < d.c_out; r0 += rows) {
                 WorkItem it{};
@@ -566,9 +570,9 @@ void lay_out_held(hsadmm_plan* p, int compute_units)
         if (want < kHeldSlots && (int64_t)items.size() > places) continue;
         // (tags and give-ups, two words an item, take the place of the residual sums' partials: four words a row item)
         if (items.size() > 2 * p->items_rows.size()) continue;
-        p->n_held = (int32_t)items.size();
-        p->items_held = std::move(items);
-        p->items_held.insert(p->items_held.end(), p->items_none.begin(), p->items_none.end());
+        n_held = (int32_t)items.size();
+        out = std::move(items);
+        out.insert(out.end(), p->items_none.begin(), p->items_none.end());
         return;
     }
 }
@@ -666,7 +670,10 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
         if (std::getenv("HSADMM_NO_ESTIMATE") == nullptr && std::getenv("HSADMM_FORCE_ESTIMATE") == nullptr &&
             hipGetDevice(&p->device) == hipSuccess &&
             hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess)
-            lay_out_held(p, compute_units);
+        {
+            lay_out_held(p, (int64_t)kHeldPerUnit * compute_units, p->items_held, p->n_held);
+            lay_out_held(p, (int64_t)kHeldWeightedPerUnit * compute_units, p->items_wheld, p->n_wheld);
+        }
         // (environment, read here once per plan: HSADMM_HELD_PATIENCE, ticks of 10 ns, is how the tests have rows written
         // before their selection is known)
         if (const char* t = std::getenv("HSADMM_HELD_PATIENCE")) p->held_patience = std::max(0ll, std::min(std::atoll(t), 100 * kHeldPatience));
@@ -730,6 +737,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
     upload(p->items_none, &p->d_items_none);
     upload(p->items_est, &p->d_items_est);
     upload(p->items_held, &p->d_items_held);
+    upload(p->items_wheld, &p->d_items_wheld);
     upload(p->items_plain, &p->d_items_plain);
     upload(p->items_bfinal, &p->d_items_bfinal);
     upload(p->items_chan, &p->d_items_chan);
@@ -758,6 +766,7 @@ void hsadmm_plan_destroy(hsadmm_plan_t* p)
     if (p->d_items_none) (void)hipFree(p->d_items_none);
     if (p->d_items_est) (void)hipFree(p->d_items_est);
     if (p->d_items_held) (void)hipFree(p->d_items_held);
+    if (p->d_items_wheld) (void)hipFree(p->d_items_wheld);
     if (p->d_items_plain) (void)hipFree(p->d_items_plain);
     if (p->d_items_bfinal) (void)hipFree(p->d_items_bfinal);
     if (p->d_items_chan) (void)hipFree(p->d_items_chan);
@@ -786,6 +795,35 @@ struct CompactOut {
     int64_t* layer_off;
     int32_t* kept_idx;
 };
+
+// What a launch over the held items needs; inside a capture its tags are cleared first.
+static hipError_t held_args(const hsadmm_plan_t* p, size_t n_items, int32_t n_held, uint8_t* mask, const CompactOut& out, char* ws, hipStream_t s,
+                            int32_t* sel_out, HeldArgs& x)
+{
+    x = HeldArgs{};
+    x.n_items = (int)n_items;
+    x.n_held = n_held;
+    x.tag = reinterpret_cast<unsigned long long*>(ws + p->ws.respart);
+    x.state = x.tag + x.n_items;
+    x.gen = held_number();
+    x.patience = p->held_patience;
+    x.pred = reinterpret_cast<int32_t*>(ws + p->ws.pred);
+    x.layers = p->d_layers;
+    x.mask = mask;
+    x.im.pos = reinterpret_cast<int32_t*>(ws + p->ws.pos);
+    x.im.cnt = reinterpret_cast<int32_t*>(ws + p->ws.cnt);
+    x.im.layer_off = reinterpret_cast<int64_t*>(ws + p->ws.layer_off);
+    x.im.kept_idx = reinterpret_cast<int32_t*>(ws + p->ws.kept_idx);
+    x.im.sel = sel_out;
+    x.co = CopyOut{out.layer_off, out.kept_idx};
+    x.packed = out.packed;
+    x.n_layers = (int)p->layers.size();
+    x.pack_align = (int)p->pack_align;
+    if (!stream_is_captured(s)) return hipSuccess;
+    const int n = x.n_items + x.n_held;
+    hipLaunchKernelGGL(held_clear, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, x.tag, n);
+    return hipGetLastError();
+}
 
 // sel_prev: the previous selection's record, which predicts this one (null: no prediction); sel_out: receives this
 // selection's record (may be null).
@@ -834,29 +872,9 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
     const bool est = !hinted && sel_prev == nullptr && U_out == nullptr && p->use_estimate;
     // ... or its rows wait for the selection on the chip, where they can (kernels_held.hpp): one launch
     if (sel_prev == nullptr && p->n_held > 0) {
-        HeldArgs x{};
-        x.tag = reinterpret_cast<unsigned long long*>(ws + p->ws.respart);
-        x.state = x.tag + p->n_held;
-        x.gen = held_number();
-        x.patience = p->held_patience;
-        x.pred = reinterpret_cast<int32_t*>(ws + p->ws.pred);
-        x.layers = p->d_layers;
-        x.mask = mask;
-        x.im.pos = reinterpret_cast<int32_t*>(ws + p->ws.pos);
-        x.im.cnt = reinterpret_cast<int32_t*>(ws + p->ws.cnt);
-        x.im.layer_off = reinterpret_cast<int64_t*>(ws + p->ws.layer_off);
-        x.im.kept_idx = reinterpret_cast<int32_t*>(ws + p->ws.kept_idx);
-        x.im.sel = sel_out;
-        if (out) { x.co = CopyOut{out->layer_off, out->kept_idx}; x.packed = out->packed; }
-        x.n_layers = (int)p->layers.size();
-        x.pack_align = (int)p->pack_align;
-        x.n_items = (int)p->items_held.size();
-        x.n_held = (int)p->n_held;
-        if (stream_is_captured(s)) {
-            const int n = 2 * p->n_held;
-            hipLaunchKernelGGL(held_clear, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, x.tag, n);
-            if (hipGetLastError() != hipSuccess) return HSADMM_ERR_HIP;
-        }
+        HeldArgs x;
+        if (held_args(p, p->items_held.size(), p->n_held, mask, out ? *out : CompactOut{}, ws, s, sel_out, x) != hipSuccess)
+            return HSADMM_ERR_HIP;
         e = for_replica_count<true>(R, [&](auto c) {
             return launch(p, kPass1, project_held<decltype(c)::value>, (unsigned)p->items_held.size() + kHeldCleaners, kBlock, s,
                           (const WorkItem*)p->d_items_held, a, (int)R, x);
@@ -1317,6 +1335,18 @@ static int project_weighted_impl(const hsadmm_plan_t* p, const float* const* W_r
     const unsigned grid = (unsigned)p->items_proj.size();
     const WorkItem* items = p->d_items_proj;
     hipError_t e;
+    // rows that can wait for the selection on the chip: one launch (kernels_held.hpp)
+    if (sel_prev == nullptr && !residuals && p->n_wheld > 0) {
+        HeldArgs x;
+        if (held_args(p, p->items_wheld.size(), p->n_wheld, mask, out ? *out : CompactOut{}, ws, s, sel_out, x) != hipSuccess)
+            return HSADMM_ERR_HIP;
+        const HeldWeighted hw{Zg, Vd, coef};
+        e = for_replica_count<false>(R, [&](auto c) {
+            return launch(p, kWKeys, weighted_held<decltype(c)::value>, (unsigned)p->items_wheld.size() + kHeldCleaners, kBlock, s,
+                          (const WorkItem*)p->d_items_wheld, w, (int)R, x, hw);
+        });
+        return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
+    }
     // (a prediction comes with the dual out of place here, so every mode can take it)
     const bool hinted_tiles = sel_prev != nullptr && (!p->items_chan.empty() || !p->items_bfinal.empty());
     const bool hinted = sel_prev != nullptr && (!p->items_plain.empty() || hinted_tiles);

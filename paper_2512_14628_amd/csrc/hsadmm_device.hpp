@@ -203,6 +203,15 @@ __device__ __forceinline__ void st1(float* p, float v) { __builtin_nontemporal_s
 __device__ __forceinline__ v4f ld4u(const float* p) { v4f v; __builtin_memcpy(&v, p, 16); return v; }
 __device__ __forceinline__ void st4u(float* p, v4f v) { __builtin_memcpy(p, &v, 16); }
 
+// Accesses that every compute unit sees the effect of, past the caches of the one that makes them.
+template <typename T>
+__device__ __forceinline__ void put_agent(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ T get_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// The wave's earlier stores have arrived where every compute unit sees them (those made by put_agent).
+__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // j / khw for 0 <= j < 2^22 without an integer division: a float estimate corrected by one step.
 struct DivKhw {
     int khw;

@@ -9,6 +9,7 @@
 #include "kernels_project.hpp"
 #include "kernels_select.hpp"
 #include "kernels_hinted.hpp"
+#include "kernels_weighted.hpp"
 
 namespace {
 
@@ -28,7 +29,6 @@ constexpr int kHeldPerUnit = 4;          // workgroups on a compute unit at once
 // us with two, 53 with four); eight replicas one, as two spill (ResNet-152: 396 / 418 us).
 constexpr int held_batch(int R) { return R <= 2 ? 4 : R == 8 ? 1 : 2; }
 constexpr int kHeldRows = kBlock;        // rows of an item, at most
-constexpr int kHeldLayerItems = 4 * kBlock;      // items of a layer, at most (four tags a thread to look at)
 constexpr int kNotSelected = INT32_MIN;  // a group's rank before its layer's selection
 // How long a workgroup waits for its layer's selection, in ticks of the 100 MHz clock: 300 us, six times what was seen.  The
 // wait ends by itself once every workgroup of the layer has found a place on the chip; other streams' work may hold the
@@ -56,16 +56,10 @@ struct HeldArgs {
     int n_items, n_held;            // items of the launch, and how many of them are held (the first ones)
 };
 
-template <typename T>
-__device__ __forceinline__ void put_agent(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <typename T>
-__device__ __forceinline__ T get_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// The wave's earlier stores have arrived where every compute unit sees them (those made by put_agent).
-__device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
+// LDS: slots whose dual waits here.
+template <int LDS>
 struct HeldShared {
-    v4f dual[kHeldLdsSlots][kBlock];
+    v4f dual[LDS][kBlock];
     TopkShared topk;
     double wsum[kHeldSlots][kWaves];
     int rank[kHeldRows];
@@ -85,16 +79,12 @@ __device__ __forceinline__ bool held_publish(const WorkItem& it, const HeldArgs&
     __syncthreads();
     const int first = (int)(it.aux & 0xffffffffll), n = (int)(it.aux >> 32);
     bool ok = true;
-#pragma unroll
-    for (int i = 0; i < kHeldLayerItems; i += kBlock) {
-        const int k = i + (int)threadIdx.x;
-        if (k < n) ok = ok && get_agent(&h.tag[first + k]) == h.gen;
-    }
+    for (int k = threadIdx.x; k < n; k += kBlock) ok = ok && get_agent(&h.tag[first + k]) == h.gen;
     return __syncthreads_and(ok) != 0;
 }
 
 // The selection of the item's layer by this workgroup, with everything a later kernel or the caller reads of it.
-__device__ __forceinline__ void held_select(const WorkItem& it, const HeldArgs& h, const double* key, HeldShared& sh)
+__device__ __forceinline__ void held_select(const WorkItem& it, const HeldArgs& h, const double* key, TopkShared& topk)
 {
     const DevLayer& L = h.layers[it.layer];
     const int G = L.G, first = L.group_base, kk = L.k;
@@ -112,9 +102,9 @@ __device__ __forceinline__ void held_select(const WorkItem& it, const HeldArgs& 
             if (ck_l) ck_l[g] = g;
         }
     } else if (G <= kTopkRegs * kBlock) {
-        topk_layer<true, kBlock, true>(G, kb, ml, kk, sh.topk, pos_l, kidx_l, sel_l, ck_l);
+        topk_layer<true, kBlock, true>(G, kb, ml, kk, topk, pos_l, kidx_l, sel_l, ck_l);
     } else {
-        topk_layer<false, kBlock, true>(G, kb, ml, kk, sh.topk, pos_l, kidx_l, sel_l, ck_l);
+        topk_layer<false, kBlock, true>(G, kb, ml, kk, topk, pos_l, kidx_l, sel_l, ck_l);
     }
 }
 
@@ -136,8 +126,8 @@ __device__ __forceinline__ void held_layer_entries(const WorkItem& it, const Hel
     }
 }
 
-// Waits for the ranks of the item's rows -> sh.rank (-1: pruned); false if the patience ran out first.
-__device__ __forceinline__ bool held_wait(const WorkItem& it, const HeldArgs& h, HeldShared& sh)
+// Waits for the ranks of the item's rows -> rank (-1: pruned); false if the patience ran out first.
+__device__ __forceinline__ bool held_wait(const WorkItem& it, const HeldArgs& h, int* rank)
 {
     const int t = threadIdx.x;
     int r = -1;
@@ -148,40 +138,38 @@ __device__ __forceinline__ bool held_wait(const WorkItem& it, const HeldArgs& h,
             if (r != kNotSelected || (long long)__builtin_amdgcn_s_memrealtime() > until) break;
             __builtin_amdgcn_s_sleep(8);
         }
-        sh.rank[t] = r;
+        rank[t] = r;
     }
     return __syncthreads_or(t < it.nr && r == kNotSelected) == 0;
 }
 
-// One FILTER row item.
-template <int R>
-__device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
-                                          HeldShared& sh)
-{
-    const int RR = R > 0 ? R : Rrt;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int row_len = it.row_len;
-    const int nchunk = row_len >> 2;
-    const bool wide = it.lpr > kWave;
-    const int lpr = wide ? kBlock : it.lpr;
-    const int rows_at_once = kBlock / lpr;
-    const int sub = threadIdx.x / lpr;
-    const int j = threadIdx.x - sub * lpr;
-    const int cpr = it.khw;                                      // slots per row, the last one for the tail of a ragged row
-    const int tail_slot = (row_len & 3) ? cpr - 1 : cpr;
-    const int nslot = cpr * ((it.nr + rows_at_once - 1) / rows_at_once);
-
-    if (threadIdx.x < it.nr) put_agent(&h.im.pos[it.g0 + threadIdx.x], (int32_t)kNotSelected);
-
-    // The loads of a slot's place: 128 bits of a row's words, or, in the slot behind them, one of a ragged row's last floats
-    // (a choice the whole workgroup makes, so that no load waits for another's register).
-    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
-    auto fetch = [&](const float* p, int q, int rd) -> v4f {
-        v4f x = zero4;
-        const int row = rd * rows_at_once + sub;
-        if (row < it.nr) {
-            const float* r = p + it.base + (int64_t)row * row_len;
+// Where the slots of a thread lie in a row item.  The choice between a row's words and a ragged row's last floats (in the
+// slot behind them, one to a lane) is one that the whole workgroup makes, so that no load waits for another's register.
+struct HeldPlaces {
+    int64_t base;
+    int nr, row_len, nchunk, lpr, rows_at_once, sub, j, cpr, tail_slot, nslot;
+    bool wide;
+    __device__ __forceinline__ explicit HeldPlaces(const WorkItem& it)
+    {
+        base = it.base;
+        nr = it.nr;
+        row_len = it.row_len;
+        nchunk = row_len >> 2;
+        wide = it.lpr > kWave;
+        lpr = wide ? kBlock : it.lpr;
+        rows_at_once = kBlock / lpr;
+        sub = threadIdx.x / lpr;
+        j = threadIdx.x - sub * lpr;
+        cpr = it.khw;                                            // slots per row
+        tail_slot = (row_len & 3) ? cpr - 1 : cpr;
+        nslot = cpr * ((nr + rows_at_once - 1) / rows_at_once);
+    }
+    __device__ __forceinline__ int row(int rd) const { return rd * rows_at_once + sub; }
+    __device__ __forceinline__ v4f fetch(const float* p, int q, int rd) const
+    {
+        v4f x = {0.f, 0.f, 0.f, 0.f};
+        if (row(rd) < nr) {
+            const float* r = p + base + (int64_t)row(rd) * row_len;
             if (q != tail_slot) {
                 const int c = j + q * lpr;
                 if (c < nchunk) x = ld4(r + 4 * c);
@@ -190,7 +178,39 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
             }
         }
         return x;
-    };
+    }
+    __device__ __forceinline__ void put(float* p, int q, int rd, const v4f& x) const
+    {
+        if (row(rd) >= nr) return;
+        float* r = p + base + (int64_t)row(rd) * row_len;
+        if (q != tail_slot) {
+            const int c = j + q * lpr;
+            if (c < nchunk) st4(r + 4 * c, x);
+        } else if (j < (row_len & 3)) {
+            st1(r + 4 * nchunk + j, x.x);
+        }
+    }
+    // the same into a packed row, which may begin at any float
+    __device__ __forceinline__ void put_packed(float* r, int q, const v4f& x) const
+    {
+        if (q != tail_slot) {
+            const int c = j + q * lpr;
+            if (c < nchunk) st4u(r + 4 * c, x);
+        } else if (j < (row_len & 3)) {
+            r[4 * nchunk + j] = x.x;
+        }
+    }
+};
+
+// One FILTER row item.
+template <int R, typename SHARED>
+__device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h, SHARED& sh)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const HeldPlaces at(it);
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    if (threadIdx.x < it.nr) put_agent(&h.im.pos[it.g0 + threadIdx.x], (int32_t)kNotSelected);
     v4f V[kHeldSlots];                                           // the candidate
     v4f D[kHeldSlots > kHeldLdsSlots ? kHeldSlots - kHeldLdsSlots : 1];   // the dual of a kept group (the first slots': in LDS)
     {
@@ -199,25 +219,25 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
         double acc = 0.0;
 #pragma unroll
         for (int s0 = 0; s0 < kHeldSlots; s0 += B)
-            if (s0 < nslot) {
+            if (s0 < at.nslot) {
                 v4f w[B], u[B];
                 int qb[B], rb[B];
 #pragma unroll
                 for (int i = 0; i < B; ++i) {
-                    qb[i] = q; rb[i] = s0 + i < nslot ? rd : it.nr;      // (no such row)
-                    if (++q == cpr) { q = 0; ++rd; }
+                    qb[i] = q; rb[i] = s0 + i < at.nslot ? rd : it.nr;   // (no such row)
+                    if (++q == at.cpr) { q = 0; ++rd; }
                 }
 #pragma unroll
                 for (int i = 0; i < B; ++i) {
-                    w[i] = fetch(a.W[0], qb[i], rb[i]);
-                    u[i] = fetch(a.Ur, qb[i], rb[i]);
+                    w[i] = at.fetch(a.W[0], qb[i], rb[i]);
+                    u[i] = at.fetch(a.Ur, qb[i], rb[i]);
                 }
                 if (R > 1) {
                     v4f x[B][R > 1 ? R - 1 : 1];
 #pragma unroll
                     for (int i = 0; i < B; ++i)
 #pragma unroll
-                        for (int r = 1; r < R; ++r) x[i][r - 1] = fetch(a.W[r], qb[i], rb[i]);
+                        for (int r = 1; r < R; ++r) x[i][r - 1] = at.fetch(a.W[r], qb[i], rb[i]);
 #pragma unroll
                     for (int i = 0; i < B; ++i)
 #pragma unroll
@@ -226,7 +246,7 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
                     for (int r = 1; r < Rrt; ++r) {
                         v4f x[B];
 #pragma unroll
-                        for (int i = 0; i < B; ++i) x[i] = fetch(a.W[r], qb[i], rb[i]);
+                        for (int i = 0; i < B; ++i) x[i] = at.fetch(a.W[r], qb[i], rb[i]);
 #pragma unroll
                         for (int i = 0; i < B; ++i) w[i] = w[i] + x[i];
                     }
@@ -241,20 +261,13 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
                     V[s] = v;
                     if (s < kHeldLdsSlots) sh.dual[s][threadIdx.x] = d;
                     else D[s - kHeldLdsSlots] = d;
-                    const int row = rb[i] * rows_at_once + sub;
-                    if (a.Wbar && row < it.nr) {
-                        float* r = a.Wbar + it.base + (int64_t)row * row_len;
-                        if (qb[i] != tail_slot) {
-                            if (const int c = j + qb[i] * lpr; c < nchunk) st4(r + 4 * c, wb);
-                        } else if (j < (row_len & 3)) {
-                            st1(r + 4 * nchunk + j, wb.x);
-                        }
-                    }
+                    if (a.Wbar) at.put(a.Wbar, qb[i], rb[i], wb);
                     acc = sq4(acc, v);                           // (lanes without an element add zeros)
-                    if (s < nslot && qb[i] == cpr - 1) {         // the row is complete
-                        if (!wide) {
-                            acc = wave_xor_sum(acc, lpr);
-                            if (j == 0 && row < it.nr) put_agent(&a.key[it.g0 + row], acc);
+                    if (s < at.nslot && qb[i] == at.cpr - 1) {   // the row is complete
+                        if (!at.wide) {
+                            acc = wave_xor_sum(acc, at.lpr);
+                            const int row = at.row(rb[i]);
+                            if (at.j == 0 && row < it.nr) put_agent(&a.key[it.g0 + row], acc);
                         } else {
                             acc = wave_xor_sum(acc, kWave);
                             if (lane == 0) sh.wsum[rb[i]][wave] = acc;
@@ -264,7 +277,7 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
                 }
             }
     }
-    if (wide) {
+    if (at.wide) {
         __syncthreads();
         if (threadIdx.x < it.nr) {
             double s = sh.wsum[threadIdx.x][0];
@@ -272,8 +285,8 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
             put_agent(&a.key[it.g0 + threadIdx.x], s);
         }
     }
-    if (held_publish(it, h)) held_select(it, h, a.key, sh);
-    const bool known = held_wait(it, h, sh);
+    if (held_publish(it, h)) held_select(it, h, a.key, sh.topk);
+    const bool known = held_wait(it, h, sh.rank);
     if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
     const DevLayer& L = h.layers[it.layer];
     const bool kept_default = 2 * L.k >= L.G;                    // written too early: in the likelier form
@@ -284,31 +297,18 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
     int q = 0, rd = 0;
 #pragma unroll
     for (int s = 0; s < kHeldSlots; ++s) {
-        if (s < nslot) {
-            const int row = rd * rows_at_once + sub;
+        if (s < at.nslot) {
+            const int row = at.row(rd);
             if (row < it.nr) {
                 const int rank = known ? sh.rank[row] : (kept_default ? 0 : -1);
                 const bool kept = rank >= 0;
                 const v4f d = s < kHeldLdsSlots ? sh.dual[s][threadIdx.x] : D[s < kHeldLdsSlots ? 0 : s - kHeldLdsSlots];
                 const v4f z = kept ? V[s] : (known ? zero4 : d);
-                const v4f u = kept ? d : V[s];
-                const int64_t base = it.base + (int64_t)row * row_len;
-                float* pk = (pk_layer && kept) ? pk_layer + (int64_t)rank * row_len : nullptr;
-                if (q != tail_slot) {
-                    const int c = j + q * lpr;
-                    if (c < nchunk) {
-                        st4(a.Z + base + 4 * c, z);
-                        st4(a.U + base + 4 * c, u);
-                        if (pk) st4u(pk + 4 * c, z);
-                    }
-                } else if (j < (row_len & 3)) {
-                    const int c = 4 * nchunk + j;
-                    st1(a.Z + base + c, z.x);
-                    st1(a.U + base + c, u.x);
-                    if (pk) pk[c] = z.x;
-                }
+                at.put(a.Z, q, rd, z);
+                at.put(a.U, q, rd, kept ? d : V[s]);
+                if (pk_layer && kept) at.put_packed(pk_layer + (int64_t)rank * it.row_len, q, z);
             }
-            if (++q == cpr) { q = 0; ++rd; }
+            if (++q == at.cpr) { q = 0; ++rd; }
         }
     }
     if (!known) {                                                // a cleaner reads the rows on another compute unit
@@ -318,11 +318,9 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
     }
 }
 
-// Rows of an unconstrained layer: final at once, packed at their own index, always kept.
-template <int R>
-__device__ __forceinline__ void held_none(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h)
+// The mappings of an unconstrained layer's rows: always kept, packed at their own index.
+__device__ __forceinline__ void held_none_entries(const WorkItem& it, const HeldArgs& h)
 {
-    const HintArgs hint{nullptr, h.packed, 0, nullptr, h.layers};
     for (int rr = threadIdx.x; rr < it.nr; rr += kBlock) {
         const int g = it.g0 + rr, row = it.row0 + rr;
         const int k = h.layers[it.layer].kept_start + row;
@@ -332,15 +330,15 @@ __device__ __forceinline__ void held_none(const WorkItem& it, const ProjectArgs&
         if (h.im.sel) h.im.sel[g] = row;
         if (h.co.kept_idx) h.co.kept_idx[k] = row;
     }
-    project_rows_hinted<R, R != 8>(it, a, Rrt, hint);
 }
 
 // A workgroup behind all the items: waits until every item of its share is done, and takes those that were written before
 // their selection was known (none, unless other work held places that a layer's workgroups needed) from that form to their
-// final one.  Its waits end because no workgroup that it waits for waits without end.
-__device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, int n_held, const ProjectArgs& a,
-                                           const HeldArgs& h)
+// final one (finish).  Its waits end because no workgroup that it waits for waits without end.
+template <typename F>
+__device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, const HeldArgs& h, F finish)
 {
+    const int n_held = h.n_held;
     const int c = (int)blockIdx.x - h.n_items;
     const long long until = (long long)__builtin_amdgcn_s_memrealtime() + kHeldCleanLimit;
     for (int i0 = c; i0 < n_held; i0 += kHeldCleaners * kBlock) {
@@ -362,7 +360,7 @@ __device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, i
                        (long long)__builtin_amdgcn_s_memrealtime() <= until) __builtin_amdgcn_s_sleep(16);
             __syncthreads();
             __threadfence();                                     // the item's rows as its workgroup left them
-            hinted_repair_rows<1>(it, a, 1, h.pred, h.im.pos, true, h.packed ? h.packed + it.packed_off : nullptr);
+            finish(it);
         }
     }
 }
@@ -371,15 +369,218 @@ template <int R>
 __global__ __launch_bounds__(kBlock, kHeldPerUnit) void project_held(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt,
                                                           HeldArgs h)
 {
-    __shared__ HeldShared sh;
+    __shared__ HeldShared<kHeldLdsSlots> sh;
     if ((int)blockIdx.x >= h.n_items) {
-        held_clean(items, h.n_held, a, h);
+        held_clean(items, h, [&](const WorkItem& it) {
+            hinted_repair_rows<1>(it, a, 1, h.pred, h.im.pos, true, h.packed ? h.packed + it.packed_off : nullptr);
+        });
         return;
     }
     const WorkItem it = items[blockIdx.x];
     if (it.row0 == 0 && threadIdx.x == 0) held_layer_entries(it, h);
-    if (item_mode(it) == HSADMM_MODE_NONE) held_none<R>(it, a, Rrt, h);
-    else held_rows<R>(it, a, Rrt, h, sh);
+    if (item_mode(it) == HSADMM_MODE_NONE) {                     // final at once
+        const HintArgs hint{nullptr, h.packed, 0, nullptr, h.layers};
+        held_none_entries(it, h);
+        project_rows_hinted<R, R != 8>(it, a, Rrt, hint);        // (one chunk at a time with eight replicas: no registers to spare)
+    } else {
+        held_rows<R>(it, a, Rrt, h, sh);
+    }
+}
+
+// ------------------------------------------------------------------ the full candidate of Eq. (9)
+
+// What the weighted forms need beside HeldArgs.
+struct HeldWeighted {
+    const float* Zg;
+    const float* Vd;
+    const float* coef;
+};
+
+// Three values a slot wait, two of them in registers, so three workgroups share a unit.  Weighted steps of ResNet-50, us, in two
+// launches that touch Z, U and the kept rows' z and v twice / in this one: 250 / 231, 300 / 277, 338 / 320, 374 / 347 with 1, 4, 6,
+// 8 replicas.  (The residual norms on the way need the replicas' values until z~ is known; with them the launch gained nothing:
+// 345 / 347 us with 4 replicas, small networks 3 to 15 % slower.  They keep the other path.)
+constexpr int kHeldWeightedPerUnit = 3;
+constexpr int kHeldWeightedLds = kHeldSlots;
+constexpr int held_weighted_batch(int R) { return R == 8 ? 1 : 2; }
+
+// One FILTER row item: held_rows with the candidate z~ = fl(fl(a t) + fl(b (z - v))), t = Wbar + U.  z~ and t wait in
+// registers, the dual of a kept row in LDS; what is packed is z~ + v, v read again.
+template <int R, typename SHARED>
+__device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
+                                                   const HeldWeighted& x, SHARED& sh)
+{
+    const int RR = R > 0 ? R : Rrt;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const HeldPlaces at(it);
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    const float al = x.coef[2 * it.layer], bl = x.coef[2 * it.layer + 1];
+    if (threadIdx.x < it.nr) put_agent(&h.im.pos[it.g0 + threadIdx.x], (int32_t)kNotSelected);
+    v4f Zt[kHeldSlots], T[kHeldSlots];
+    {
+        constexpr int B = held_weighted_batch(R);
+        constexpr int kIn = R > 0 ? R : 1;
+        int q = 0, rd = 0;
+        double acc = 0.0;
+#pragma unroll
+        for (int s0 = 0; s0 < kHeldSlots; s0 += B)
+            if (s0 < at.nslot) {
+                v4f in[B][kIn], u[B], zg[B], vd[B];
+                int qb[B], rb[B];
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    qb[i] = q; rb[i] = s0 + i < at.nslot ? rd : it.nr;   // (no such row)
+                    if (++q == at.cpr) { q = 0; ++rd; }
+                }
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+#pragma unroll
+                    for (int r = 0; r < kIn; ++r) in[i][r] = at.fetch(a.W[r], qb[i], rb[i]);
+                    u[i] = at.fetch(a.Ur, qb[i], rb[i]);
+                    zg[i] = at.fetch(x.Zg, qb[i], rb[i]);
+                    vd[i] = at.fetch(x.Vd, qb[i], rb[i]);
+                }
+                v4f sum[B];
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    sum[i] = in[i][0];
+#pragma unroll
+                    for (int r = 1; r < kIn; ++r) sum[i] = sum[i] + in[i][r];
+                }
+                if (R == 0)
+                    for (int r = 1; r < RR; ++r) {
+                        v4f y[B];
+#pragma unroll
+                        for (int i = 0; i < B; ++i) y[i] = at.fetch(a.W[r], qb[i], rb[i]);
+#pragma unroll
+                        for (int i = 0; i < B; ++i) sum[i] = sum[i] + y[i];
+                    }
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    const int s = s0 + i;
+                    const v4f wb = sum[i] * a.inv_R;
+                    const v4f t = wb + u[i];
+                    const v4f qd = zg[i] - vd[i];
+                    const v4f att = t * al;
+                    const v4f bq = qd * bl;
+                    const v4f zt = att + bq;
+                    Zt[s] = zt;
+                    T[s] = t;
+                    sh.dual[s][threadIdx.x] = u[i] + (wb - zt);
+                    if (a.Wbar) at.put(a.Wbar, qb[i], rb[i], wb);
+                    acc = sq4(acc, zt);                          // (lanes without an element add zeros)
+                    if (s < at.nslot && qb[i] == at.cpr - 1) {   // the row is complete
+                        if (!at.wide) {
+                            acc = wave_xor_sum(acc, at.lpr);
+                            const int row = at.row(rb[i]);
+                            if (at.j == 0 && row < it.nr) put_agent(&a.key[it.g0 + row], acc);
+                        } else {
+                            acc = wave_xor_sum(acc, kWave);
+                            if (lane == 0) sh.wsum[rb[i]][wave] = acc;
+                        }
+                        acc = 0.0;
+                    }
+                }
+            }
+    }
+    if (at.wide) {
+        __syncthreads();
+        if (threadIdx.x < it.nr) {
+            double s = sh.wsum[threadIdx.x][0];
+            for (int w = 1; w < kWaves; ++w) s += sh.wsum[threadIdx.x][w];
+            put_agent(&a.key[it.g0 + threadIdx.x], s);
+        }
+    }
+    if (held_publish(it, h)) held_select(it, h, a.key, sh.topk);
+    const bool known = held_wait(it, h, sh.rank);
+    if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
+    float* const pk_layer = (h.packed && known) ? h.packed + it.packed_off : nullptr;
+    {
+        constexpr int B = 5;
+        int q = 0, rd = 0;
+#pragma unroll
+        for (int s0 = 0; s0 < kHeldSlots; s0 += B) {
+            if (s0 < at.nslot) {
+                v4f vd[B];
+                int qb[B], rb[B], rank[B];
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    qb[i] = q; rb[i] = s0 + i < at.nslot ? rd : it.nr;
+                    if (++q == at.cpr) { q = 0; ++rd; }
+                    const int row = at.row(rb[i]);
+                    rank[i] = row < it.nr ? (known ? sh.rank[row] : 0) : -1;
+                    vd[i] = zero4;
+                    if (pk_layer && rank[i] >= 0) vd[i] = at.fetch(x.Vd, qb[i], rb[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    const int s = s0 + i;
+                    const bool kept = rank[i] >= 0;
+                    const v4f d = sh.dual[s][threadIdx.x];
+                    // (written too early: t and the dual of a kept row, from which either outcome can be formed)
+                    at.put(a.Z, qb[i], rb[i], known ? (kept ? Zt[s] : zero4) : T[s]);
+                    at.put(a.U, qb[i], rb[i], kept ? d : T[s]);
+                    if (pk_layer && kept) at.put_packed(pk_layer + (int64_t)rank[i] * it.row_len, qb[i], Zt[s] + vd[i]);
+                }
+            }
+        }
+    }
+    if (!known) {                                                // a cleaner reads the rows on another compute unit
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 2);
+    }
+}
+
+// weighted_fixup_rows by a cleaner: the item's ranks and rows as other workgroups of this launch left them.
+__device__ __forceinline__ void held_weighted_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h,
+                                                     const HeldWeighted& x)
+{
+    const HeldPlaces at(it);
+    const float al = x.coef[2 * it.layer], bl = x.coef[2 * it.layer + 1];
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    int q = 0, rd = 0;
+    for (int s = 0; s < at.nslot; ++s) {
+        const int row = at.row(rd);
+        if (row < it.nr) {
+            const int rank = get_agent(&h.im.pos[it.g0 + row]);
+            const v4f t = at.fetch(a.Z, q, rd);
+            if (rank >= 0) {
+                const v4f vd = at.fetch(x.Vd, q, rd);
+                const v4f qd = at.fetch(x.Zg, q, rd) - vd;
+                const v4f att = t * al;
+                const v4f bq = qd * bl;
+                const v4f zt = att + bq;
+                at.put(a.Z, q, rd, zt);
+                if (h.packed) at.put_packed(h.packed + it.packed_off + (int64_t)rank * it.row_len, q, zt + vd);
+            } else {
+                at.put(a.U, q, rd, t);
+                at.put(a.Z, q, rd, zero4);
+            }
+        }
+        if (++q == at.cpr) { q = 0; ++rd; }
+    }
+}
+
+template <int R>
+__global__ __launch_bounds__(kBlock, kHeldWeightedPerUnit) void weighted_held(const WorkItem* __restrict__ items, WeightedArgs w,
+                                                                              int Rrt, HeldArgs h, HeldWeighted x)
+{
+    __shared__ HeldShared<kHeldWeightedLds> sh;
+    if ((int)blockIdx.x >= h.n_items) {
+        held_clean(items, h, [&](const WorkItem& it) { held_weighted_finish(it, w.p, h, x); });
+        return;
+    }
+    const WorkItem it = items[blockIdx.x];
+    if (it.row0 == 0 && threadIdx.x == 0) held_layer_entries(it, h);
+    if (item_mode(it) == HSADMM_MODE_NONE) {
+        const WeightedHint hint{nullptr, h.packed, nullptr, h.layers};
+        held_none_entries(it, h);
+        weighted_rows_hinted<R, false>(it, w, Rrt, hint);
+    } else {
+        held_weighted_rows<R>(it, w.p, Rrt, h, x, sh);
+    }
 }
 
 // Inside a captured graph a call's number is the same in every replay: the tags are cleared first.

@@ -49,6 +49,20 @@ def test_edges_of_what_a_workgroup_holds(R, patience):
     r.close()
 
 
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 8])
+def test_edges_with_the_full_candidate(R, patience):
+    """The candidate of Eq. (9), with and without the shrinkage, then the expansion with the inter-node dual: against the
+    oracle's chain."""
+    from tests.test_gpu_weighted import _phase4_chain
+    wl = wk.custom_workload(EDGES, R=R, seed=60 + R, sigma_replica=0.03)
+    W, U = wk.generate(wl)
+    rng = np.random.default_rng(R)
+    L = len(wl.layers)
+    a, b = rng.uniform(0.3, 1.0, L).astype(np.float32), rng.uniform(0.0, 0.7, L).astype(np.float32)
+    for one_call in (True, False):
+        _phase4_chain(wl, W, U, a, b, rng, fused_dual=True, one_call=one_call)
+
+
 @pytest.mark.parametrize("n_layers", [1, 40])
 def test_small_and_full_items(n_layers, patience):
     """Layers alone (items of one chunk a lane) and enough of them to fill every place with ten."""
