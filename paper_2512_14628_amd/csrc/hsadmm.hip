@@ -130,6 +130,10 @@ struct hsadmm_plan {
     // them are held (FILTER; none: the plan does not take that path)
     std::vector<WorkItem> items_held, items_wheld;
     int32_t n_held = 0, n_wheld = 0;
+    // tiles_held: the tiles of the CHANNEL layers, then the row items of the unconstrained ones
+    std::vector<WorkItem> items_theld;
+    int32_t n_theld = 0;
+    bool theld_two = false;             // ... also where only two workgroups share a compute unit
     long long held_patience = kHeldPatience;
     std::vector<WorkItem> items_rows;   // compact / expand kernels
     std::vector<WorkItem> items_fix;    // project_fixup, weighted_fixup: the row items of the FILTER layers
@@ -152,6 +156,7 @@ struct hsadmm_plan {
     WorkItem* d_items_est = nullptr;
     WorkItem* d_items_held = nullptr;
     WorkItem* d_items_wheld = nullptr;
+    WorkItem* d_items_theld = nullptr;
     WorkItem* d_items_rows = nullptr;
     WorkItem* d_items_fix = nullptr;
     WorkItem* d_items_none = nullptr;
@@ -577,6 +582,37 @@ void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& o
     }
 }
 
+// Weighted steps with eight replicas load a tile's rows one at a time (two spill), which few tiles do not hide: plain networks of
+// width 64 (38 tiles) 54.0 us without, 59.2 with, 88 (79 tiles) 66.5 / 66.0, 112 (107) 75.9 / 71.2.
+constexpr int kHeldTilesWeighted8 = 80;
+
+// The held tiles (kernels_held.hpp), for plans of CHANNEL and unconstrained layers without runs of channels, every layer's
+// tiles on the chip at once with a quarter of the places to spare, three quarters of all tiles of whole words (a ragged
+// one holds a quarter of the elements).
+void lay_out_held_tiles(hsadmm_plan* p, int compute_units)
+{
+    std::vector<WorkItem> items;
+    int64_t largest = 0, narrow = 0;
+    for (size_t l = 0; l < p->dev_layers.size(); ++l) {
+        const DevLayer& d = p->dev_layers[l];
+        if (d.mode == HSADMM_MODE_NONE) continue;
+        if (d.mode != HSADMM_MODE_CHANNEL || d.span >= 1 || d.khw > kColChunk) return;
+        const size_t first = items.size();
+        add_tile_items(items, (int)l, d, kChanRows, false);
+        for (size_t i = first; i < items.size(); ++i) items[i].lpr = (int32_t)first;
+        largest = std::max(largest, (int64_t)(items.size() - first));
+        if (d.row_len % 4 != 0) narrow += (int64_t)(items.size() - first);
+    }
+    if (items.empty()) return;
+    const auto fits = [&](int per_unit) { return largest <= (int64_t)per_unit * compute_units * 3 / 4; };
+    // (a tag, a state, a strip's tag and its claim for every tile take the place of the residual sums' partials)
+    if (!fits(held_tile_per_unit(1, false)) || narrow * 4 > (int64_t)items.size() || items.size() > p->items_rows.size()) return;
+    p->n_theld = (int32_t)items.size();
+    p->theld_two = fits(held_tile_per_unit(1, true));
+    p->items_theld = std::move(items);
+    p->items_theld.insert(p->items_theld.end(), p->items_none.begin(), p->items_none.end());
+}
+
 // A number for a call of project_held that no other call has and no other content of the scratch can equal: a negative
 // NaN's bits (the scratch holds sums of squares and whole numbers otherwise) with 50 bits of a counter that starts
 // anywhere.
@@ -673,6 +709,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
         {
             lay_out_held(p, (int64_t)kHeldPerUnit * compute_units, p->items_held, p->n_held);
             lay_out_held(p, (int64_t)kHeldWeightedPerUnit * compute_units, p->items_wheld, p->n_wheld);
+            lay_out_held_tiles(p, compute_units);
         }
         // (environment, read here once per plan: HSADMM_HELD_PATIENCE, ticks of 10 ns, is how the tests have rows written
         // before their selection is known)
@@ -738,6 +775,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
     upload(p->items_est, &p->d_items_est);
     upload(p->items_held, &p->d_items_held);
     upload(p->items_wheld, &p->d_items_wheld);
+    upload(p->items_theld, &p->d_items_theld);
     upload(p->items_plain, &p->d_items_plain);
     upload(p->items_bfinal, &p->d_items_bfinal);
     upload(p->items_chan, &p->d_items_chan);
@@ -767,6 +805,7 @@ void hsadmm_plan_destroy(hsadmm_plan_t* p)
     if (p->d_items_est) (void)hipFree(p->d_items_est);
     if (p->d_items_held) (void)hipFree(p->d_items_held);
     if (p->d_items_wheld) (void)hipFree(p->d_items_wheld);
+    if (p->d_items_theld) (void)hipFree(p->d_items_theld);
     if (p->d_items_plain) (void)hipFree(p->d_items_plain);
     if (p->d_items_bfinal) (void)hipFree(p->d_items_bfinal);
     if (p->d_items_chan) (void)hipFree(p->d_items_chan);
@@ -798,7 +837,7 @@ struct CompactOut {
 
 // What a launch over the held items needs; inside a capture its tags are cleared first.
 static hipError_t held_args(const hsadmm_plan_t* p, size_t n_items, int32_t n_held, uint8_t* mask, const CompactOut& out, char* ws, hipStream_t s,
-                            int32_t* sel_out, HeldArgs& x)
+                            int32_t* sel_out, HeldArgs& x, size_t words = 0)
 {
     x = HeldArgs{};
     x.n_items = (int)n_items;
@@ -820,9 +859,28 @@ static hipError_t held_args(const hsadmm_plan_t* p, size_t n_items, int32_t n_he
     x.n_layers = (int)p->layers.size();
     x.pack_align = (int)p->pack_align;
     if (!stream_is_captured(s)) return hipSuccess;
-    const int n = x.n_items + x.n_held;
+    const int n = words ? (int)words : x.n_items + x.n_held;
     hipLaunchKernelGGL(held_clear, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, x.tag, n);
     return hipGetLastError();
+}
+
+static hipError_t launch_tiles_held(const hsadmm_plan_t* p, bool weighted, const WeightedArgs& w, int R, uint8_t* mask,
+                                    const CompactOut& out, char* ws, hipStream_t s, int32_t* sel_out)
+{
+    const size_t n = (size_t)p->n_theld;
+    unsigned long long* tag = reinterpret_cast<unsigned long long*>(ws + p->ws.respart);
+    HeldArgs x;
+    hipError_t e = held_args(p, p->items_theld.size(), p->n_theld, mask, out, ws, s, sel_out, x, 4 * n);
+    if (e != hipSuccess) return e;
+    x.state = tag + n;
+    const HeldTiles t{tag + 2 * n, tag + 3 * n, w.p.colpart};
+    return for_replica_count<false>(R, [&](auto c) {
+        constexpr int RC = decltype(c)::value;
+        const unsigned grid = (unsigned)p->items_theld.size() + kHeldCleaners;
+        const WorkItem* items = p->d_items_theld;
+        return weighted ? launch(p, kWKeys, tiles_held<RC, true>, grid, kBlock, s, items, w, R, x, t)
+                        : launch(p, kPass1, tiles_held<RC, false>, grid, kBlock, s, items, w, R, x, t);
+    });
 }
 
 // sel_prev: the previous selection's record, which predicts this one (null: no prediction); sel_out: receives this
@@ -880,6 +938,12 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
                           (const WorkItem*)p->d_items_held, a, (int)R, x);
         });
         return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
+    }
+    if (sel_prev == nullptr && p->n_theld > 0 && (R != 8 || p->theld_two)) {
+        WeightedArgs w{};
+        w.p = a;
+        return launch_tiles_held(p, false, w, R, mask, out ? *out : CompactOut{}, ws, s, sel_out) == hipSuccess ? HSADMM_OK
+                                                                                                              : HSADMM_ERR_HIP;
     }
     EstArgs ex{};
     if (est) {
@@ -1335,6 +1399,9 @@ static int project_weighted_impl(const hsadmm_plan_t* p, const float* const* W_r
     const unsigned grid = (unsigned)p->items_proj.size();
     const WorkItem* items = p->d_items_proj;
     hipError_t e;
+    if (sel_prev == nullptr && !residuals && p->n_theld >= (R == 8 ? kHeldTilesWeighted8 : 1) && p->theld_two)
+        return launch_tiles_held(p, true, w, R, mask, out ? *out : CompactOut{}, ws, s, sel_out) == hipSuccess ? HSADMM_OK
+                                                                                                             : HSADMM_ERR_HIP;
     // rows that can wait for the selection on the chip: one launch (kernels_held.hpp)
     if (sel_prev == nullptr && !residuals && p->n_wheld > 0) {
         HeldArgs x;

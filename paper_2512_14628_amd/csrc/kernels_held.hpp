@@ -20,7 +20,7 @@ namespace {
 // thread, the dual in 32 KB of LDS and 8 registers (10 M elements on 256 units).  ResNet-50, 4 replicas, a step: eight slots all
 // in registers 178 us, ten of them on three workgroups 178, twelve on three 198, twenty on two 198; with LDS ten on four
 // 162, twelve 168 to 173, sixteen on three 206, twenty-four on two 179.  Before (pass 1, selection, fix-up and packing) / now:
-// ResNet-50, 4 replicas 183 / 162; ResNet-18, 1 replica 77.7 / 62.0; of width 45, 3 replicas 60.8 / 46.2; a plain network
+// ResNet-50, 4 replicas 183 / 159; ResNet-18, 1 replica 77.7 / 61.2; of width 45, 3 replicas 60.8 / 47; a plain network
 // of width 16 21.0 / 15.4.
 constexpr int kHeldSlots = 10;           // 128-bit chunks a thread holds
 constexpr int kHeldLdsSlots = 8;         // ... the duals of the first ones in LDS, the others' in registers
@@ -126,25 +126,26 @@ __device__ __forceinline__ void held_layer_entries(const WorkItem& it, const Hel
     }
 }
 
-// Waits for the ranks of the item's rows -> rank (-1: pruned); false if the patience ran out first.
-__device__ __forceinline__ bool held_wait(const WorkItem& it, const HeldArgs& h, int* rank)
+// Waits for the ranks of n groups (a thread each) from group g0 on -> rank (-1: pruned); false if the patience ran out first.
+__device__ __forceinline__ bool held_wait_groups(int g0, int n, const HeldArgs& h, int* rank)
 {
     const int t = threadIdx.x;
     int r = -1;
-    if (t < it.nr) {
+    if (t < n) {
         const long long until = (long long)__builtin_amdgcn_s_memrealtime() + h.patience;
         for (;;) {
-            r = get_agent(&h.im.pos[it.g0 + t]);
+            r = get_agent(&h.im.pos[g0 + t]);
             if (r != kNotSelected || (long long)__builtin_amdgcn_s_memrealtime() > until) break;
             __builtin_amdgcn_s_sleep(8);
         }
         rank[t] = r;
     }
-    return __syncthreads_or(t < it.nr && r == kNotSelected) == 0;
+    return __syncthreads_or(t < n && r == kNotSelected) == 0;
 }
 
-// Where the slots of a thread lie in a row item.  The choice between a row's words and a ragged row's last floats (in the
-// slot behind them, one to a lane) is one that the whole workgroup makes, so that no load waits for another's register.
+// Where the slots of a thread lie in a row item; the last floats of a ragged row lie in the slot behind its words, one to a
+// lane.  WHOLE: no row has a tail (a choice made per slot would have loads wait for each other).
+template <bool WHOLE>
 struct HeldPlaces {
     int64_t base;
     int nr, row_len, nchunk, lpr, rows_at_once, sub, j, cpr, tail_slot, nslot;
@@ -161,7 +162,7 @@ struct HeldPlaces {
         sub = threadIdx.x / lpr;
         j = threadIdx.x - sub * lpr;
         cpr = it.khw;                                            // slots per row
-        tail_slot = (row_len & 3) ? cpr - 1 : cpr;
+        tail_slot = WHOLE ? cpr : cpr - 1;
         nslot = cpr * ((nr + rows_at_once - 1) / rows_at_once);
     }
     __device__ __forceinline__ int row(int rd) const { return rd * rows_at_once + sub; }
@@ -170,7 +171,7 @@ struct HeldPlaces {
         v4f x = {0.f, 0.f, 0.f, 0.f};
         if (row(rd) < nr) {
             const float* r = p + base + (int64_t)row(rd) * row_len;
-            if (q != tail_slot) {
+            if (WHOLE || q != tail_slot) {
                 const int c = j + q * lpr;
                 if (c < nchunk) x = ld4(r + 4 * c);
             } else if (j < (row_len & 3)) {
@@ -183,7 +184,7 @@ struct HeldPlaces {
     {
         if (row(rd) >= nr) return;
         float* r = p + base + (int64_t)row(rd) * row_len;
-        if (q != tail_slot) {
+        if (WHOLE || q != tail_slot) {
             const int c = j + q * lpr;
             if (c < nchunk) st4(r + 4 * c, x);
         } else if (j < (row_len & 3)) {
@@ -193,7 +194,7 @@ struct HeldPlaces {
     // the same into a packed row, which may begin at any float
     __device__ __forceinline__ void put_packed(float* r, int q, const v4f& x) const
     {
-        if (q != tail_slot) {
+        if (WHOLE || q != tail_slot) {
             const int c = j + q * lpr;
             if (c < nchunk) st4u(r + 4 * c, x);
         } else if (j < (row_len & 3)) {
@@ -203,12 +204,12 @@ struct HeldPlaces {
 };
 
 // One FILTER row item.
-template <int R, typename SHARED>
+template <int R, bool WHOLE, typename SHARED>
 __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h, SHARED& sh)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const HeldPlaces at(it);
+    const HeldPlaces<WHOLE> at(it);
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
     if (threadIdx.x < it.nr) put_agent(&h.im.pos[it.g0 + threadIdx.x], (int32_t)kNotSelected);
     v4f V[kHeldSlots];                                           // the candidate
@@ -286,7 +287,7 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
         }
     }
     if (held_publish(it, h)) held_select(it, h, a.key, sh.topk);
-    const bool known = held_wait(it, h, sh.rank);
+    const bool known = held_wait_groups(it.g0, it.nr, h, sh.rank);
     if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
     const DevLayer& L = h.layers[it.layer];
     const bool kept_default = 2 * L.k >= L.G;                    // written too early: in the likelier form
@@ -332,11 +333,14 @@ __device__ __forceinline__ void held_none_entries(const WorkItem& it, const Held
     }
 }
 
+__device__ __forceinline__ int held_row_group(const WorkItem& it, int t) { return t < it.nr ? it.g0 + t : -1; }
+
 // A workgroup behind all the items: waits until every item of its share is done, and takes those that were written before
 // their selection was known (none, unless other work held places that a layer's workgroups needed) from that form to their
 // final one (finish).  Its waits end because no workgroup that it waits for waits without end.
-template <typename F>
-__device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, const HeldArgs& h, F finish)
+// group(item, t): the group whose rank thread t waits for before that (-1: none).
+template <typename G, typename F>
+__device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, const HeldArgs& h, G group, F finish)
 {
     const int n_held = h.n_held;
     const int c = (int)blockIdx.x - h.n_items;
@@ -355,9 +359,9 @@ __device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, c
             if (k >= n_held) break;
             if (get_agent(&h.state[k]) != h.gen + 2) continue;
             const WorkItem it = items[k];
-            if ((int)threadIdx.x < it.nr)
-                while (get_agent(&h.im.pos[it.g0 + threadIdx.x]) == kNotSelected &&
-                       (long long)__builtin_amdgcn_s_memrealtime() <= until) __builtin_amdgcn_s_sleep(16);
+            if (const int g = group(it, (int)threadIdx.x); g >= 0)
+                while (get_agent(&h.im.pos[g]) == kNotSelected && (long long)__builtin_amdgcn_s_memrealtime() <= until)
+                    __builtin_amdgcn_s_sleep(16);
             __syncthreads();
             __threadfence();                                     // the item's rows as its workgroup left them
             finish(it);
@@ -371,7 +375,7 @@ __global__ __launch_bounds__(kBlock, kHeldPerUnit) void project_held(const WorkI
 {
     __shared__ HeldShared<kHeldLdsSlots> sh;
     if ((int)blockIdx.x >= h.n_items) {
-        held_clean(items, h, [&](const WorkItem& it) {
+        held_clean(items, h, held_row_group, [&](const WorkItem& it) {
             hinted_repair_rows<1>(it, a, 1, h.pred, h.im.pos, true, h.packed ? h.packed + it.packed_off : nullptr);
         });
         return;
@@ -383,7 +387,8 @@ __global__ __launch_bounds__(kBlock, kHeldPerUnit) void project_held(const WorkI
         held_none_entries(it, h);
         project_rows_hinted<R, R != 8>(it, a, Rrt, hint);        // (one chunk at a time with eight replicas: no registers to spare)
     } else {
-        held_rows<R>(it, a, Rrt, h, sh);
+        if (item_vec(it)) held_rows<R, true>(it, a, Rrt, h, sh);
+        else held_rows<R, false>(it, a, Rrt, h, sh);
     }
 }
 
@@ -406,14 +411,14 @@ constexpr int held_weighted_batch(int R) { return R == 8 ? 1 : 2; }
 
 // One FILTER row item: held_rows with the candidate z~ = fl(fl(a t) + fl(b (z - v))), t = Wbar + U.  z~ and t wait in
 // registers, the dual of a kept row in LDS; what is packed is z~ + v, v read again.
-template <int R, typename SHARED>
+template <int R, bool WHOLE, typename SHARED>
 __device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
                                                    const HeldWeighted& x, SHARED& sh)
 {
     const int RR = R > 0 ? R : Rrt;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const HeldPlaces at(it);
+    const HeldPlaces<WHOLE> at(it);
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
     const float al = x.coef[2 * it.layer], bl = x.coef[2 * it.layer + 1];
     if (threadIdx.x < it.nr) put_agent(&h.im.pos[it.g0 + threadIdx.x], (int32_t)kNotSelected);
@@ -493,7 +498,7 @@ __device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const Pro
         }
     }
     if (held_publish(it, h)) held_select(it, h, a.key, sh.topk);
-    const bool known = held_wait(it, h, sh.rank);
+    const bool known = held_wait_groups(it.g0, it.nr, h, sh.rank);
     if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
     float* const pk_layer = (h.packed && known) ? h.packed + it.packed_off : nullptr;
     {
@@ -534,10 +539,11 @@ __device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const Pro
 }
 
 // weighted_fixup_rows by a cleaner: the item's ranks and rows as other workgroups of this launch left them.
+template <bool WHOLE>
 __device__ __forceinline__ void held_weighted_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h,
                                                      const HeldWeighted& x)
 {
-    const HeldPlaces at(it);
+    const HeldPlaces<WHOLE> at(it);
     const float al = x.coef[2 * it.layer], bl = x.coef[2 * it.layer + 1];
     const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
     int q = 0, rd = 0;
@@ -569,7 +575,10 @@ __global__ __launch_bounds__(kBlock, kHeldWeightedPerUnit) void weighted_held(co
 {
     __shared__ HeldShared<kHeldWeightedLds> sh;
     if ((int)blockIdx.x >= h.n_items) {
-        held_clean(items, h, [&](const WorkItem& it) { held_weighted_finish(it, w.p, h, x); });
+        held_clean(items, h, held_row_group, [&](const WorkItem& it) {
+            if (item_vec(it)) held_weighted_finish<true>(it, w.p, h, x);
+            else held_weighted_finish<false>(it, w.p, h, x);
+        });
         return;
     }
     const WorkItem it = items[blockIdx.x];
@@ -579,7 +588,339 @@ __global__ __launch_bounds__(kBlock, kHeldWeightedPerUnit) void weighted_held(co
         held_none_entries(it, h);
         weighted_rows_hinted<R, false>(it, w, Rrt, hint);
     } else {
-        held_weighted_rows<R>(it, w.p, Rrt, h, x, sh);
+        if (item_vec(it)) held_weighted_rows<R, true>(it, w.p, Rrt, h, x, sh);
+        else held_weighted_rows<R, false>(it, w.p, Rrt, h, x, sh);
+    }
+}
+
+// ------------------------------------------------------------------ input-channel groups
+
+// A tile of a CHANNEL layer (kChanRows rows by one column strip, project_tile's) waits in the same way: a wave has its
+// sixteen rows in as many slots, the candidate in registers, the dual of a kept element in LDS and registers.  The tile that
+// finds its strip complete adds up the strip's column sums, the one that finds the layer's strips complete finishes the
+// channel keys and selects; additions in the order of the other forms.  Bounded by HBM traffic, R + 3 arenas and the packed
+// rows; before, pass 1 parked the mean (or the replicas were read twice) and a final pass read it and the dual again, R + 6.
+// Three workgroups a compute unit hold 12.6 M elements, two (weighted: three values an element; eight replicas) 8.4 M.
+// Before / with it, us: ResNet-152, 4 replicas, a step 525 / 441, weighted 808 / 688; ResNet-50, keep 0.5, 1, 2, 4, 8
+// replicas 164 / 141, 193 / 158, 243 / 193, 322 / 255, weighted 280 / 250, 313 / 266, 368 / 299, 449 / 374; plain network of
+// width 64, 4 replicas 38.5 / 33.1.
+constexpr int kHeldTileSlots = kChanRows / kWaves;
+constexpr int kHeldTileLds = 10;         // ... the duals of the first ones in LDS
+constexpr int held_tile_per_unit(int R, bool weighted) { return weighted || R == 8 ? 2 : 3; }
+// slots whose loads are in flight together, as many as spill nothing
+constexpr int held_tile_batch(int R, bool weighted) { return weighted ? (R == 1 ? 4 : R == 8 ? 1 : 2) : (R <= 2 ? 4 : 2); }
+
+// WorkItem fields of a held tile: lpr = index of the layer's first tile.
+struct HeldTiles {
+    unsigned long long* strip_tag;      // per strip (at the layer's first tile + strip): gen once its column sums are complete
+    unsigned long long* strip_claim;    // ... gen once a tile has begun to add them up
+    double* colpart;
+};
+
+struct HeldTileShared {
+    v4f dual[kHeldTileLds][kBlock];
+    TopkShared topk;
+    double part[kWaves][kWave * 4];
+    int rank[kBlock];
+    int claimed;
+};
+
+__device__ __forceinline__ int tile_strip_cols(const WorkItem& it) { return kWave * (item_vec(it) ? 4 : 1); }
+
+// Called by the whole workgroup when its column sums have been stored by put_agent.  True: all column sums of the layer are
+// complete, in the first row block's place.
+__device__ __forceinline__ bool held_tile_publish(const WorkItem& it, const HeldArgs& h, const HeldTiles& x, HeldTileShared& sh)
+{
+    const int cols = tile_strip_cols(it);
+    const int n_strips = (it.row_len + cols - 1) / cols;
+    const int n_rb = h.layers[it.layer].n_rowblocks;
+    const int strip = it.col0 / cols;
+    const int first = it.lpr;
+    stores_arrived();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        put_agent(&h.tag[blockIdx.x], h.gen);
+        stores_arrived();
+    }
+    __syncthreads();
+    bool ok = true;
+    for (int rb = threadIdx.x; rb < n_rb; rb += kBlock) ok = ok && get_agent(&h.tag[first + rb * n_strips + strip]) == h.gen;
+    if (__syncthreads_and(ok) == 0) return false;
+    // one tile alone adds the strip up, as the sums take the place of the first row block's
+    if (threadIdx.x == 0)
+        sh.claimed = __hip_atomic_exchange(&x.strip_claim[first + strip], h.gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == h.gen;
+    __syncthreads();
+    if (sh.claimed) return false;
+    double* const sums = x.colpart + h.layers[it.layer].colpart_off;
+    const int col = it.col0 + (int)threadIdx.x;
+    if ((int)threadIdx.x < cols && col < it.row_len) {
+        double acc = 0.0;
+        int rb = 0;
+        for (; rb + 8 <= n_rb; rb += 8) {
+            double p[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) p[b] = get_agent(&sums[(int64_t)(rb + b) * it.row_len + col]);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) acc += p[b];
+        }
+        for (; rb < n_rb; ++rb) acc += get_agent(&sums[(int64_t)rb * it.row_len + col]);
+        put_agent(&sums[col], acc);
+    }
+    stores_arrived();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        put_agent(&x.strip_tag[first + strip], h.gen);
+        stores_arrived();
+    }
+    __syncthreads();
+    ok = true;
+    for (int s = threadIdx.x; s < n_strips; s += kBlock) ok = ok && get_agent(&x.strip_tag[first + s]) == h.gen;
+    return __syncthreads_and(ok) != 0;
+}
+
+// The channel keys from the column sums, then the selection.
+__device__ __forceinline__ void held_tile_select(const WorkItem& it, const HeldArgs& h, const HeldTiles& x, double* key,
+                                                 HeldTileShared& sh)
+{
+    const DevLayer& L = h.layers[it.layer];
+    const double* const sums = x.colpart + L.colpart_off;
+    for (int g = threadIdx.x; g < L.G; g += kBlock) {
+        const double* const c = sums + (int64_t)g * L.khw;
+        double acc = 0.0;
+        int t = 0;
+        for (; t + 9 <= L.khw; t += 9) {                         // (a 3 x 3 kernel's in one go)
+            double y[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) y[i] = get_agent(&c[t + i]);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) acc += y[i];
+        }
+        for (; t < L.khw; ++t) acc += get_agent(&c[t]);
+        put_agent(&key[L.group_base + g], acc);
+    }
+    stores_arrived();
+    __syncthreads();
+    held_select(it, h, key, sh.topk);
+}
+
+// VEC: rows of whole words (four columns a lane, else one); a choice within the loop would make loads wait for each other.
+template <int R, bool WEIGHTED, bool VEC>
+__device__ __forceinline__ void held_tile(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
+                                          const HeldTiles& x, HeldTileShared& sh)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int row_len = it.row_len;
+    constexpr int vw = VEC ? 4 : 1;
+    const int col = it.col0 + lane * vw;
+    const bool in = col < row_len;
+    const int khw = it.khw;
+    const DivKhw div(khw);
+    const int last_col = min(row_len, it.col0 + kWave * vw) - 1;
+    const int ch0 = div(it.col0), n_ch = div(last_col) - ch0 + 1;        // the strip's channels, at most a thread each
+    const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    if ((int)threadIdx.x < n_ch) put_agent(&h.im.pos[it.g0 + ch0 + threadIdx.x], (int32_t)kNotSelected);
+    auto fetch = [&](const float* p, int s) -> v4f {
+        v4f v = zero4;
+        const int rr = wave + s * kWaves;
+        if (in && rr < it.nr) {
+            if (VEC) v = ld4(p + it.base + (int64_t)rr * row_len + col);
+            else v.x = ld1(p + it.base + (int64_t)rr * row_len + col);
+        }
+        return v;
+    };
+    auto put = [&](float* p, int s, const v4f& v) {
+        const int rr = wave + s * kWaves;
+        if (!in || rr >= it.nr) return;
+        if (VEC) st4(p + it.base + (int64_t)rr * row_len + col, v);
+        else st1(p + it.base + (int64_t)rr * row_len + col, v.x);
+    };
+    v4f V[kHeldTileSlots], D[kHeldTileSlots - kHeldTileLds], T[WEIGHTED ? kHeldTileSlots : 1];
+    {
+        constexpr int B = held_tile_batch(R, WEIGHTED);
+        constexpr int kIn = R > 0 ? R : 1;
+        double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
+#pragma unroll
+        for (int s0 = 0; s0 < kHeldTileSlots; s0 += B)
+            if (s0 * kWaves < it.nr) {
+                v4f w[B][kIn], u[B], zg[B], vd[B], sum[B];
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+#pragma unroll
+                    for (int r = 0; r < kIn; ++r) w[i][r] = fetch(a.W[r], s0 + i);
+                    u[i] = fetch(a.Ur, s0 + i);
+                    if (WEIGHTED) {
+                        zg[i] = fetch(a.Zg, s0 + i);
+                        vd[i] = fetch(a.Vd, s0 + i);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    sum[i] = w[i][0];
+#pragma unroll
+                    for (int r = 1; r < kIn; ++r) sum[i] = sum[i] + w[i][r];
+                }
+                if (R == 0)
+                    for (int r = 1; r < Rrt; ++r) {
+                        v4f y[B];
+#pragma unroll
+                        for (int i = 0; i < B; ++i) y[i] = fetch(a.W[r], s0 + i);
+#pragma unroll
+                        for (int i = 0; i < B; ++i) sum[i] = sum[i] + y[i];
+                    }
+#pragma unroll
+                for (int i = 0; i < B; ++i) {
+                    const int s = s0 + i;
+                    const v4f wb = sum[i] * a.inv_R;
+                    v4f v = wb + u[i];
+                    if (WEIGHTED) {
+                        T[WEIGHTED ? s : 0] = v;
+                        const v4f q = zg[i] - vd[i];
+                        const v4f at = v * al;
+                        const v4f bq = q * bl;
+                        v = at + bq;
+                    }
+                    V[s] = v;
+                    const v4f d = u[i] + (wb - v);
+                    if (s < kHeldTileLds) sh.dual[s][threadIdx.x] = d;
+                    else D[s - kHeldTileLds] = d;
+                    if (a.Wbar) put(a.Wbar, s, wb);
+                    acc0 = fma((double)v.x, (double)v.x, acc0);  // (rows that are not there add zeros)
+                    acc1 = fma((double)v.y, (double)v.y, acc1);
+                    acc2 = fma((double)v.z, (double)v.z, acc2);
+                    acc3 = fma((double)v.w, (double)v.w, acc3);
+                }
+            }
+        sh.part[wave][lane * 4 + 0] = acc0;
+        sh.part[wave][lane * 4 + 1] = acc1;
+        sh.part[wave][lane * 4 + 2] = acc2;
+        sh.part[wave][lane * 4 + 3] = acc3;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < kWave * vw && it.col0 + (int)threadIdx.x < row_len) {
+        const int k = VEC ? (int)threadIdx.x : 4 * (int)threadIdx.x;
+        double s = sh.part[0][k];
+        for (int w = 1; w < kWaves; ++w) s += sh.part[w][k];
+        put_agent(&x.colpart[it.aux + it.col0 + threadIdx.x], s);
+    }
+    if (held_tile_publish(it, h, x, sh)) held_tile_select(it, h, x, a.key, sh);
+    const bool known = held_wait_groups(it.g0 + ch0, n_ch, h, sh.rank);
+    if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
+    bool kept[4] = {true, true, true, true};
+    int pc[4] = {-1, -1, -1, -1};                // packed column, -1: not packed
+    if (known && in) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < vw) {
+                const int ch = div(col + i);
+                const int r = sh.rank[ch - ch0];
+                kept[i] = r >= 0;
+                if (h.packed && r >= 0) pc[i] = r * khw + (col + i - ch * khw);
+            }
+    }
+    const int64_t packed_row_len = (int64_t)it.k * khw;
+    float* const pk = h.packed ? h.packed + it.packed_off + it.row0 * packed_row_len : nullptr;
+#pragma unroll
+    for (int s0 = 0; s0 < kHeldTileSlots; s0 += 4)
+        if (s0 * kWaves < it.nr) {
+            v4f vd[4];
+            if (WEIGHTED) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    vd[i] = zero4;
+                    if (pc[0] >= 0 || pc[1] >= 0 || pc[2] >= 0 || pc[3] >= 0) vd[i] = fetch(a.Vd, s0 + i);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int s = s0 + i;
+                const v4f d = s < kHeldTileLds ? sh.dual[s][threadIdx.x] : D[s < kHeldTileLds ? 0 : s - kHeldTileLds];
+                const v4f p = WEIGHTED ? T[WEIGHTED ? s : 0] : V[s];             // the dual of a pruned element
+                v4f z, u;
+                z.x = kept[0] ? V[s].x : 0.f; z.y = kept[1] ? V[s].y : 0.f; z.z = kept[2] ? V[s].z : 0.f; z.w = kept[3] ? V[s].w : 0.f;
+                u.x = kept[0] ? d.x : p.x; u.y = kept[1] ? d.y : p.y; u.z = kept[2] ? d.z : p.z; u.w = kept[3] ? d.w : p.w;
+                // (written too early: the candidate, or what it is made of, and the dual of a kept element)
+                put(a.Z, s, known ? z : p);
+                put(a.U, s, u);
+                const int rr = wave + s * kWaves;
+                if (pk && in && rr < it.nr) {
+                    float* row = pk + rr * packed_row_len;
+                    const v4f c = WEIGHTED ? z + vd[i] : z;
+                    if (pc[0] >= 0) row[pc[0]] = c.x;
+                    if (pc[1] >= 0) row[pc[1]] = c.y;
+                    if (pc[2] >= 0) row[pc[2]] = c.z;
+                    if (pc[3] >= 0) row[pc[3]] = c.w;
+                }
+            }
+        }
+    if (!known) {                                                // a cleaner reads the rows on another compute unit
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 2);
+    }
+}
+
+// A tile that was written before its selection was known: a thread takes a column.
+template <bool WEIGHTED>
+__device__ __forceinline__ void held_tile_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h)
+{
+    const int col = it.col0 + (int)threadIdx.x;
+    if ((int)threadIdx.x >= tile_strip_cols(it) || col >= it.row_len) return;
+    const DivKhw div(it.khw);
+    const int ch = div(col);
+    const int rank = get_agent(&h.im.pos[it.g0 + ch]);
+    const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
+    const int64_t packed_row_len = (int64_t)it.k * it.khw;
+    for (int rr = 0; rr < it.nr; ++rr) {
+        const int64_t e = it.base + (int64_t)rr * it.row_len + col;
+        float z = ld1(a.Z + e);
+        if (rank < 0) {
+            st1(a.U + e, z);
+            st1(a.Z + e, 0.f);
+            continue;
+        }
+        float vd = 0.f;
+        if (WEIGHTED) {
+            vd = ld1(a.Vd + e);
+            const float q = ld1(a.Zg + e) - vd;
+            const float at = z * al;
+            const float bq = q * bl;
+            z = at + bq;
+            st1(a.Z + e, z);
+        }
+        if (h.packed)
+            h.packed[it.packed_off + (it.row0 + rr) * packed_row_len + (int64_t)rank * it.khw + (col - ch * it.khw)] = WEIGHTED ? z + vd : z;
+    }
+}
+
+template <int R, bool WEIGHTED>
+__global__ __launch_bounds__(kBlock, held_tile_per_unit(R, WEIGHTED)) void tiles_held(const WorkItem* __restrict__ items, WeightedArgs w,
+                                                                                   int Rrt, HeldArgs h, HeldTiles x)
+{
+    __shared__ HeldTileShared sh;
+    if ((int)blockIdx.x >= h.n_items) {
+        held_clean(items, h, [&](const WorkItem& it, int t) {
+            const DivKhw div(it.khw);
+            const int ch0 = div(it.col0), last = min(it.row_len, it.col0 + tile_strip_cols(it)) - 1;
+            return ch0 + t <= div(last) ? it.g0 + ch0 + t : -1;
+        }, [&](const WorkItem& it) { held_tile_finish<WEIGHTED>(it, w.p, h); });
+        return;
+    }
+    const WorkItem it = items[blockIdx.x];
+    if (it.row0 == 0 && it.col0 == 0 && threadIdx.x == 0) held_layer_entries(it, h);
+    if (item_mode(it) == HSADMM_MODE_NONE) {                     // final at once
+        held_none_entries(it, h);
+        if constexpr (WEIGHTED) {
+            const WeightedHint hint{nullptr, h.packed, nullptr, h.layers};
+            weighted_rows_hinted<R, false>(it, w, Rrt, hint);
+        } else {
+            const HintArgs hint{nullptr, h.packed, 0, nullptr, h.layers};
+            project_rows_hinted<R>(it, w.p, Rrt, hint);
+        }
+    } else {
+        if (item_vec(it)) held_tile<R, WEIGHTED, true>(it, w.p, Rrt, h, x, sh);
+        else held_tile<R, WEIGHTED, false>(it, w.p, Rrt, h, x, sh);
     }
 }
 

@@ -13,12 +13,19 @@ import workloads as wk
 
 pytestmark = pytest.mark.gpu
 
-F, N = wk.MODE_FILTER, wk.MODE_NONE
+F, C, N = wk.MODE_FILTER, wk.MODE_CHANNEL, wk.MODE_NONE
 # (c_out, c_in, khw, mode, k): row lengths 1 .. 10240 floats, on either side of four floats, a wave and the whole workgroup
 EDGES = [(700, 1, 1, F, 300), (260, 2, 1, F, 7), (2600, 4, 1, F, 1300), (90, 5, 1, F, 90), (300, 7, 9, F, 100),
          (64, 64, 1, F, 1), (129, 65, 1, F, 64), (40, 255, 1, F, 39), (37, 256, 1, F, 12), (33, 2047, 1, F, 20),
          (18, 2048, 1, F, 5), (21, 2049, 1, F, 11), (1, 512, 9, F, 1), (19, 1024, 9, F, 9), (7, 9215, 1, F, 3),
          (9, 10240, 1, F, 4), (30, 100, 1, N, 30), (3, 2050, 1, N, 3)]
+
+
+# tiles of 64 rows by 256 columns (64 of a ragged row): one row, one strip, channels across strips, more channels than the
+# selection ranks from registers, one and all channels kept
+TILES = [(1, 4, 1, C, 2), (63, 8, 1, C, 1), (64, 64, 4, C, 30), (65, 65, 4, C, 64), (129, 28, 9, C, 28), (200, 60, 9, C, 25),
+         (64, 86, 6, C, 40), (70, 2500, 1, C, 1200), (130, 512, 9, C, 200), (17, 23, 3, C, 5), (40, 100, 1, N, 40),
+         (3, 2050, 1, N, 3)]
 
 
 @pytest.fixture(params=["", "0"], ids=["patient", "impatient"])
@@ -63,6 +70,24 @@ def test_edges_with_the_full_candidate(R, patience):
         _phase4_chain(wl, W, U, a, b, rng, fused_dual=True, one_call=one_call)
 
 
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 8])
+def test_tiles_of_channel_groups(R, patience):
+    from tests.gpu_harness import GpuRun
+    from tests.test_gpu_parity import _run
+    from tests.test_gpu_weighted import _phase4_chain
+    wl = wk.custom_workload(TILES, R=R, seed=80 + R, sigma_replica=0.03)
+    _run(wl, pack_align=4 if R == 3 else 1)
+    W, U = wk.generate(wl)
+    rng = np.random.default_rng(R)
+    L = len(wl.layers)
+    a, b = rng.uniform(0.3, 1.0, L).astype(np.float32), rng.uniform(0.0, 0.7, L).astype(np.float32)
+    for one_call in (True, False):
+        _phase4_chain(wl, W, U, a, b, rng, fused_dual=True, one_call=one_call)
+    r = GpuRun(wl, W, U)
+    assert _launches(r.plan, r.project_compact) == {"project_pass1": 1}
+    r.close()
+
+
 @pytest.mark.parametrize("n_layers", [1, 40])
 def test_small_and_full_items(n_layers, patience):
     """Layers alone (items of one chunk a lane) and enough of them to fill every place with ten."""
@@ -71,11 +96,13 @@ def test_small_and_full_items(n_layers, patience):
                             sigma_replica=0.03), determinism=False)
 
 
-def test_steps_on_one_workspace_with_every_option_and_replayed(patience):
+@pytest.mark.parametrize("shapes", [
+    [(384, 128, 9, F, 150), (512, 256, 1, F, 200), (100, 512, 1, N, 100), (300, 147, 1, F, 100)],
+    [(384, 128, 9, C, 50), (512, 256, 1, C, 200), (100, 512, 1, N, 100), (300, 148, 1, C, 100)]], ids=["filter", "channel"])
+def test_steps_on_one_workspace_with_every_option_and_replayed(shapes, patience):
     """Outer iterations with the selection record, the dual in place and in a second buffer, on one scratch that starts as
     garbage, then replayed from a captured graph (where a call's number is always the same)."""
-    wl = wk.custom_workload([(384, 128, 9, F, 150), (512, 256, 1, F, 200), (100, 512, 1, N, 100), (300, 147, 1, F, 100)],
-                            R=3, seed=8, sigma_replica=0.03)
+    wl = wk.custom_workload(shapes, R=3, seed=8, sigma_replica=0.03)
     W, U = wk.generate(wl)
     t = wl.table()
     dev = torch.device("cuda:0")
