@@ -573,8 +573,9 @@ void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& o
             }
         }
         if (want < kHeldSlots && (int64_t)items.size() > places) continue;
-        // (tags and give-ups, two words an item, take the place of the residual sums' partials: four words a row item)
-        if (items.size() > 2 * p->items_rows.size()) continue;
+        // (a tag for every item and a state for the held ones take the place of the residual sums' partials: four words a
+        // row item)
+        if (2 * items.size() + p->items_none.size() > 4 * p->items_rows.size()) continue;
         n_held = (int32_t)items.size();
         out = std::move(items);
         out.insert(out.end(), p->items_none.begin(), p->items_none.end());

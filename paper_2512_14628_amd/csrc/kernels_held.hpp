@@ -402,9 +402,10 @@ struct HeldWeighted {
 };
 
 // Three values a slot wait, two of them in registers, so three workgroups share a unit.  Weighted steps of ResNet-50, us, in two
-// launches that touch Z, U and the kept rows' z and v twice / in this one: 250 / 231, 300 / 277, 338 / 320, 374 / 347 with 1, 4, 6,
-// 8 replicas.  (The residual norms on the way need the replicas' values until z~ is known; with them the launch gained nothing:
-// 345 / 347 us with 4 replicas, small networks 3 to 15 % slower.  They keep the other path.)
+// launches that touch Z, U and the kept rows' z and v twice / in this one: 303 / 271 with 4 replicas; ResNet-152 with 8
+// 641 / 587; a plain network of width 100 with 1, 4, 8 replicas 34.2 / 31.4, 36.8 / 35.2, 53.8 / 43.0.  (The residual norms
+// on the way need the replicas' values until z~ is known: ResNet-50 350 / 341 us, but ResNet-18 of width 45 with 3 replicas
+// 130 / 137 and a plain network of width 128 with 8 57 / 66.  They keep the other path.)
 constexpr int kHeldWeightedPerUnit = 3;
 constexpr int kHeldWeightedLds = kHeldSlots;
 constexpr int held_weighted_batch(int R) { return R == 8 ? 1 : 2; }
