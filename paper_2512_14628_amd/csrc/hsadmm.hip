@@ -841,13 +841,10 @@ static hipError_t held_args(const hsadmm_plan_t* p, size_t n_items, int32_t n_he
                             int32_t* sel_out, HeldArgs& x, size_t words = 0)
 {
     x = HeldArgs{};
-    x.n_items = (int)n_items;
-    x.n_held = n_held;
     x.tag = reinterpret_cast<unsigned long long*>(ws + p->ws.respart);
-    x.state = x.tag + x.n_items;
+    x.state = x.tag + n_items;
     x.gen = held_number();
     x.patience = p->held_patience;
-    x.pred = reinterpret_cast<int32_t*>(ws + p->ws.pred);
     x.layers = p->d_layers;
     x.mask = mask;
     x.im.pos = reinterpret_cast<int32_t*>(ws + p->ws.pos);
@@ -860,7 +857,7 @@ static hipError_t held_args(const hsadmm_plan_t* p, size_t n_items, int32_t n_he
     x.n_layers = (int)p->layers.size();
     x.pack_align = (int)p->pack_align;
     if (!stream_is_captured(s)) return hipSuccess;
-    const int n = words ? (int)words : x.n_items + x.n_held;
+    const int n = words ? (int)words : (int)n_items + n_held;
     hipLaunchKernelGGL(held_clear, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, x.tag, n);
     return hipGetLastError();
 }
@@ -877,7 +874,7 @@ static hipError_t launch_tiles_held(const hsadmm_plan_t* p, bool weighted, const
     const HeldTiles t{tag + 2 * n, tag + 3 * n, w.p.colpart};
     return for_replica_count<false>(R, [&](auto c) {
         constexpr int RC = decltype(c)::value;
-        const unsigned grid = (unsigned)p->items_theld.size() + kHeldCleaners;
+        const unsigned grid = (unsigned)p->items_theld.size();
         const WorkItem* items = p->d_items_theld;
         return weighted ? launch(p, kWKeys, tiles_held<RC, true>, grid, kBlock, s, items, w, R, x, t)
                         : launch(p, kPass1, tiles_held<RC, false>, grid, kBlock, s, items, w, R, x, t);
@@ -935,7 +932,7 @@ static int project_impl(const hsadmm_plan_t* p, const float* const* W_replicas, 
         if (held_args(p, p->items_held.size(), p->n_held, mask, out ? *out : CompactOut{}, ws, s, sel_out, x) != hipSuccess)
             return HSADMM_ERR_HIP;
         e = for_replica_count<true>(R, [&](auto c) {
-            return launch(p, kPass1, project_held<decltype(c)::value>, (unsigned)p->items_held.size() + kHeldCleaners, kBlock, s,
+            return launch(p, kPass1, project_held<decltype(c)::value>, (unsigned)p->items_held.size(), kBlock, s,
                           (const WorkItem*)p->d_items_held, a, (int)R, x);
         });
         return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;
@@ -1410,7 +1407,7 @@ static int project_weighted_impl(const hsadmm_plan_t* p, const float* const* W_r
             return HSADMM_ERR_HIP;
         const HeldWeighted hw{Zg, Vd, coef};
         e = for_replica_count<false>(R, [&](auto c) {
-            return launch(p, kWKeys, weighted_held<decltype(c)::value>, (unsigned)p->items_wheld.size() + kHeldCleaners, kBlock, s,
+            return launch(p, kWKeys, weighted_held<decltype(c)::value>, (unsigned)p->items_wheld.size(), kBlock, s,
                           (const WorkItem*)p->d_items_wheld, w, (int)R, x, hw);
         });
         return e == hipSuccess ? HSADMM_OK : HSADMM_ERR_HIP;

@@ -35,17 +35,14 @@ constexpr int kNotSelected = INT32_MIN;  // a group's rank before its layer's se
 // places, and such work may be waiting in the same way, so after this long the rows are written as they stand (either outcome
 // can be finished from that form) and the place is given up.
 constexpr long long kHeldPatience = 30000;
-constexpr int kHeldCleaners = 16;        // workgroups at the end of the grid that finish what was written too early
-constexpr long long kHeldCleanLimit = 400000000;   // ... give up themselves after four seconds: every wave comes to an end
 
 // WorkItem fields of a held row item: aux = index of the layer's first held item | items of the layer << 32; khw = chunks
 // (slots) of a thread per row.
 struct HeldArgs {
     unsigned long long* tag;        // per held item: gen once the item's keys are published
-    unsigned long long* state;      // per held item: gen + 1 when it is done, gen + 2 when it was written too early
-    unsigned long long gen;         // this call's number; neither it nor the two after it are any other call's, or a value
+    unsigned long long* state;      // per held item: who finishes its rows if they were written too early (held_left_early)
+    unsigned long long gen;         // this call's number; neither it nor the three after it are any other call's, or a value
                                     // that anything else writes there
-    int32_t* pred;                  // groups_total: the form of a row written too early (kKeptNoRank or -1)
     long long patience;             // ticks
     const DevLayer* layers;
     uint8_t* mask;
@@ -53,7 +50,12 @@ struct HeldArgs {
     CopyOut co;                     // the caller's layer_off / kept_idx (nulls: no compaction)
     float* packed;                  // null: no compaction
     int n_layers, pack_align;
-    int n_items, n_held;            // items of the launch, and how many of them are held (the first ones)
+};
+
+// What the threads of a workgroup tell each other about rows written too early.
+struct HeldTurn {
+    unsigned long long early[kWaves];
+    int mine;
 };
 
 // LDS: slots whose dual waits here.
@@ -63,6 +65,7 @@ struct HeldShared {
     TopkShared topk;
     double wsum[kHeldSlots][kWaves];
     int rank[kHeldRows];
+    HeldTurn turn;
 };
 
 // Called by the whole workgroup when all keys of the item's rows have been stored by put_agent.  Publishes the item and
@@ -143,6 +146,57 @@ __device__ __forceinline__ bool held_wait_groups(int g0, int n, const HeldArgs& 
     return __syncthreads_or(t < n && r == kNotSelected) == 0;
 }
 
+// Rows that were written before their selection was known.
+//
+// An item's state word says who finishes them.  It is changed by exchanges only: the item's workgroup leaves gen + 2 once its
+// rows lie in memory in their early form, the workgroup that has made the layer's selection leaves gen + 1 once the ranks lie
+// there.  Whoever finds the other's number came second and finishes the item; the selecting workgroup then marks it gen + 3.
+// Nobody waits for anybody, so there is nothing to give up, however long other work keeps a layer's last workgroups off the chip.
+__device__ __forceinline__ unsigned long long exchange_agent(unsigned long long* p, unsigned long long v)
+{
+    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Called by the whole workgroup when it has stored its rows in their early form.  True: it finishes them itself.
+__device__ __forceinline__ bool held_left_early(const HeldArgs& h, HeldTurn& turn)
+{
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) turn.mine = exchange_agent(&h.state[blockIdx.x], h.gen + 2) == h.gen + 1;
+    __syncthreads();
+    return turn.mine != 0;
+}
+
+// Called by a whole workgroup that has selected for the layer whose items are first .. first + n - 1, behind its own rows: the
+// rows that were written too early are finished (finish).  claim: the word that the layer's complete keys were told by (gen), as
+// two workgroups may both have found them complete.
+template <typename F>
+__device__ __forceinline__ void held_finish_early(const WorkItem* __restrict__ items, const HeldArgs& h, int first, int n,
+                                                  unsigned long long* claim, HeldTurn& turn, F finish)
+{
+    stores_arrived();                                            // the ranks
+    __syncthreads();
+    if (threadIdx.x == 0) turn.mine = exchange_agent(claim, h.gen + 1) == h.gen;
+    __syncthreads();
+    if (turn.mine == 0) return;
+    for (int k0 = 0; k0 < n; k0 += kBlock) {
+        const int k = k0 + (int)threadIdx.x;
+        const bool early = k < n && exchange_agent(&h.state[first + k], h.gen + 1) == h.gen + 2;
+        const unsigned long long b = __ballot(early);
+        if ((threadIdx.x & (kWave - 1)) == 0) turn.early[threadIdx.x / kWave] = b;
+        if (__syncthreads_or(early) == 0) continue;
+        if (early) put_agent(&h.state[first + k], h.gen + 3);
+        __threadfence();                                         // the rows as their workgroups left them
+        for (int w = 0; w < kWaves; ++w) {
+            unsigned long long m = turn.early[w];
+            unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)m), hi = __builtin_amdgcn_readfirstlane((unsigned int)(m >> 32));
+            for (m = ((unsigned long long)hi << 32) | lo; m != 0ull; m &= m - 1ull)
+                finish(items[first + k0 + w * kWave + __builtin_ctzll(m)]);
+        }
+        __syncthreads();                                         // (the masks may be written again)
+    }
+}
+
 // Where the slots of a thread lie in a row item; the last floats of a ragged row lie in the slot behind its words, one to a
 // lane.  WHOLE: no row has a tail (a choice made per slot would have loads wait for each other).
 template <bool WHOLE>
@@ -203,9 +257,46 @@ struct HeldPlaces {
     }
 };
 
+// The early form of a row: the kept one where most of the layer is kept, else the pruned one with the kept form's dual in Z.
+__device__ __forceinline__ bool held_early_kept(const DevLayer& L) { return 2 * L.k >= L.G; }
+
+// From its early to its final form.
+template <bool WHOLE>
+__device__ __forceinline__ void held_rows_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h)
+{
+    constexpr int B = 5;                                         // slots whose loads are in flight together
+    const HeldPlaces<WHOLE> at(it);
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    const bool kept_form = held_early_kept(h.layers[it.layer]);
+    float* const pk_layer = h.packed ? h.packed + it.packed_off : nullptr;
+    int q = 0, rd = 0;
+    for (int s0 = 0; s0 < at.nslot; s0 += B) {
+        v4f z[B], u[B];
+        int qb[B], rb[B], rank[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            qb[i] = q; rb[i] = s0 + i < at.nslot ? rd : it.nr;   // (no such row)
+            if (++q == at.cpr) { q = 0; ++rd; }
+            const int row = at.row(rb[i]);
+            rank[i] = row < it.nr ? get_agent(&h.im.pos[it.g0 + row]) : -1;
+            z[i] = at.fetch(a.Z, qb[i], rb[i]);
+            u[i] = kept_form ? zero4 : at.fetch(a.U, qb[i], rb[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const bool kept = rank[i] >= 0;
+            const v4f v = kept_form ? z[i] : u[i];               // the candidate
+            if (!kept) at.put(a.Z, qb[i], rb[i], zero4);
+            else if (!kept_form) at.put(a.Z, qb[i], rb[i], v);
+            if (kept != kept_form) at.put(a.U, qb[i], rb[i], z[i]);
+            if (kept && pk_layer) at.put_packed(pk_layer + (int64_t)rank[i] * it.row_len, qb[i], v);
+        }
+    }
+}
+
 // One FILTER row item.
 template <int R, bool WHOLE, typename SHARED>
-__device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h, SHARED& sh)
+__device__ __forceinline__ void held_rows(const WorkItem* __restrict__ items, const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h, SHARED& sh)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
@@ -286,14 +377,10 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
             put_agent(&a.key[it.g0 + threadIdx.x], s);
         }
     }
-    if (held_publish(it, h)) held_select(it, h, a.key, sh.topk);
+    const bool selects = held_publish(it, h);
+    if (selects) held_select(it, h, a.key, sh.topk);
     const bool known = held_wait_groups(it.g0, it.nr, h, sh.rank);
-    if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
-    const DevLayer& L = h.layers[it.layer];
-    const bool kept_default = 2 * L.k >= L.G;                    // written too early: in the likelier form
-    if (!known) {
-        if (threadIdx.x < it.nr) h.pred[it.g0 + threadIdx.x] = kept_default ? 0x7fffffff : -1;
-    }
+    const bool kept_default = held_early_kept(h.layers[it.layer]);
     float* const pk_layer = (h.packed && known) ? h.packed + it.packed_off : nullptr;
     int q = 0, rd = 0;
 #pragma unroll
@@ -312,10 +399,11 @@ __device__ __forceinline__ void held_rows(const WorkItem& it, const ProjectArgs&
             if (++q == at.cpr) { q = 0; ++rd; }
         }
     }
-    if (!known) {                                                // a cleaner reads the rows on another compute unit
-        __threadfence();
-        __syncthreads();
-        if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 2);
+    if (!known && held_left_early(h, sh.turn)) held_rows_finish<WHOLE>(it, a, h);
+    if (selects) {
+        const int first = (int)(it.aux & 0xffffffffll);
+        held_finish_early(items, h, first, (int)(it.aux >> 32), &h.tag[first], sh.turn,
+                          [&](const WorkItem& x) { held_rows_finish<WHOLE>(x, a, h); });   // (a layer's rows are of one length)
     }
 }
 
@@ -333,53 +421,11 @@ __device__ __forceinline__ void held_none_entries(const WorkItem& it, const Held
     }
 }
 
-__device__ __forceinline__ int held_row_group(const WorkItem& it, int t) { return t < it.nr ? it.g0 + t : -1; }
-
-// A workgroup behind all the items: waits until every item of its share is done, and takes those that were written before
-// their selection was known (none, unless other work held places that a layer's workgroups needed) from that form to their
-// final one (finish).  Its waits end because no workgroup that it waits for waits without end.
-// group(item, t): the group whose rank thread t waits for before that (-1: none).
-template <typename G, typename F>
-__device__ __forceinline__ void held_clean(const WorkItem* __restrict__ items, const HeldArgs& h, G group, F finish)
-{
-    const int n_held = h.n_held;
-    const int c = (int)blockIdx.x - h.n_items;
-    const long long until = (long long)__builtin_amdgcn_s_memrealtime() + kHeldCleanLimit;
-    for (int i0 = c; i0 < n_held; i0 += kHeldCleaners * kBlock) {
-        const int i = i0 + (int)threadIdx.x * kHeldCleaners;
-        unsigned long long st = h.gen + 1;
-        while (i < n_held) {
-            st = get_agent(&h.state[i]);
-            if (st == h.gen + 1 || st == h.gen + 2 || (long long)__builtin_amdgcn_s_memrealtime() > until) break;
-            __builtin_amdgcn_s_sleep(16);
-        }
-        if (__syncthreads_or(st == h.gen + 2) == 0) continue;
-        for (int t = 0; t < kBlock; ++t) {
-            const int k = i0 + t * kHeldCleaners;
-            if (k >= n_held) break;
-            if (get_agent(&h.state[k]) != h.gen + 2) continue;
-            const WorkItem it = items[k];
-            if (const int g = group(it, (int)threadIdx.x); g >= 0)
-                while (get_agent(&h.im.pos[g]) == kNotSelected && (long long)__builtin_amdgcn_s_memrealtime() <= until)
-                    __builtin_amdgcn_s_sleep(16);
-            __syncthreads();
-            __threadfence();                                     // the item's rows as its workgroup left them
-            finish(it);
-        }
-    }
-}
-
 template <int R>
 __global__ __launch_bounds__(kBlock, kHeldPerUnit) void project_held(const WorkItem* __restrict__ items, ProjectArgs a, int Rrt,
                                                           HeldArgs h)
 {
     __shared__ HeldShared<kHeldLdsSlots> sh;
-    if ((int)blockIdx.x >= h.n_items) {
-        held_clean(items, h, held_row_group, [&](const WorkItem& it) {
-            hinted_repair_rows<1>(it, a, 1, h.pred, h.im.pos, true, h.packed ? h.packed + it.packed_off : nullptr);
-        });
-        return;
-    }
     const WorkItem it = items[blockIdx.x];
     if (it.row0 == 0 && threadIdx.x == 0) held_layer_entries(it, h);
     if (item_mode(it) == HSADMM_MODE_NONE) {                     // final at once
@@ -387,8 +433,8 @@ __global__ __launch_bounds__(kBlock, kHeldPerUnit) void project_held(const WorkI
         held_none_entries(it, h);
         project_rows_hinted<R, R != 8>(it, a, Rrt, hint);        // (one chunk at a time with eight replicas: no registers to spare)
     } else {
-        if (item_vec(it)) held_rows<R, true>(it, a, Rrt, h, sh);
-        else held_rows<R, false>(it, a, Rrt, h, sh);
+        if (item_vec(it)) held_rows<R, true>(items, it, a, Rrt, h, sh);
+        else held_rows<R, false>(items, it, a, Rrt, h, sh);
     }
 }
 
@@ -410,10 +456,48 @@ constexpr int kHeldWeightedPerUnit = 3;
 constexpr int kHeldWeightedLds = kHeldSlots;
 constexpr int held_weighted_batch(int R) { return R == 8 ? 1 : 2; }
 
+// From the early form, t in Z and the dual of a kept row in U, to the final one.
+template <bool WHOLE>
+__device__ __forceinline__ void held_weighted_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h,
+                                                     const HeldWeighted& x)
+{
+    constexpr int B = 5;                                         // slots whose loads are in flight together
+    const HeldPlaces<WHOLE> at(it);
+    const float al = x.coef[2 * it.layer], bl = x.coef[2 * it.layer + 1];
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    float* const pk_layer = h.packed ? h.packed + it.packed_off : nullptr;
+    int q = 0, rd = 0;
+    for (int s0 = 0; s0 < at.nslot; s0 += B) {
+        v4f t[B], zg[B], vd[B];
+        int qb[B], rb[B], rank[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            qb[i] = q; rb[i] = s0 + i < at.nslot ? rd : it.nr;   // (no such row)
+            if (++q == at.cpr) { q = 0; ++rd; }
+            const int row = at.row(rb[i]);
+            rank[i] = row < it.nr ? get_agent(&h.im.pos[it.g0 + row]) : -1;
+            t[i] = at.fetch(a.Z, qb[i], rb[i]);
+            zg[i] = at.fetch(x.Zg, qb[i], rb[i]);
+            vd[i] = at.fetch(x.Vd, qb[i], rb[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const bool kept = rank[i] >= 0;
+            const v4f qd = zg[i] - vd[i];
+            const v4f att = t[i] * al;
+            const v4f bq = qd * bl;
+            const v4f zt = att + bq;
+            at.put(a.Z, qb[i], rb[i], kept ? zt : zero4);
+            if (!kept) at.put(a.U, qb[i], rb[i], t[i]);
+            else if (pk_layer) at.put_packed(pk_layer + (int64_t)rank[i] * it.row_len, qb[i], zt + vd[i]);
+        }
+    }
+}
+
 // One FILTER row item: held_rows with the candidate z~ = fl(fl(a t) + fl(b (z - v))), t = Wbar + U.  z~ and t wait in
 // registers, the dual of a kept row in LDS; what is packed is z~ + v, v read again.
 template <int R, bool WHOLE, typename SHARED>
-__device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
+__device__ __forceinline__ void held_weighted_rows(const WorkItem* __restrict__ items, const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
                                                    const HeldWeighted& x, SHARED& sh)
 {
     const int RR = R > 0 ? R : Rrt;
@@ -498,9 +582,9 @@ __device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const Pro
             put_agent(&a.key[it.g0 + threadIdx.x], s);
         }
     }
-    if (held_publish(it, h)) held_select(it, h, a.key, sh.topk);
+    const bool selects = held_publish(it, h);
+    if (selects) held_select(it, h, a.key, sh.topk);
     const bool known = held_wait_groups(it.g0, it.nr, h, sh.rank);
-    if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
     float* const pk_layer = (h.packed && known) ? h.packed + it.packed_off : nullptr;
     {
         constexpr int B = 5;
@@ -532,41 +616,11 @@ __device__ __forceinline__ void held_weighted_rows(const WorkItem& it, const Pro
             }
         }
     }
-    if (!known) {                                                // a cleaner reads the rows on another compute unit
-        __threadfence();
-        __syncthreads();
-        if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 2);
-    }
-}
-
-// weighted_fixup_rows by a cleaner: the item's ranks and rows as other workgroups of this launch left them.
-template <bool WHOLE>
-__device__ __forceinline__ void held_weighted_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h,
-                                                     const HeldWeighted& x)
-{
-    const HeldPlaces<WHOLE> at(it);
-    const float al = x.coef[2 * it.layer], bl = x.coef[2 * it.layer + 1];
-    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
-    int q = 0, rd = 0;
-    for (int s = 0; s < at.nslot; ++s) {
-        const int row = at.row(rd);
-        if (row < it.nr) {
-            const int rank = get_agent(&h.im.pos[it.g0 + row]);
-            const v4f t = at.fetch(a.Z, q, rd);
-            if (rank >= 0) {
-                const v4f vd = at.fetch(x.Vd, q, rd);
-                const v4f qd = at.fetch(x.Zg, q, rd) - vd;
-                const v4f att = t * al;
-                const v4f bq = qd * bl;
-                const v4f zt = att + bq;
-                at.put(a.Z, q, rd, zt);
-                if (h.packed) at.put_packed(h.packed + it.packed_off + (int64_t)rank * it.row_len, q, zt + vd);
-            } else {
-                at.put(a.U, q, rd, t);
-                at.put(a.Z, q, rd, zero4);
-            }
-        }
-        if (++q == at.cpr) { q = 0; ++rd; }
+    if (!known && held_left_early(h, sh.turn)) held_weighted_finish<WHOLE>(it, a, h, x);
+    if (selects) {
+        const int first = (int)(it.aux & 0xffffffffll);
+        held_finish_early(items, h, first, (int)(it.aux >> 32), &h.tag[first], sh.turn,
+                          [&](const WorkItem& y) { held_weighted_finish<WHOLE>(y, a, h, x); });
     }
 }
 
@@ -575,13 +629,6 @@ __global__ __launch_bounds__(kBlock, kHeldWeightedPerUnit) void weighted_held(co
                                                                               int Rrt, HeldArgs h, HeldWeighted x)
 {
     __shared__ HeldShared<kHeldWeightedLds> sh;
-    if ((int)blockIdx.x >= h.n_items) {
-        held_clean(items, h, held_row_group, [&](const WorkItem& it) {
-            if (item_vec(it)) held_weighted_finish<true>(it, w.p, h, x);
-            else held_weighted_finish<false>(it, w.p, h, x);
-        });
-        return;
-    }
     const WorkItem it = items[blockIdx.x];
     if (it.row0 == 0 && threadIdx.x == 0) held_layer_entries(it, h);
     if (item_mode(it) == HSADMM_MODE_NONE) {
@@ -589,8 +636,8 @@ __global__ __launch_bounds__(kBlock, kHeldWeightedPerUnit) void weighted_held(co
         held_none_entries(it, h);
         weighted_rows_hinted<R, false>(it, w, Rrt, hint);
     } else {
-        if (item_vec(it)) held_weighted_rows<R, true>(it, w.p, Rrt, h, x, sh);
-        else held_weighted_rows<R, false>(it, w.p, Rrt, h, x, sh);
+        if (item_vec(it)) held_weighted_rows<R, true>(items, it, w.p, Rrt, h, x, sh);
+        else held_weighted_rows<R, false>(items, it, w.p, Rrt, h, x, sh);
     }
 }
 
@@ -624,16 +671,18 @@ struct HeldTileShared {
     double part[kWaves][kWave * 4];
     int rank[kBlock];
     int claimed;
+    HeldTurn turn;
 };
 
 __device__ __forceinline__ int tile_strip_cols(const WorkItem& it) { return kWave * (item_vec(it) ? 4 : 1); }
+__device__ __forceinline__ int tile_strips(const WorkItem& it) { return (it.row_len + tile_strip_cols(it) - 1) / tile_strip_cols(it); }
 
 // Called by the whole workgroup when its column sums have been stored by put_agent.  True: all column sums of the layer are
 // complete, in the first row block's place.
 __device__ __forceinline__ bool held_tile_publish(const WorkItem& it, const HeldArgs& h, const HeldTiles& x, HeldTileShared& sh)
 {
     const int cols = tile_strip_cols(it);
-    const int n_strips = (it.row_len + cols - 1) / cols;
+    const int n_strips = tile_strips(it);
     const int n_rb = h.layers[it.layer].n_rowblocks;
     const int strip = it.col0 / cols;
     const int first = it.lpr;
@@ -704,9 +753,42 @@ __device__ __forceinline__ void held_tile_select(const WorkItem& it, const HeldA
     held_select(it, h, key, sh.topk);
 }
 
+// A tile that was written before its selection was known: a thread takes a column.
+template <bool WEIGHTED>
+__device__ __forceinline__ void held_tile_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h)
+{
+    const int col = it.col0 + (int)threadIdx.x;
+    if ((int)threadIdx.x >= tile_strip_cols(it) || col >= it.row_len) return;
+    const DivKhw div(it.khw);
+    const int ch = div(col);
+    const int rank = get_agent(&h.im.pos[it.g0 + ch]);
+    const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
+    const int64_t packed_row_len = (int64_t)it.k * it.khw;
+    for (int rr = 0; rr < it.nr; ++rr) {
+        const int64_t e = it.base + (int64_t)rr * it.row_len + col;
+        float z = ld1(a.Z + e);
+        if (rank < 0) {
+            st1(a.U + e, z);
+            st1(a.Z + e, 0.f);
+            continue;
+        }
+        float vd = 0.f;
+        if (WEIGHTED) {
+            vd = ld1(a.Vd + e);
+            const float q = ld1(a.Zg + e) - vd;
+            const float at = z * al;
+            const float bq = q * bl;
+            z = at + bq;
+            st1(a.Z + e, z);
+        }
+        if (h.packed)
+            h.packed[it.packed_off + (it.row0 + rr) * packed_row_len + (int64_t)rank * it.khw + (col - ch * it.khw)] = WEIGHTED ? z + vd : z;
+    }
+}
+
 // VEC: rows of whole words (four columns a lane, else one); a choice within the loop would make loads wait for each other.
 template <int R, bool WEIGHTED, bool VEC>
-__device__ __forceinline__ void held_tile(const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
+__device__ __forceinline__ void held_tile(const WorkItem* __restrict__ items, const WorkItem& it, const ProjectArgs& a, int Rrt, const HeldArgs& h,
                                           const HeldTiles& x, HeldTileShared& sh)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -805,9 +887,9 @@ __device__ __forceinline__ void held_tile(const WorkItem& it, const ProjectArgs&
         for (int w = 1; w < kWaves; ++w) s += sh.part[w][k];
         put_agent(&x.colpart[it.aux + it.col0 + threadIdx.x], s);
     }
-    if (held_tile_publish(it, h, x, sh)) held_tile_select(it, h, x, a.key, sh);
+    const bool selects = held_tile_publish(it, h, x, sh);
+    if (selects) held_tile_select(it, h, x, a.key, sh);
     const bool known = held_wait_groups(it.g0 + ch0, n_ch, h, sh.rank);
-    if (known && threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 1);   // (no one reads the rows in this launch)
     bool kept[4] = {true, true, true, true};
     int pc[4] = {-1, -1, -1, -1};                // packed column, -1: not packed
     if (known && in) {
@@ -855,44 +937,10 @@ __device__ __forceinline__ void held_tile(const WorkItem& it, const ProjectArgs&
                 }
             }
         }
-    if (!known) {                                                // a cleaner reads the rows on another compute unit
-        __threadfence();
-        __syncthreads();
-        if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen + 2);
-    }
-}
-
-// A tile that was written before its selection was known: a thread takes a column.
-template <bool WEIGHTED>
-__device__ __forceinline__ void held_tile_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h)
-{
-    const int col = it.col0 + (int)threadIdx.x;
-    if ((int)threadIdx.x >= tile_strip_cols(it) || col >= it.row_len) return;
-    const DivKhw div(it.khw);
-    const int ch = div(col);
-    const int rank = get_agent(&h.im.pos[it.g0 + ch]);
-    const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
-    const int64_t packed_row_len = (int64_t)it.k * it.khw;
-    for (int rr = 0; rr < it.nr; ++rr) {
-        const int64_t e = it.base + (int64_t)rr * it.row_len + col;
-        float z = ld1(a.Z + e);
-        if (rank < 0) {
-            st1(a.U + e, z);
-            st1(a.Z + e, 0.f);
-            continue;
-        }
-        float vd = 0.f;
-        if (WEIGHTED) {
-            vd = ld1(a.Vd + e);
-            const float q = ld1(a.Zg + e) - vd;
-            const float at = z * al;
-            const float bq = q * bl;
-            z = at + bq;
-            st1(a.Z + e, z);
-        }
-        if (h.packed)
-            h.packed[it.packed_off + (it.row0 + rr) * packed_row_len + (int64_t)rank * it.khw + (col - ch * it.khw)] = WEIGHTED ? z + vd : z;
-    }
+    if (!known && held_left_early(h, sh.turn)) held_tile_finish<WEIGHTED>(it, a, h);
+    if (selects)
+        held_finish_early(items, h, it.lpr, tile_strips(it) * h.layers[it.layer].n_rowblocks, &x.strip_tag[it.lpr], sh.turn,
+                          [&](const WorkItem& y) { held_tile_finish<WEIGHTED>(y, a, h); });
 }
 
 template <int R, bool WEIGHTED>
@@ -900,14 +948,6 @@ __global__ __launch_bounds__(kBlock, held_tile_per_unit(R, WEIGHTED)) void tiles
                                                                                    int Rrt, HeldArgs h, HeldTiles x)
 {
     __shared__ HeldTileShared sh;
-    if ((int)blockIdx.x >= h.n_items) {
-        held_clean(items, h, [&](const WorkItem& it, int t) {
-            const DivKhw div(it.khw);
-            const int ch0 = div(it.col0), last = min(it.row_len, it.col0 + tile_strip_cols(it)) - 1;
-            return ch0 + t <= div(last) ? it.g0 + ch0 + t : -1;
-        }, [&](const WorkItem& it) { held_tile_finish<WEIGHTED>(it, w.p, h); });
-        return;
-    }
     const WorkItem it = items[blockIdx.x];
     if (it.row0 == 0 && it.col0 == 0 && threadIdx.x == 0) held_layer_entries(it, h);
     if (item_mode(it) == HSADMM_MODE_NONE) {                     // final at once
@@ -920,8 +960,8 @@ __global__ __launch_bounds__(kBlock, held_tile_per_unit(R, WEIGHTED)) void tiles
             project_rows_hinted<R>(it, w.p, Rrt, hint);
         }
     } else {
-        if (item_vec(it)) held_tile<R, WEIGHTED, true>(it, w.p, Rrt, h, x, sh);
-        else held_tile<R, WEIGHTED, false>(it, w.p, Rrt, h, x, sh);
+        if (item_vec(it)) held_tile<R, WEIGHTED, true>(items, it, w.p, Rrt, h, x, sh);
+        else held_tile<R, WEIGHTED, false>(items, it, w.p, Rrt, h, x, sh);
     }
 }
 

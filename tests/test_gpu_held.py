@@ -45,6 +45,50 @@ def _launches(plan, call):
     return got
 
 
+def _early(ws):
+    """Items that the last call wrote before their selection was known: their state words are its number (a negative NaN's
+    pattern, a multiple of four) and 2 or 3."""
+    words = ws.cpu().numpy()[:ws.numel() // 8 * 8].view(np.uint64)
+    return int(np.count_nonzero(((words >> np.uint64(50)) == 0x3FFD) & ((words & np.uint64(3)) >= 2)))
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["step", "weighted"])
+@pytest.mark.parametrize("mode", [F, C], ids=["filter", "channel"])
+@pytest.mark.parametrize("keep", [0.3, 0.7])
+def test_rows_written_early_are_finished_by_whoever_comes_second(mode, keep, weighted, monkeypatch):
+    """Without patience rows are written before their selection is known, in either early form, and finished by their own
+    workgroup or by the one that has selected.  The launch has one workgroup an item: none that waits on behalf of others,
+    and could give up."""
+    from tests.gpu_harness import GpuRun, check_against_oracle
+    from tests.test_gpu_weighted import _phase4_chain
+    for name in ("HSADMM_NO_ESTIMATE", "HSADMM_FORCE_ESTIMATE"):
+        monkeypatch.delenv(name, raising=False)
+    monkeypatch.setenv("HSADMM_HELD_PATIENCE", "0")
+    wl = wk.custom_workload([(128, 64, 9, mode, int(keep * (128 if mode == F else 64)))], R=4, seed=12, sigma_replica=0.03)
+    W, U = wk.generate(wl)
+    t = wl.table()
+    r = GpuRun(wl, W, U)
+    pkg.hsadmm_kernel_timing_enable(r.plan, True)
+    if weighted:
+        rng = np.random.default_rng(5)
+        _phase4_chain(wl, W, U, np.float32([0.6]), np.float32([0.3]), rng, fused_dual=True, one_call=True)
+        dev = r.dev
+        Zg, Vd = (torch.from_numpy(rng.standard_normal(wl.n_arena).astype(np.float32)).to(dev) for _ in range(2))
+        pkg.hsadmm_project_weighted_compact(r.plan, r.dW, r.dU, Zg, Vd, r.dZ, None, r.dmask, None, r.dpacked, r.doff, r.dkept,
+                                            r.ws)
+    else:
+        ref = oracle.project(t, W, U, want_wbar=True)
+        r.step(fused=True)
+        rep = check_against_oracle(wl, r.outputs(), ref, oracle.compact(t, ref["Z"], ref["mask"]))
+        assert all(v == 0 for v in rep.values()), rep
+    torch.cuda.synchronize()
+    assert _early(r.ws) >= 1
+    grid = pkg.hsadmm_kernel_grids(r.plan)["weighted_pass1" if weighted else "project_pass1"]
+    # rows of 144 chunks share a wave: four at once, one slot's worth an item; tiles of 64 rows by 256 columns
+    assert grid == (32 if mode == F else 6)
+    r.close()
+
+
 @pytest.mark.parametrize("R", [1, 2, 3, 4, 5, 8])
 def test_edges_of_what_a_workgroup_holds(R, patience):
     from tests.gpu_harness import GpuRun
