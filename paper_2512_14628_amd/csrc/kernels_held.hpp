@@ -753,36 +753,79 @@ __device__ __forceinline__ void held_tile_select(const WorkItem& it, const HeldA
     held_select(it, h, key, sh.topk);
 }
 
-// A tile that was written before its selection was known: a thread takes a column.
-template <bool WEIGHTED>
+// A tile that was written before its selection was known, from that form to its final one: the lanes and rows of held_tile, four
+// of a wave's rows in flight.
+template <bool WEIGHTED, bool VEC>
 __device__ __forceinline__ void held_tile_finish(const WorkItem& it, const ProjectArgs& a, const HeldArgs& h)
 {
-    const int col = it.col0 + (int)threadIdx.x;
-    if ((int)threadIdx.x >= tile_strip_cols(it) || col >= it.row_len) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int row_len = it.row_len;
+    constexpr int vw = VEC ? 4 : 1, B = 4;
+    const int col = it.col0 + lane * vw;
+    if (col >= row_len) return;
     const DivKhw div(it.khw);
-    const int ch = div(col);
-    const int rank = get_agent(&h.im.pos[it.g0 + ch]);
     const float al = WEIGHTED ? a.coef[2 * it.layer] : 1.f, bl = WEIGHTED ? a.coef[2 * it.layer + 1] : 0.f;
+    const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+    bool kept[4] = {true, true, true, true};
+    int pc[4] = {-1, -1, -1, -1};                // packed column, -1: not packed
+#pragma unroll
+    for (int i = 0; i < vw; ++i) {
+        const int ch = div(col + i);
+        const int r = get_agent(&h.im.pos[it.g0 + ch]);
+        kept[i] = r >= 0;
+        if (h.packed && r >= 0) pc[i] = r * it.khw + (col + i - ch * it.khw);
+    }
+    auto fetch = [&](const float* p, int rr) -> v4f {
+        v4f v = zero4;
+        if (rr < it.nr) {
+            if (VEC) v = ld4(p + it.base + (int64_t)rr * row_len + col);
+            else v.x = ld1(p + it.base + (int64_t)rr * row_len + col);
+        }
+        return v;
+    };
+    auto put = [&](float* p, int rr, const v4f& v) {
+        if (rr >= it.nr) return;
+        if (VEC) st4(p + it.base + (int64_t)rr * row_len + col, v);
+        else st1(p + it.base + (int64_t)rr * row_len + col, v.x);
+    };
     const int64_t packed_row_len = (int64_t)it.k * it.khw;
-    for (int rr = 0; rr < it.nr; ++rr) {
-        const int64_t e = it.base + (int64_t)rr * it.row_len + col;
-        float z = ld1(a.Z + e);
-        if (rank < 0) {
-            st1(a.U + e, z);
-            st1(a.Z + e, 0.f);
-            continue;
+    for (int r0 = wave; r0 < it.nr; r0 += B * kWaves) {
+        v4f p[B], d[B], zg[B], vd[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            p[i] = fetch(a.Z, r0 + i * kWaves);                  // the dual of a pruned element
+            d[i] = fetch(a.U, r0 + i * kWaves);                  // ... of a kept one
+            if (WEIGHTED) {
+                zg[i] = fetch(a.Zg, r0 + i * kWaves);
+                vd[i] = fetch(a.Vd, r0 + i * kWaves);
+            }
         }
-        float vd = 0.f;
-        if (WEIGHTED) {
-            vd = ld1(a.Vd + e);
-            const float q = ld1(a.Zg + e) - vd;
-            const float at = z * al;
-            const float bq = q * bl;
-            z = at + bq;
-            st1(a.Z + e, z);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int rr = r0 + i * kWaves;
+            v4f c = p[i];
+            if (WEIGHTED) {
+                const v4f q = zg[i] - vd[i];
+                const v4f at = p[i] * al;
+                const v4f bq = q * bl;
+                c = at + bq;
+            }
+            v4f z, u;
+            z.x = kept[0] ? c.x : 0.f; z.y = kept[1] ? c.y : 0.f; z.z = kept[2] ? c.z : 0.f; z.w = kept[3] ? c.w : 0.f;
+            u.x = kept[0] ? d[i].x : p[i].x; u.y = kept[1] ? d[i].y : p[i].y;
+            u.z = kept[2] ? d[i].z : p[i].z; u.w = kept[3] ? d[i].w : p[i].w;
+            put(a.Z, rr, z);
+            put(a.U, rr, u);
+            if (h.packed && rr < it.nr) {
+                float* row = h.packed + it.packed_off + (it.row0 + rr) * packed_row_len;
+                const v4f y = WEIGHTED ? z + vd[i] : z;
+                if (pc[0] >= 0) row[pc[0]] = y.x;
+                if (pc[1] >= 0) row[pc[1]] = y.y;
+                if (pc[2] >= 0) row[pc[2]] = y.z;
+                if (pc[3] >= 0) row[pc[3]] = y.w;
+            }
         }
-        if (h.packed)
-            h.packed[it.packed_off + (it.row0 + rr) * packed_row_len + (int64_t)rank * it.khw + (col - ch * it.khw)] = WEIGHTED ? z + vd : z;
     }
 }
 
@@ -937,10 +980,10 @@ __device__ __forceinline__ void held_tile(const WorkItem* __restrict__ items, co
                 }
             }
         }
-    if (!known && held_left_early(h, sh.turn)) held_tile_finish<WEIGHTED>(it, a, h);
+    if (!known && held_left_early(h, sh.turn)) held_tile_finish<WEIGHTED, VEC>(it, a, h);
     if (selects)
         held_finish_early(items, h, it.lpr, tile_strips(it) * h.layers[it.layer].n_rowblocks, &x.strip_tag[it.lpr], sh.turn,
-                          [&](const WorkItem& y) { held_tile_finish<WEIGHTED>(y, a, h); });
+                          [&](const WorkItem& y) { held_tile_finish<WEIGHTED, VEC>(y, a, h); });
 }
 
 template <int R, bool WEIGHTED>
