@@ -523,6 +523,18 @@ int lay_out(hsadmm_plan* p, const hsadmm_layer_t* layers, const hsadmm_nest_t* n
     return HSADMM_OK;
 }
 
+// Workgroups of a held kernel on a compute unit at once: what its registers are bounded for, or fewer if its LDS is too much for
+// that (it is given out in pieces of 1280 bytes, and a kernel has more than its own structure: a layer that counts on places
+// which are not there waits out its patience on every call).
+int held_per_unit(const void* kernel, int per_unit)
+{
+    constexpr int kLdsPiece = 1280;
+    hipFuncAttributes attr{};
+    if (hipFuncGetAttributes(&attr, kernel) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    const int pieces = std::max(1, ((int)attr.sharedSizeBytes + kLdsPiece - 1) / kLdsPiece);
+    return std::min(per_unit, (int)kLdsPerUnit / kLdsPiece / pieces);
+}
+
 // The held row items (kernels_held.hpp), if the plan's rows can wait for their selection on the chip: FILTER and
 // unconstrained layers only, rows of at most kHeldSlots chunks per lane, and every layer's items on the chip at once
 // with a quarter of the places to spare, as a layer that takes them all leaves no one to load while it waits.  Without /
@@ -590,7 +602,7 @@ constexpr int kHeldTilesWeighted8 = 80;
 // The held tiles (kernels_held.hpp), for plans of CHANNEL and unconstrained layers without runs of channels, every layer's
 // tiles on the chip at once with a quarter of the places to spare, three quarters of all tiles of whole words (a ragged
 // one holds a quarter of the elements).
-void lay_out_held_tiles(hsadmm_plan* p, int compute_units)
+void lay_out_held_tiles(hsadmm_plan* p, int64_t places, int64_t places_two)
 {
     std::vector<WorkItem> items;
     int64_t largest = 0, narrow = 0;
@@ -605,11 +617,11 @@ void lay_out_held_tiles(hsadmm_plan* p, int compute_units)
         if (d.row_len % 4 != 0) narrow += (int64_t)(items.size() - first);
     }
     if (items.empty()) return;
-    const auto fits = [&](int per_unit) { return largest <= (int64_t)per_unit * compute_units * 3 / 4; };
+    const auto fits = [&](int64_t n) { return largest <= n * 3 / 4; };
     // (a tag, a state, a strip's tag and its claim for every tile take the place of the residual sums' partials)
-    if (!fits(held_tile_per_unit(1, false)) || narrow * 4 > (int64_t)items.size() || items.size() > p->items_rows.size()) return;
+    if (!fits(places) || narrow * 4 > (int64_t)items.size() || items.size() > p->items_rows.size()) return;
     p->n_theld = (int32_t)items.size();
-    p->theld_two = fits(held_tile_per_unit(1, true));
+    p->theld_two = fits(places_two);
     p->items_theld = std::move(items);
     p->items_theld.insert(p->items_theld.end(), p->items_none.begin(), p->items_none.end());
 }
@@ -708,9 +720,11 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
             hipGetDevice(&p->device) == hipSuccess &&
             hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess)
         {
-            lay_out_held(p, (int64_t)kHeldPerUnit * compute_units, p->items_held, p->n_held);
-            lay_out_held(p, (int64_t)kHeldWeightedPerUnit * compute_units, p->items_wheld, p->n_wheld);
-            lay_out_held_tiles(p, compute_units);
+            const auto places = [&](const void* kernel, int per_unit) { return (int64_t)compute_units * held_per_unit(kernel, per_unit); };
+            lay_out_held(p, places((const void*)project_held<0>, kHeldPerUnit), p->items_held, p->n_held);
+            lay_out_held(p, places((const void*)weighted_held<0>, kHeldWeightedPerUnit), p->items_wheld, p->n_wheld);
+            lay_out_held_tiles(p, places((const void*)tiles_held<0, false>, held_tile_per_unit(0, false)),
+                               places((const void*)tiles_held<0, true>, held_tile_per_unit(0, true)));
         }
         // (environment, read here once per plan: HSADMM_HELD_PATIENCE, ticks of 10 ns, is how the tests have rows written
         // before their selection is known)

@@ -665,11 +665,17 @@ struct HeldTiles {
     double* colpart;
 };
 
+// The waves' column sums are through before the selection begins, so they share its place: LDS is given out in pieces of 1280
+// bytes, and a workgroup with both took 43 of the 128 pieces a unit has.
 struct HeldTileShared {
     v4f dual[kHeldTileLds][kBlock];
-    TopkShared topk;
-    double part[kWaves][kWave * 4];
-    int rank[kBlock];
+    union {
+        double part[kWaves][kWave * 4];
+        struct {
+            TopkShared topk;
+            int rank[kBlock];
+        } sel;
+    };
     int claimed;
     HeldTurn turn;
 };
@@ -750,7 +756,7 @@ __device__ __forceinline__ void held_tile_select(const WorkItem& it, const HeldA
     }
     stores_arrived();
     __syncthreads();
-    held_select(it, h, key, sh.topk);
+    held_select(it, h, key, sh.sel.topk);
 }
 
 // A tile that was written before its selection was known, from that form to its final one: the lanes and rows of held_tile, four
@@ -932,7 +938,7 @@ __device__ __forceinline__ void held_tile(const WorkItem* __restrict__ items, co
     }
     const bool selects = held_tile_publish(it, h, x, sh);
     if (selects) held_tile_select(it, h, x, a.key, sh);
-    const bool known = held_wait_groups(it.g0 + ch0, n_ch, h, sh.rank);
+    const bool known = held_wait_groups(it.g0 + ch0, n_ch, h, sh.sel.rank);
     bool kept[4] = {true, true, true, true};
     int pc[4] = {-1, -1, -1, -1};                // packed column, -1: not packed
     if (known && in) {
@@ -940,7 +946,7 @@ __device__ __forceinline__ void held_tile(const WorkItem* __restrict__ items, co
         for (int i = 0; i < 4; ++i)
             if (i < vw) {
                 const int ch = div(col + i);
-                const int r = sh.rank[ch - ch0];
+                const int r = sh.sel.rank[ch - ch0];
                 kept[i] = r >= 0;
                 if (h.packed && r >= 0) pc[i] = r * khw + (col + i - ch * khw);
             }

@@ -255,3 +255,20 @@ def test_two_streams_at_once(patience):
                 sl = slice(l.elem_off, l.elem_off + l.n)
                 assert np.array_equal(g[sl].view(np.uint32), want[sl].view(np.uint32)), l.name
     plan.close()
+
+
+@pytest.mark.parametrize("shape", [(1024, 1024, 9, C, 400), (768, 10240, 1, F, 300)], ids=["tiles", "rows"])
+def test_the_largest_layers_find_their_places(shape, monkeypatch):
+    """Layers of as many items as a plan may count on (three quarters of the places): alone on the device none of them waits
+    in vain."""
+    from tests.gpu_harness import GpuRun
+    for name in ("HSADMM_NO_ESTIMATE", "HSADMM_FORCE_ESTIMATE", "HSADMM_HELD_PATIENCE"):
+        monkeypatch.delenv(name, raising=False)
+    wl = wk.custom_workload([shape], R=2, seed=4, sigma_replica=0.03)
+    W, U = wk.generate(wl, threads=8)
+    ref = oracle.project(wl.table(), W, U)
+    r = GpuRun(wl, W, U, want_wbar=False)
+    assert _launches(r.plan, r.project_compact) == {"project_pass1": 1}
+    assert _early(r.ws) == 0
+    assert np.array_equal(r.dmask.cpu().numpy(), ref["mask"])
+    r.close()
