@@ -535,6 +535,25 @@ int held_per_unit(const void* kernel, int per_unit)
     return std::min(per_unit, (int)kLdsPerUnit / kLdsPiece / pieces);
 }
 
+// Whether every layer's selection is quick enough to be made by a workgroup of 256 threads with its own rows in its registers.  Keys
+// stay in registers up to kTopkRegs a thread; a group beyond that costs about 4 ns more than in a selection of 1024 threads, which
+// 4096 held elements give back (ResNet-50, 25 M elements: 23 us).  Without / with, us, 2 replicas, eight layers of 128 x 576 or 64 x 1152 and
+// one of 64 floats a group: 2048 filters 15.7 / 14.9, 2304 15.4 / 20.7, 4096 16.9 / 26.3, 8192 22.3 / 43.7; channels 26.1 / 26.4,
+// 26.6 / 32.2, 29.3 / 41.0, 38.2 / 63.9; bottleneck 3-4-6-3 of width 80 (2560 groups, 39 M elements), 1 and 4 replicas: filters
+// 188 / 179, 268 / 255, channels 214 / 185, 351 / 276.  At 16384 groups it takes a third of the rows' patience.
+constexpr int kHeldGroups = 16384;
+bool selects_in_time(const std::vector<DevLayer>& layers)
+{
+    int64_t n = 0, largest = 0;
+    for (const DevLayer& d : layers)
+        if (d.mode != HSADMM_MODE_NONE) {
+            n += (int64_t)d.c_out * d.row_len;
+            largest = std::max(largest, (int64_t)d.G);
+        }
+    const int64_t beyond = largest - kTopkRegs * kBlock;
+    return beyond <= 0 || (largest <= kHeldGroups && beyond <= n / 4096);
+}
+
 // The held row items (kernels_held.hpp), if the plan's rows can wait for their selection on the chip: FILTER and
 // unconstrained layers only, rows of at most kHeldSlots chunks per lane, and every layer's items on the chip at once
 // with a quarter of the places to spare, as a layer that takes them all leaves no one to load while it waits.  Without /
@@ -550,7 +569,7 @@ void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& o
         if (mode_has_channels_host(d.mode)) return;
         any_filter = any_filter || d.mode == HSADMM_MODE_FILTER;
     }
-    if (!any_filter) return;
+    if (!any_filter || !selects_in_time(p->dev_layers)) return;
     // the fewest slots with which the whole plan is on the chip at once, or, if it never is, all of them
     for (int want = 1; want <= kHeldSlots; ++want) {
         std::vector<WorkItem> items;
@@ -616,7 +635,7 @@ void lay_out_held_tiles(hsadmm_plan* p, int64_t places, int64_t places_two)
         largest = std::max(largest, (int64_t)(items.size() - first));
         if (d.row_len % 4 != 0) narrow += (int64_t)(items.size() - first);
     }
-    if (items.empty()) return;
+    if (items.empty() || !selects_in_time(p->dev_layers)) return;
     const auto fits = [&](int64_t n) { return largest <= n * 3 / 4; };
     // (a tag, a state, a strip's tag and its claim for every tile take the place of the residual sums' partials)
     if (!fits(places) || narrow * 4 > (int64_t)items.size() || items.size() > p->items_rows.size()) return;

@@ -740,19 +740,29 @@ __device__ __forceinline__ void held_tile_select(const WorkItem& it, const HeldA
 {
     const DevLayer& L = h.layers[it.layer];
     const double* const sums = x.colpart + L.colpart_off;
-    for (int g = threadIdx.x; g < L.G; g += kBlock) {
-        const double* const c = sums + (int64_t)g * L.khw;
-        double acc = 0.0;
-        int t = 0;
-        for (; t + 9 <= L.khw; t += 9) {                         // (a 3 x 3 kernel's in one go)
-            double y[9];
+    if (L.khw == 1) {
+        constexpr int B = kTopkInFlight;
+        for (int g0 = (int)threadIdx.x; g0 < L.G; g0 += B * kBlock) {
+            double y[B];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) y[i] = get_agent(&c[t + i]);
+            for (int i = 0; i < B; ++i) y[i] = g0 + i * kBlock < L.G ? get_agent(&sums[g0 + i * kBlock]) : 0.0;
 #pragma unroll
-            for (int i = 0; i < 9; ++i) acc += y[i];
+            for (int i = 0; i < B; ++i)
+                if (g0 + i * kBlock < L.G) put_agent(&key[L.group_base + g0 + i * kBlock], y[i]);
         }
-        for (; t < L.khw; ++t) acc += get_agent(&c[t]);
-        put_agent(&key[L.group_base + g], acc);
+    } else {
+        for (int g = threadIdx.x; g < L.G; g += kBlock) {
+            const double* const c = sums + (int64_t)g * L.khw;
+            double acc = 0.0;
+            for (int t = 0; t < L.khw; t += 9) {                 // (a 3 x 3 kernel's in one go; a zero added to a sum of squares leaves it)
+                double y[9];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) y[i] = t + i < L.khw ? get_agent(&c[t + i]) : 0.0;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) acc += y[i];
+            }
+            put_agent(&key[L.group_base + g], acc);
+        }
     }
     stores_arrived();
     __syncthreads();

@@ -87,6 +87,7 @@ struct TopkShared {
 // Keys of a layer as seen by the selection: in registers (G <= 8 * the workgroup's threads) or re-read from memory.
 // NT: the threads of the workgroup that selects.  AGENT: the keys were written inside this launch, by workgroups on other
 // compute units, and are read past the caches that may hold older values.
+constexpr int kTopkInFlight = 8;            // ... and those of a thread in flight together where they are read again and again
 template <int NT, bool INREG, bool AGENT>
 struct LayerKeys {
     unsigned long long kreg[kTopkRegs];
@@ -118,6 +119,15 @@ struct LayerKeys {
             for (int i = 0; i < kTopkRegs; ++i) {
                 const int g = (int)threadIdx.x + i * NT;
                 if (g < G) f(g, kreg[i]);
+            }
+        } else if (AGENT) {
+            for (int g0 = (int)threadIdx.x; g0 < G; g0 += kTopkInFlight * NT) {
+                unsigned long long x[kTopkInFlight];
+#pragma unroll
+                for (int i = 0; i < kTopkInFlight; ++i) x[i] = (g0 + i * NT < G) ? at(g0 + i * NT) : 0ull;
+#pragma unroll
+                for (int i = 0; i < kTopkInFlight; ++i)
+                    if (g0 + i * NT < G) f(g0 + i * NT, x[i]);
             }
         } else {
             for (int g = threadIdx.x; g < G; g += NT) f(g, at(g));

@@ -18,14 +18,14 @@ F, C, N = wk.MODE_FILTER, wk.MODE_CHANNEL, wk.MODE_NONE
 EDGES = [(700, 1, 1, F, 300), (260, 2, 1, F, 7), (2600, 4, 1, F, 1300), (90, 5, 1, F, 90), (300, 7, 9, F, 100),
          (64, 64, 1, F, 1), (129, 65, 1, F, 64), (40, 255, 1, F, 39), (37, 256, 1, F, 12), (33, 2047, 1, F, 20),
          (18, 2048, 1, F, 5), (21, 2049, 1, F, 11), (1, 512, 9, F, 1), (19, 1024, 9, F, 9), (7, 9215, 1, F, 3),
-         (9, 10240, 1, F, 4), (30, 100, 1, N, 30), (3, 2050, 1, N, 3)]
+         (9, 10240, 1, F, 4), (30, 100, 1, N, 30), (3, 2050, 1, N, 3), (300, 6144, 1, F, 120)]   # (size, for the 2600 groups)
 
 
 # tiles of 64 rows by 256 columns (64 of a ragged row): one row, one strip, channels across strips, more channels than the
 # selection ranks from registers, one and all channels kept
 TILES = [(1, 4, 1, C, 2), (63, 8, 1, C, 1), (64, 64, 4, C, 30), (65, 65, 4, C, 64), (129, 28, 9, C, 28), (200, 60, 9, C, 25),
          (64, 86, 6, C, 40), (70, 2500, 1, C, 1200), (130, 512, 9, C, 200), (17, 23, 3, C, 5), (40, 100, 1, N, 40),
-         (3, 2050, 1, N, 3)]
+         (3, 2050, 1, N, 3), (256, 512, 9, C, 200)]              # (size, for the 2500 groups)
 
 
 @pytest.fixture(params=["", "0"], ids=["patient", "impatient"])
@@ -271,4 +271,37 @@ def test_the_largest_layers_find_their_places(shape, monkeypatch):
     assert _launches(r.plan, r.project_compact) == {"project_pass1": 1}
     assert _early(r.ws) == 0
     assert np.array_equal(r.dmask.cpu().numpy(), ref["mask"])
+    r.close()
+
+
+@pytest.mark.parametrize("mode", [F, C], ids=["filter", "channel"])
+@pytest.mark.parametrize("groups,size,one", [(2048, 0, True), (2304, 255, False), (2304, 256, True), (16384, 14336, True),
+                                             (16388, 14340, False)])
+def test_layers_of_many_groups_wait_only_where_their_selection_is_worth_it(mode, groups, size, one, monkeypatch):
+    """A layer of more groups than the selecting workgroup ranks from registers, in plans of `size` times 4096 elements beside
+    it, on either side of both lines of the rule."""
+    from tests.gpu_harness import GpuRun, check_against_oracle
+    for name in ("HSADMM_NO_ESTIMATE", "HSADMM_FORCE_ESTIMATE", "HSADMM_HELD_PATIENCE"):
+        monkeypatch.delenv(name, raising=False)
+    unit, few = (4 if mode == F else 64), 4096                   # floats a group; columns of the other layers
+    own = groups * unit
+    rest = max(0, size * 4096 - own)
+    shapes = [(groups, unit, 1, mode, groups // 3) if mode == F else (unit, groups, 1, mode, groups // 3)]
+    while rest > 0:                                              # ... other layers make up the size, the last one a part
+        rows = min(512, -(-rest // few)) if rest >= few else 1
+        cols = few if rest >= few else rest // 4 * 4
+        rows = min(rows, rest // cols)
+        shapes.append((rows, cols // 4, 4, mode, max(1, (rows if mode == F else cols // 4) // 2)))
+        rest -= rows * cols
+    wl = wk.custom_workload(shapes, R=1, seed=6, sigma_replica=0.03)
+    assert sum(l.n for l in wl.layers) // 4096 == max(size, own // 4096)
+    W, U = wk.generate(wl, threads=8)
+    t = wl.table()
+    ref = oracle.project(t, W, U, want_wbar=True)
+    r = GpuRun(wl, W, U)
+    got = _launches(r.plan, lambda: r.step(fused=True))
+    assert (got.get("select_topk", 0) == 0) == one, got
+    rep = check_against_oracle(wl, r.outputs(), ref, oracle.compact(t, ref["Z"], ref["mask"]))
+    assert all(v == 0 for v in rep.values()), rep
+    assert _early(r.ws) == 0
     r.close()
