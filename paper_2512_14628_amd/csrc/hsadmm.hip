@@ -61,10 +61,10 @@
 #include <cstdlib>
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <new>
-#include <random>
 #include <type_traits>
 #include <vector>
 
@@ -645,14 +645,20 @@ void lay_out_held_tiles(hsadmm_plan* p, int64_t places, int64_t places_two)
     p->items_theld.insert(p->items_theld.end(), p->items_none.begin(), p->items_none.end());
 }
 
-// A number for a call of project_held that no other call has and no other content of the scratch can equal: a negative
+// A number for a call of a held kernel that no other call has and no other content of the scratch can equal: a negative
 // NaN's bits (the scratch holds sums of squares and whole numbers otherwise) with 50 bits of a counter that starts
-// anywhere.
-unsigned long long held_number()
+// anywhere (the clocks and where the library lies, mixed by splitmix64's finaliser: nothing here can fail or throw).
+unsigned long long held_number() noexcept
 {
-    static const unsigned long long start =
-        ((unsigned long long)std::random_device{}() << 32) ^ (unsigned long long)std::random_device{}();
     static std::atomic<unsigned long long> calls{0};
+    static const unsigned long long start = [] () noexcept {
+        unsigned long long x = (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count();
+        x = x * 0x9E3779B97F4A7C15ull + (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count();
+        x += (unsigned long long)reinterpret_cast<uintptr_t>(&calls);
+        x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+        x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+        return x ^ (x >> 31);
+    }();
     return 0xFFF4000000000000ull | ((start + 4 * calls.fetch_add(1, std::memory_order_relaxed)) & 0x3FFFFFFFFFFFCull);
 }
 

@@ -297,6 +297,15 @@ def lib_handle():
     return pkg.load_library()
 
 
+def test_nothing_that_throws_by_itself_is_called():
+    """No exception crosses the C boundary: beside allocations (caught where plans are made), the library takes nothing from the
+    C++ runtime that reports its failures by throwing."""
+    import subprocess
+    names = subprocess.check_output(["nm", "-D", "-C", "--undefined-only", binding.LIB_PATH], text=True)
+    for word in ("random_device", "std::thread", "std::locale", "basic_ios", "std::filesystem"):
+        assert word not in names, word
+
+
 def test_bench_refuses_more_than_one_gpu():
     """This build has no collectives: bench.py --gpus N with N > 1 exits with a message instead of running."""
     import subprocess
