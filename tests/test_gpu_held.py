@@ -45,6 +45,21 @@ def _launches(plan, call):
     return got
 
 
+def _weighted_launches(wl, W, U, a, b):
+    from tests.gpu_harness import GpuRun
+    r = GpuRun(wl, W, U)
+    pkg.hsadmm_plan_set_node_weights(r.plan, a, b)
+    Zg, Vd = torch.zeros_like(r.dU), torch.zeros_like(r.dU)
+    got = _launches(r.plan, lambda: pkg.hsadmm_project_weighted_compact(r.plan, r.dW, r.dU, Zg, Vd, r.dZ, None, r.dmask, None,
+                                                                        r.dpacked, r.doff, r.dkept, r.ws))
+    r.close()
+    return got
+
+
+def _tiles(wl):
+    return sum(-(-l.c_out // 64) * -(-l.c_in * l.khw // (64 if l.c_in * l.khw % 4 else 256)) for l in wl.layers if l.mode == C)
+
+
 def _early(ws):
     """Items that the last call wrote before their selection was known: their state words are its number (a negative NaN's
     pattern, a multiple of four) and 2 or 3."""
@@ -112,6 +127,7 @@ def test_edges_with_the_full_candidate(R, patience):
     a, b = rng.uniform(0.3, 1.0, L).astype(np.float32), rng.uniform(0.0, 0.7, L).astype(np.float32)
     for one_call in (True, False):
         _phase4_chain(wl, W, U, a, b, rng, fused_dual=True, one_call=one_call)
+    assert _weighted_launches(wl, W, U, a, b) == {"weighted_pass1": 1}
 
 
 @pytest.mark.parametrize("R", [1, 2, 3, 4, 8])
@@ -130,6 +146,8 @@ def test_tiles_of_channel_groups(R, patience):
     r = GpuRun(wl, W, U)
     assert _launches(r.plan, r.project_compact) == {"project_pass1": 1}
     r.close()
+    # (eight replicas: fewer than 80 tiles keep the other path)
+    assert (_weighted_launches(wl, W, U, a, b) == {"weighted_pass1": 1}) == (R != 8 or _tiles(wl) >= 80)
 
 
 @pytest.mark.parametrize("n_layers", [1, 40])
@@ -304,4 +322,87 @@ def test_layers_of_many_groups_wait_only_where_their_selection_is_worth_it(mode,
     rep = check_against_oracle(wl, r.outputs(), ref, oracle.compact(t, ref["Z"], ref["mask"]))
     assert all(v == 0 for v in rep.values()), rep
     assert _early(r.ws) == 0
+    r.close()
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["step", "weighted"])
+@pytest.mark.parametrize("mode", [F, C], ids=["filter", "channel"])
+def test_values_that_are_not_finite_fare_as_in_separate_launches(mode, weighted, monkeypatch):
+    """Infinities, NaN, zeros of both signs, the smallest and largest magnitudes and layers of zeros (every key tied): the one
+    launch against the launches it takes the place of, bit for bit where a value is not NaN."""
+    monkeypatch.delenv("HSADMM_FORCE_ESTIMATE", raising=False)
+    shapes = [(96, 64, 9, mode, 40), (130, 256, 1, mode, 60), (64, 48, 1, mode, 48 if mode == C else 64), (40, 100, 1, mode, 3)]
+    wl = wk.custom_workload(shapes, R=3, seed=17, sigma_replica=0.03)
+    W, U = (np.array(x) for x in wk.generate(wl))
+    rng = np.random.default_rng(2)
+    for l, values in ((wl.layers[0], [np.inf, -np.inf, 0.0, -0.0, 1e-45, 3e38]), (wl.layers[1], [np.nan, np.inf, -3e38, 1e-40])):
+        at = l.elem_off + rng.choice(l.n, 4 * len(values), replace=False)
+        W[:, at] = np.float32(values * 4)
+        U[l.elem_off + rng.choice(l.n, len(values), replace=False)] = np.float32(values)
+    last = wl.layers[-1]
+    W[:, last.elem_off:last.elem_off + last.n] = 0.0
+    U[last.elem_off:last.elem_off + last.n] = 0.0
+    n, dev = wl.n_arena, torch.device("cuda:0")
+    zv = rng.standard_normal((2, n)).astype(np.float32)
+
+    def outputs(held):
+        if held:
+            monkeypatch.delenv("HSADMM_NO_ESTIMATE", raising=False)
+        else:
+            monkeypatch.setenv("HSADMM_NO_ESTIMATE", "1")
+        plan = pkg.Plan(wl.table())
+        dW = [torch.from_numpy(np.ascontiguousarray(w)).to(dev) for w in W]
+        Zg, Vd = (torch.from_numpy(x.copy()).to(dev) for x in zv)
+        out = {"U": torch.from_numpy(U.copy()).to(dev), "Z": torch.zeros(n, device=dev),
+               "mask": torch.zeros(plan.groups_total, dtype=torch.uint8, device=dev),
+               "packed": torch.zeros(plan.packed_capacity_elems, device=dev),
+               "off": torch.zeros(plan.n_layers + 1, dtype=torch.int64, device=dev),
+               "kept": torch.zeros(plan.groups_total, dtype=torch.int32, device=dev)}
+        ws = torch.zeros(plan.workspace_bytes, dtype=torch.uint8, device=dev)
+        rest = (out["Z"], None, out["mask"], None, out["packed"], out["off"], out["kept"], ws)
+        if weighted:
+            pkg.hsadmm_plan_set_node_weights(plan, [0.6] * 4, [0.3] * 4)
+            got = _launches(plan, lambda: pkg.hsadmm_project_weighted_compact(plan, dW, out["U"], Zg, Vd, *rest))
+        else:
+            got = _launches(plan, lambda: pkg.hsadmm_project_compact(plan, dW, out["U"], *rest))
+        assert (sum(got.values()) == 1) == held, got
+        plan.close()
+        return {k: v.cpu().numpy() for k, v in out.items()}
+
+    one, several = outputs(True), outputs(False)
+    for name, got in one.items():
+        want = several[name]
+        if got.dtype == np.float32:
+            assert np.array_equal(np.isnan(got), np.isnan(want)), name
+            got, want = (np.where(np.isnan(x), np.float32(0), x).view(np.uint32) for x in (got, want))
+        assert np.array_equal(got, want), name
+
+
+@pytest.mark.parametrize("weighted", [False, True], ids=["step", "weighted"])
+@pytest.mark.parametrize("shape", [(1024, 64, 1, F, 400), (64, 1024, 1, F, 30), (512, 64, 9, C, 30)], ids=["short", "long", "tiles"])
+@pytest.mark.parametrize("whole", [0, 1, 3, 12, 60])
+def test_tags_and_states_stay_in_their_part_of_the_scratch(shape, weighted, whole, monkeypatch):
+    """Few and many unconstrained layers beside a held one: the words of this call lie within four words a row item."""
+    from tests.gpu_harness import GpuRun
+    for name in ("HSADMM_NO_ESTIMATE", "HSADMM_FORCE_ESTIMATE", "HSADMM_HELD_PATIENCE"):
+        monkeypatch.delenv(name, raising=False)
+    wl = wk.custom_workload([shape] + [(70, 64, 1, N, 70)] * whole, R=2, seed=9, sigma_replica=0.03)
+    W, U = wk.generate(wl)
+    r = GpuRun(wl, W, U)
+    if weighted:
+        pkg.hsadmm_plan_set_node_weights(r.plan, [1.0] * len(wl.layers), [0.0] * len(wl.layers))
+        zeros = torch.zeros_like(r.dU)
+        got = _launches(r.plan, lambda: pkg.hsadmm_project_weighted_compact(r.plan, r.dW, r.dU, zeros, zeros, r.dZ, None, r.dmask,
+                                                                            None, r.dpacked, r.doff, r.dkept, r.ws))
+    else:
+        got = _launches(r.plan, r.project_compact)
+    words = r.ws.cpu().numpy()[:r.ws.numel() // 8 * 8].view(np.uint64)
+    at = np.flatnonzero((words >> np.uint64(50)) == 0x3FFD)
+    if sum(got.values()) == 1:                                   # (else there was no room, and none was taken)
+        held = pkg.hsadmm_kernel_grids(r.plan)["weighted_pass1" if weighted else "project_pass1"]
+        assert _launches(r.plan, lambda: r.compact(cached=True)) == {"compact_gather": 1}     # a workgroup a row item
+        assert at.size > 0 and at[-1] - at[0] < 4 * pkg.hsadmm_kernel_grids(r.plan)["compact_gather"], held
+    else:
+        assert at.size == 0
+    assert np.array_equal(r.dmask.cpu().numpy(), oracle.project(wl.table(), W, U)["mask"])
     r.close()
