@@ -41,6 +41,18 @@ def kernel_source_digest():
     return h.hexdigest()
 
 
+def pass1_bytes(wl, one_launch, packs):
+    """Algorithmic bytes of project_pass1.  one_launch: it makes the selection itself, writes every layer's outputs and (packs)
+    packs what it keeps.  Otherwise it is charged with what it must move itself: on FILTER and unconstrained layers all of the
+    projection's traffic (R replicas + U in, Z + U out), on layers whose outputs a later pass writes (CHANNEL, BOTH) only
+    its reads and the mean it parks for that pass (CHANNEL: from 3 replicas on)."""
+    import workloads as wk
+    if one_launch:
+        return 4 * wl.n_total * (wl.R + 3) + (4 * wl.n_kept if packs else 0)
+    parked = {wk.MODE_CHANNEL: 1 + (1 if wl.R >= 3 else 0), wk.MODE_BOTH: 2}
+    return sum(4 * l.n * (wl.R + parked.get(l.mode, 3)) for l in wl.layers)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -378,22 +390,11 @@ def main():
 
     # algorithmic bytes each kernel is charged with (per launch)
     nk = wl.n_kept
-    # pass 1 is charged with what it must move itself: on FILTER and unconstrained layers all of the projection's
-    # traffic (R replicas + U in, Z + U out); on layers whose outputs a later pass writes (CHANNEL, BOTH) only its
-    # reads and the mean it parks for that pass (CHANNEL: from 3 replicas on)
-    def pass1_bytes(l):
-        if l.mode == wk.MODE_CHANNEL:
-            return 4 * l.n * (wl.R + 1 + (1 if wl.R >= 3 else 0))
-        if l.mode == wk.MODE_BOTH:
-            return 4 * l.n * (wl.R + 2)
-        return 4 * l.n * (wl.R + 3)
     kernel_bytes = {
-        "project_pass1": sum(pass1_bytes(l) for l in wl.layers),
+        "project_pass1": pass1_bytes(wl, not launches_per_step.get("select_topk"), one_call),
         "compact_gather": bytes_["compact"],
         "expand_scatter": bytes_["expand"],
     }
-    if one_call and not launches_per_step.get("select_topk"):     # one launch that selects, and packs what it keeps
-        kernel_bytes["project_pass1"] += 4 * nk
     dom = max(kernel_us_per_step, key=lambda k: kernel_us_per_step[k])
     dom_us = per_launch_us[dom]
     achieved = kernel_bytes.get(dom, 0) / (dom_us * 1e-6) / 1e9 if dom_us else 0.0

@@ -76,3 +76,18 @@ def test_the_shared_module_holds_none_of_the_methods_arithmetic():
     used |= {n.attr for n in ast.walk(tree) if isinstance(n, ast.Attribute)}
     assert not used & {"argsort", "argpartition", "partition", "sort", "cumsum", "linalg", "norm", "mean", "average",
                        "topk", "oracle", "paper_2512_14628_amd"}
+
+
+@pytest.mark.parametrize("mode", [wk.MODE_FILTER, wk.MODE_CHANNEL, wk.MODE_BOTH])
+@pytest.mark.parametrize("R", [1, 2, 4])
+def test_bytes_the_benchmark_charges_the_first_pass_with(mode, R):
+    """A launch that selects by itself writes both outputs of every layer and packs; one that another pass follows is charged
+    with what it moves itself."""
+    import bench
+    wl = wk.custom_workload([(8, 6, 1, mode, 4) + ((3,) if mode == wk.MODE_BOTH else ()), (5, 4, 1, wk.MODE_NONE, 5)], R=R)
+    n = 48 + 20
+    kept = {wk.MODE_FILTER: 4 * 6, wk.MODE_CHANNEL: 8 * 4, wk.MODE_BOTH: 4 * 3}[mode] + 20
+    assert bench.pass1_bytes(wl, True, False) == 4 * n * (R + 3)
+    assert bench.pass1_bytes(wl, True, True) == 4 * n * (R + 3) + 4 * kept
+    own = {wk.MODE_FILTER: 3, wk.MODE_CHANNEL: 2 if R >= 3 else 1, wk.MODE_BOTH: 2}[mode]
+    assert bench.pass1_bytes(wl, False, True) == 4 * 48 * (R + own) + 4 * 20 * (R + 3)
