@@ -558,7 +558,7 @@ bool selects_in_time(const std::vector<DevLayer>& layers)
 // unconstrained layers only, rows of at most kHeldSlots chunks per lane, and every layer's items on the chip at once
 // with a quarter of the places to spare, as a layer that takes them all leaves no one to load while it waits.  Without /
 // with, us: bottleneck 3-4-23-3 of width 96 (768 items in the largest layer) 512 / 511, 719 / 686, 967 / 937 with 1, 4, 8
-// replicas; 3-4-6-3 of width 112 (896 items) 414 / 434, 587 / 598, 800 / 838.
+// replicas; 3-4-6-3 of width 112 (896 items, projection alone) 351 / 348, 525 / 511 with 1 and 4.
 // places: workgroups on the chip at once.
 void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& out, int32_t& n_held)
 {
@@ -570,48 +570,58 @@ void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& o
         any_filter = any_filter || d.mode == HSADMM_MODE_FILTER;
     }
     if (!any_filter || !selects_in_time(p->dev_layers)) return;
+    // (what a layer's rows take: lanes, slots)
+    struct Lanes { int lpr, cpr; };
+    const auto lanes = [](const DevLayer& d) {
+        const bool vec = (d.row_len % 4) == 0;
+        const int nchunk = d.row_len / 4;
+        const int lpr = d.row_len >= kWideRow ? kBlock : lanes_of(vec ? nchunk : std::max(4, nchunk));
+        return Lanes{lpr, (nchunk + lpr - 1) / lpr + (vec ? 0 : 1)};
+    };
+    const auto item_rows = [](const Lanes& x, int want) { return std::min(std::max(1, want / x.cpr) * (kBlock / x.lpr), kHeldRows); };
     // the fewest slots with which the whole plan is on the chip at once, or, if it never is, all of them
-    for (int want = 1; want <= kHeldSlots; ++want) {
-        std::vector<WorkItem> items;
-        for (size_t l = 0; l < p->dev_layers.size(); ++l) {
-            const DevLayer& d = p->dev_layers[l];
+    int want = 1;
+    for (; want <= kHeldSlots; ++want) {
+        int64_t total = 0;
+        for (const DevLayer& d : p->dev_layers) {
             if (d.mode != HSADMM_MODE_FILTER) continue;
-            const bool vec = (d.row_len % 4) == 0;
-            const int nchunk = d.row_len / 4;
-            const int lpr = d.row_len >= kWideRow ? kBlock : lanes_of(vec ? nchunk : std::max(4, nchunk));
-            const int cpr = (nchunk + lpr - 1) / lpr + (vec ? 0 : 1);
-            if (cpr > kHeldSlots) return;
-            const int at_once = kBlock / lpr;
-            const int rows = std::min((int)std::max(1, want / cpr) * at_once, kHeldRows);
-            const int64_t n = (d.c_out + rows - 1) / rows;
-            if (want == kHeldSlots && (n > places * 3 / 4)) return;
-            const int64_t first = (int64_t)items.size();
-            for (int r0 = 0; r0 < d.c_out; r0 += rows) {
-                WorkItem it{};
-                it.base = d.elem_off + (int64_t)r0 * d.row_len;
-                it.aux = first | (n << 32);
-                it.g0 = d.group_base + r0;
-                it.nr = std::min(rows, d.c_out - r0);
-                it.row_len = d.row_len;
-                it.lpr = lpr;
-                it.flags = HSADMM_MODE_FILTER | (vec ? 4 : 0);
-                it.khw = cpr;
-                it.layer = (int)l;
-                it.row0 = r0;
-                it.k = d.k;
-                it.packed_off = d.packed_off;
-                items.push_back(it);
-            }
+            const Lanes x = lanes(d);
+            if (x.cpr > kHeldSlots) return;
+            const int64_t n = (d.c_out + item_rows(x, want) - 1) / item_rows(x, want);
+            if (want == kHeldSlots && n > places * 3 / 4) return;
+            total += n;
         }
-        if (want < kHeldSlots && (int64_t)items.size() > places) continue;
+        if (want < kHeldSlots && total > places) continue;
         // (a tag for every item and a state for the held ones take the place of the residual sums' partials: four words a
         // row item)
-        if (2 * items.size() + p->items_none.size() > 4 * p->items_rows.size()) continue;
-        n_held = (int32_t)items.size();
-        out = std::move(items);
-        out.insert(out.end(), p->items_none.begin(), p->items_none.end());
-        return;
+        if (2 * total + (int64_t)p->items_none.size() <= 4 * (int64_t)p->items_rows.size()) break;
     }
+    if (want > kHeldSlots) return;
+    for (size_t l = 0; l < p->dev_layers.size(); ++l) {
+        const DevLayer& d = p->dev_layers[l];
+        if (d.mode != HSADMM_MODE_FILTER) continue;
+        const Lanes x = lanes(d);
+        const int rows = item_rows(x, want);
+        const int64_t n = (d.c_out + rows - 1) / rows, first = (int64_t)out.size();
+        for (int r0 = 0; r0 < d.c_out; r0 += rows) {
+            WorkItem it{};
+            it.base = d.elem_off + (int64_t)r0 * d.row_len;
+            it.aux = first | (n << 32);
+            it.g0 = d.group_base + r0;
+            it.nr = std::min(rows, d.c_out - r0);
+            it.row_len = d.row_len;
+            it.lpr = x.lpr;
+            it.flags = HSADMM_MODE_FILTER | ((d.row_len % 4) == 0 ? 4 : 0);
+            it.khw = x.cpr;
+            it.layer = (int)l;
+            it.row0 = r0;
+            it.k = d.k;
+            it.packed_off = d.packed_off;
+            out.push_back(it);
+        }
+    }
+    n_held = (int32_t)out.size();
+    out.insert(out.end(), p->items_none.begin(), p->items_none.end());
 }
 
 // Weighted steps with eight replicas load a tile's rows one at a time (two spill), which few tiles do not hide: plain networks of
