@@ -184,6 +184,11 @@ struct ProjectArgs {
     double* colpart;  // CHANNEL partial column sums
     float inv_R;
     int park_mean;    // pass 1 parks the mean of a CHANNEL layer's replicas in Z (read back by the final pass)
+    // The compiler reads inv_R as the first of four floats where it multiplies four by it.  With a pointer among those bytes
+    // the kernel's copy of this structure did not come apart into registers: it went to LDS, at places that tiles_held computed from
+    // the launch's packet in host memory.  Weighted channel step, bottleneck 2-3-9-1 of width 12, 1 and 4 replicas, us: 61.6 / 51.4,
+    // 67.8 / 57.4; plain network of width 128, 1 replica 54.1 / 47.0.
+    float beside_inv_R[2];
     // weighted candidate of Eq. (9) (null / unused in the base projection)
     const float* Zg;      // global consensus z
     const float* Vd;      // inter-node dual v_i
