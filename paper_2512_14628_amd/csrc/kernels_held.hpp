@@ -40,7 +40,7 @@ constexpr long long kHeldPatience = 30000;
 // (slots) of a thread per row.
 struct HeldArgs {
     unsigned long long* tag;        // per held item: gen once the item's keys are published
-    unsigned long long* state;      // per held item: who finishes its rows if they were written too early (held_left_early)
+    unsigned long long* state;      // per held item: who finishes its rows if they were written too early (held_finish_early)
     unsigned long long gen;         // this call's number; neither it nor the three after it are any other call's, or a value
                                     // that anything else writes there
     long long patience;             // ticks
@@ -55,7 +55,7 @@ struct HeldArgs {
 // What the threads of a workgroup tell each other about rows written too early.
 struct HeldTurn {
     unsigned long long early[kWaves];
-    int mine;
+    unsigned long long was;
 };
 
 // LDS: slots whose dual waits here.
@@ -73,6 +73,7 @@ struct HeldShared {
 // A store has arrived before the tags are looked at, so the one whose store arrives last sees all the others'.
 __device__ __forceinline__ bool held_publish(const WorkItem& it, const HeldArgs& h)
 {
+    if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen);
     stores_arrived();
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -130,6 +131,7 @@ __device__ __forceinline__ void held_layer_entries(const WorkItem& it, const Hel
 }
 
 // Waits for the ranks of n groups (a thread each) from group g0 on -> rank (-1: pruned); false if the patience ran out first.
+// Behind it the ranks that this workgroup has stored have arrived, if it has selected.
 __device__ __forceinline__ bool held_wait_groups(int g0, int n, const HeldArgs& h, int* rank)
 {
     const int t = threadIdx.x;
@@ -143,55 +145,51 @@ __device__ __forceinline__ bool held_wait_groups(int g0, int n, const HeldArgs& 
         }
         rank[t] = r;
     }
+    stores_arrived();
     return __syncthreads_or(t < n && r == kNotSelected) == 0;
 }
 
 // Rows that were written before their selection was known.
 //
-// An item's state word says who finishes them.  It is changed by exchanges only: the item's workgroup leaves gen + 2 once its
-// rows lie in memory in their early form, the workgroup that has made the layer's selection leaves gen + 1 once the ranks lie
-// there.  Whoever finds the other's number came second and finishes the item; the selecting workgroup then marks it gen + 3.
-// Nobody waits for anybody, so there is nothing to give up, however long other work keeps a layer's last workgroups off the chip.
-__device__ __forceinline__ unsigned long long exchange_agent(unsigned long long* p, unsigned long long v)
+// An item's state word says who finishes them.  It is gen before the item's keys are published and then only gains bits: the
+// item's workgroup adds 2 once its rows lie in memory in their early form, a workgroup that has made the layer's selection adds
+// 1 once the ranks lie there.  The item's workgroup finishes what has a 1 before its 2, the first to add a 1 what has a 2.
+// Nobody waits for anybody, so there is nothing to give up, however long other work keeps a layer's last workgroups off the
+// chip.  (Two workgroups may both have selected: the second finds the first's 1.)
+__device__ __forceinline__ unsigned long long gain_agent(unsigned long long* p, unsigned long long bit)
 {
-    return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Called by the whole workgroup when it has stored its rows in their early form.  True: it finishes them itself.
-__device__ __forceinline__ bool held_left_early(const HeldArgs& h, HeldTurn& turn)
-{
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) turn.mine = exchange_agent(&h.state[blockIdx.x], h.gen + 2) == h.gen + 1;
-    __syncthreads();
-    return turn.mine != 0;
-}
-
-// Called by a whole workgroup that has selected for the layer whose items are first .. first + n - 1, behind its own rows: the
-// rows that were written too early are finished (finish).  claim: the word that the layer's complete keys were told by (gen), as
-// two workgroups may both have found them complete.
+// Called by the whole workgroup behind its own rows.  early: it has stored them in their early form; n: items of its layer, from the
+// first one on, if it has made their selection, else 0.  What is to be finished by it goes to finish.  (Told that this
+// is rare, the compiler spills for this code and not for the loads.  Plain network of width 24, channel groups, 1, 4, 8 replicas,
+// us, not told / told: 26.6 / 26.3, 31.3 / 29.6, 37.0 / 33.2.)
 template <typename F>
-__device__ __forceinline__ void held_finish_early(const WorkItem* __restrict__ items, const HeldArgs& h, int first, int n,
-                                                  unsigned long long* claim, HeldTurn& turn, F finish)
+__device__ __forceinline__ void held_finish_early(const WorkItem* __restrict__ items, const HeldArgs& h, bool early, int first, int n,
+                                                  HeldTurn& turn, F finish)
 {
-    stores_arrived();                                            // the ranks
-    __syncthreads();
-    if (threadIdx.x == 0) turn.mine = exchange_agent(claim, h.gen + 1) == h.gen;
-    __syncthreads();
-    if (turn.mine == 0) return;
-    for (int k0 = 0; k0 < n; k0 += kBlock) {
+    if (__builtin_expect(!early && n == 0, 1)) return;
+    for (int k0 = early ? -kBlock : 0; k0 < n; k0 += kBlock) {
+        const bool own = k0 < 0;
+        if (own) {
+            __threadfence();
+            __syncthreads();
+            if (threadIdx.x == 0) turn.was = gain_agent(&h.state[blockIdx.x], 2ull);
+            __syncthreads();
+        }
         const int k = k0 + (int)threadIdx.x;
-        const bool early = k < n && exchange_agent(&h.state[first + k], h.gen + 1) == h.gen + 2;
-        const unsigned long long b = __ballot(early);
+        const bool mine = own ? threadIdx.x == 0 && (turn.was & 1ull) != 0ull
+                              : k < n && gain_agent(&h.state[first + k], 1ull) == h.gen + 2ull;
+        const unsigned long long b = __ballot(mine);
         if ((threadIdx.x & (kWave - 1)) == 0) turn.early[threadIdx.x / kWave] = b;
-        if (__syncthreads_or(early) == 0) continue;
-        if (early) put_agent(&h.state[first + k], h.gen + 3);
+        if (__builtin_expect(__syncthreads_or(mine) == 0, 1)) continue;
         __threadfence();                                         // the rows as their workgroups left them
         for (int w = 0; w < kWaves; ++w) {
             unsigned long long m = turn.early[w];
             unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)m), hi = __builtin_amdgcn_readfirstlane((unsigned int)(m >> 32));
             for (m = ((unsigned long long)hi << 32) | lo; m != 0ull; m &= m - 1ull)
-                finish(items[first + k0 + w * kWave + __builtin_ctzll(m)]);
+                finish(items[own ? (int)blockIdx.x : first + k0 + w * kWave + __builtin_ctzll(m)]);
         }
         __syncthreads();                                         // (the masks may be written again)
     }
@@ -399,12 +397,8 @@ __device__ __forceinline__ void held_rows(const WorkItem* __restrict__ items, co
             if (++q == at.cpr) { q = 0; ++rd; }
         }
     }
-    if (!known && held_left_early(h, sh.turn)) held_rows_finish<WHOLE>(it, a, h);
-    if (selects) {
-        const int first = (int)(it.aux & 0xffffffffll);
-        held_finish_early(items, h, first, (int)(it.aux >> 32), &h.tag[first], sh.turn,
-                          [&](const WorkItem& x) { held_rows_finish<WHOLE>(x, a, h); });   // (a layer's rows are of one length)
-    }
+    held_finish_early(items, h, !known, (int)(it.aux & 0xffffffffll), selects ? (int)(it.aux >> 32) : 0, sh.turn,
+                      [&](const WorkItem& x) { held_rows_finish<WHOLE>(x, a, h); });   // (a layer's rows are of one length)
 }
 
 // The mappings of an unconstrained layer's rows: always kept, packed at their own index.
@@ -616,12 +610,8 @@ __device__ __forceinline__ void held_weighted_rows(const WorkItem* __restrict__ 
             }
         }
     }
-    if (!known && held_left_early(h, sh.turn)) held_weighted_finish<WHOLE>(it, a, h, x);
-    if (selects) {
-        const int first = (int)(it.aux & 0xffffffffll);
-        held_finish_early(items, h, first, (int)(it.aux >> 32), &h.tag[first], sh.turn,
-                          [&](const WorkItem& y) { held_weighted_finish<WHOLE>(y, a, h, x); });
-    }
+    held_finish_early(items, h, !known, (int)(it.aux & 0xffffffffll), selects ? (int)(it.aux >> 32) : 0, sh.turn,
+                      [&](const WorkItem& y) { held_weighted_finish<WHOLE>(y, a, h, x); });
 }
 
 template <int R>
@@ -692,6 +682,7 @@ __device__ __forceinline__ bool held_tile_publish(const WorkItem& it, const Held
     const int n_rb = h.layers[it.layer].n_rowblocks;
     const int strip = it.col0 / cols;
     const int first = it.lpr;
+    if (threadIdx.x == 0) put_agent(&h.state[blockIdx.x], h.gen);
     stores_arrived();
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -996,10 +987,8 @@ __device__ __forceinline__ void held_tile(const WorkItem* __restrict__ items, co
                 }
             }
         }
-    if (!known && held_left_early(h, sh.turn)) held_tile_finish<WEIGHTED, VEC>(it, a, h);
-    if (selects)
-        held_finish_early(items, h, it.lpr, tile_strips(it) * h.layers[it.layer].n_rowblocks, &x.strip_tag[it.lpr], sh.turn,
-                          [&](const WorkItem& y) { held_tile_finish<WEIGHTED, VEC>(y, a, h); });
+    held_finish_early(items, h, !known, it.lpr, selects ? tile_strips(it) * h.layers[it.layer].n_rowblocks : 0, sh.turn,
+                      [&](const WorkItem& y) { held_tile_finish<WEIGHTED, VEC>(y, a, h); });
 }
 
 template <int R, bool WEIGHTED>
