@@ -775,10 +775,17 @@ int hsadmm_kernel_timing_read(hsadmm_plan_t* plan, double* total_ms, int64_t* la
 int hsadmm_kernel_grid(const hsadmm_plan_t* plan, int kernel_id);
 /*
  * 1 if the un-predicted projection of this plan (hsadmm_project, hsadmm_project_compact, hsadmm_step without sel_prev,
- * dual in place) forms a prediction inside its first pass, else 0 (also for a NULL plan).  Plans of FILTER and
- * unconstrained layers whose rows can wait for their selection on the chip (rows of at most about 10 K floats, no layer larger
- * than about 7 M elements) need none: one launch makes the selection and writes every row once.  Of the
- * others, those of 20 Mi elements or more estimate: every FILTER layer's first rows (a sixteenth, 16 to 128)
+ * dual in place) forms a prediction inside its first pass, else 0 (also for a NULL plan).  Plans whose rows can wait for their
+ * selection on the chip need none: one launch makes the selection and writes every row once.  These are plans of FILTER and
+ * unconstrained layers, or of CHANNEL (without runs) and unconstrained layers, whose largest layer takes no more than three
+ * quarters of the workgroups that the chip holds at once.  An item of a FILTER layer is a workgroup's: at most 256 rows, at
+ * most ten chunks of four floats a thread, one row from about 5 K floats on (so at best a layer of about 7 M elements fits; rows
+ * of more than 10 K floats never do); an item of a CHANNEL layer is a tile of 64 rows by 256 columns (64 of a ragged row),
+ * and no more than a quarter of the tiles may be ragged.  A layer of more than 2048 groups has to be worth its selection: a
+ * group beyond them for every 4096 constrained elements of the plan, 16384 groups at most.  The weighted projection without
+ * residual norms (hsadmm_project_weighted, hsadmm_project_weighted_compact, hsadmm_step with Zg) takes the same form with fewer
+ * workgroups on the chip.  Of the other plans
+ * of FILTER and unconstrained layers, those of 20 Mi elements or more estimate: every FILTER layer's first rows (a sixteenth, 16 to 128)
  * are processed ahead of the rest, the key that the layer's keep ratio of them exceed estimates the layer's selection
  * threshold (Eq. (10) keeps the k largest norms), and every later row is written in the form its own key suggests --
  * kept, or pruned with the kept-form dual held in Z -- before the selection has been made.  The selection and the
@@ -790,8 +797,10 @@ int hsadmm_kernel_grid(const hsadmm_plan_t* plan, int kernel_id);
  * a call changes in a plan; every plan counts from a start of its own), so calls from several threads stay safe and
  * plans that take turns on one workspace do not read each other's keys.  A captured graph replays its call number: a
  * replay may then use the estimate an earlier replay left, which again changes no result.  Environment, read by
- * hsadmm_plan_create: HSADMM_NO_ESTIMATE (any value)
- * switches the estimate and the one launch off, HSADMM_FORCE_ESTIMATE takes the estimate whatever the size.
+ * hsadmm_plan_create: HSADMM_NO_ESTIMATE (any value) switches the estimate off and the one launch of every kind of plan,
+ * HSADMM_FORCE_ESTIMATE takes the estimate whatever the size and no one launch.  HSADMM_HELD_PATIENCE: how long rows wait for their
+ * selection in the one launch, in ticks of 10 ns (30000 without it; for tests); rows that have waited so long are written in
+ * a form that is finished once the selection is there, within the same launch.
  */
 int hsadmm_plan_estimates(const hsadmm_plan_t* plan);
 /* Name of a kernel id ("" when out of range). */
