@@ -131,6 +131,7 @@ struct hsadmm_plan {
     std::vector<WorkItem> items_held, items_wheld;
     int32_t n_held = 0, n_wheld = 0;
     // tiles_held: the tiles of the CHANNEL layers, then the row items of the unconstrained ones
+    int64_t wheld_ragged = 0;           // elements of a plan of few layers that are mostly ragged, else 0 (see ragged_weighted)
     std::vector<WorkItem> items_theld;
     int32_t n_theld = 0;
     bool theld_two = false;             // ... also where only two workgroups share a compute unit
@@ -624,6 +625,27 @@ void lay_out_held(const hsadmm_plan* p, int64_t places, std::vector<WorkItem>& o
     out.insert(out.end(), p->items_none.begin(), p->items_none.end());
 }
 
+// Ragged rows take a round trip more for their tails, five loads a chunk in the weighted form, and a plan of few layers has no
+// others to load meanwhile.  Weighted steps of plain networks (5 layers, most rows ragged), us, without / with held rows, 1, 4, 8
+// replicas: width 45 (0.26 M elements) 22.7 / 22.1, 23.2 / 24.5, 29.9 / 27.5; 61 (0.47 M) 22.6 / 24.9, 22.9 / 27.6, 30.7 / 31.8;
+// 101 (1.3 M) 30.0 / 33.6, 33.5 / 37.6, 52.0 / 45.0; 125 (2.0 M) 36.9 / 39.0, 41.0 / 45.5, 52.9 / 57.7; 139 (2.4 M) 41.0 / 42.3,
+// 47.3 / 50.6, 57.9 / 62.3; 187 (4.4 M) 62.5 / 58.1, 71.6 / 71.5, 95.8 / 90.6.  ResNet-18 of width 21 (1.3 M) 33.3 / 29.8, 36.9 / 32.9,
+// 50.9 / 37.6.
+constexpr int kHeldRaggedLayers = 8;
+int64_t ragged_weighted(const std::vector<DevLayer>& layers)
+{
+    int64_t n = 0, ragged = 0;
+    int count = 0;
+    for (const DevLayer& d : layers) {
+        if (d.mode != HSADMM_MODE_FILTER) continue;
+        ++count;
+        n += (int64_t)d.c_out * d.row_len;
+        if (d.row_len % 4 != 0) ragged += (int64_t)d.c_out * d.row_len;
+    }
+    return count <= kHeldRaggedLayers && 2 * ragged > n ? n : 0;
+}
+bool ragged_weighted_loses(int64_t n, int R) { return n >= (R == 8 ? 1600000 : 300000) && n < 3500000; }
+
 // Weighted steps with eight replicas load a tile's rows one at a time (two spill), which few tiles do not hide: plain networks of
 // width 64 (38 tiles) 54.0 us without, 59.2 with, 88 (79 tiles) 66.5 / 66.0, 112 (107) 75.9 / 71.2.
 constexpr int kHeldTilesWeighted8 = 80;
@@ -758,6 +780,7 @@ int hsadmm_plan_create_nested(const hsadmm_layer_t* layers, const hsadmm_nest_t*
             const auto places = [&](const void* kernel, int per_unit) { return (int64_t)compute_units * held_per_unit(kernel, per_unit); };
             lay_out_held(p, places((const void*)project_held<0>, kHeldPerUnit), p->items_held, p->n_held);
             lay_out_held(p, places((const void*)weighted_held<0>, kHeldWeightedPerUnit), p->items_wheld, p->n_wheld);
+            p->wheld_ragged = ragged_weighted(p->dev_layers);
             lay_out_held_tiles(p, places((const void*)tiles_held<0, false>, held_tile_per_unit(0, false)),
                                places((const void*)tiles_held<0, true>, held_tile_per_unit(0, true)));
         }
@@ -1450,7 +1473,7 @@ static int project_weighted_impl(const hsadmm_plan_t* p, const float* const* W_r
         return launch_tiles_held(p, true, w, R, mask, out ? *out : CompactOut{}, ws, s, sel_out) == hipSuccess ? HSADMM_OK
                                                                                                              : HSADMM_ERR_HIP;
     // rows that can wait for the selection on the chip: one launch (kernels_held.hpp)
-    if (sel_prev == nullptr && !residuals && p->n_wheld > 0) {
+    if (sel_prev == nullptr && !residuals && p->n_wheld > 0 && !ragged_weighted_loses(p->wheld_ragged, R)) {
         HeldArgs x;
         if (held_args(p, p->items_wheld.size(), p->n_wheld, mask, out ? *out : CompactOut{}, ws, s, sel_out, x) != hipSuccess)
             return HSADMM_ERR_HIP;

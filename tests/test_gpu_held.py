@@ -406,3 +406,20 @@ def test_tags_and_states_stay_in_their_part_of_the_scratch(shape, weighted, whol
         assert at.size == 0
     assert np.array_equal(r.dmask.cpu().numpy(), oracle.project(wl.table(), W, U)["mask"])
     r.close()
+
+
+@pytest.mark.parametrize("R,width,one", [(1, 45, True), (4, 61, False), (8, 61, True), (3, 139, False), (8, 139, False), (8, 187, True),
+                                         (4, 64, True)])
+def test_few_ragged_layers_keep_the_weighted_step_in_launches_of_its_own(R, width, one, monkeypatch):
+    """On either side of the sizes between which they do."""
+    from tests.test_gpu_weighted import _phase4_chain
+    for name in ("HSADMM_NO_ESTIMATE", "HSADMM_FORCE_ESTIMATE", "HSADMM_HELD_PATIENCE"):
+        monkeypatch.delenv(name, raising=False)
+    w = width
+    wl = wk.custom_workload([(w, 3, 9, F, w // 2), (2 * w, w, 9, F, w), (2 * w, 2 * w, 9, F, w), (4 * w, 2 * w, 9, F, 2 * w),
+                             (10, 4 * w, 1, F, 5)], R=R, seed=21, sigma_replica=0.03)
+    W, U = wk.generate(wl, threads=8)
+    rng = np.random.default_rng(R)
+    a, b = rng.uniform(0.3, 1.0, 5).astype(np.float32), rng.uniform(0.0, 0.7, 5).astype(np.float32)
+    assert (_weighted_launches(wl, W, U, a, b) == {"weighted_pass1": 1}) == one
+    _phase4_chain(wl, W, U, a, b, rng, fused_dual=True, one_call=True)
