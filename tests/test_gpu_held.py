@@ -2,7 +2,7 @@
 is one launch that makes the selection itself and writes every row once.  Every output against the oracle, at the edges of
 what a workgroup holds (rows of one to ten chunks a lane, ragged rows, one row to 256 rows an item, layers of one item and
 of more groups than the selection ranks from registers), and with no patience at all, so that rows are written before
-their selection is known and the workgroups behind finish them."""
+their selection is known and finished by whoever comes second."""
 import numpy as np
 import pytest
 import torch
